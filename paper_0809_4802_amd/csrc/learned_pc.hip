@@ -99,7 +99,37 @@ __global__ void features_kernel(int n, const int32_t* __restrict__ rowptr, const
         for (int q = 0; q < 16; ++q) dinv[(size_t)i * 16 + q] = float(Di[q]);
 }
 
+// Four consecutive values of a caller's array: one wide load that asks for no more than the
+// alignment of its entries.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef double f64x4u __attribute__((ext_vector_type(4), aligned(8)));
+__device__ __forceinline__ f32x4 load4(const float* p) { return *reinterpret_cast<const f32x4u*>(p); }
+__device__ __forceinline__ f32x4 load4(const double* p) {
+    const f64x4u v = *reinterpret_cast<const f64x4u*>(p);
+    return f32x4{float(v.x), float(v.y), float(v.z), float(v.w)};
+}
+
+// The network runs on the matrix cores (v_mfma_f32_16x16x4: FP32 inputs, products and sums), a
+// wave taking 16 nodes at a time.  With g = lane / 16 and c = lane % 16 the instruction takes
+// A[row c][k g], B[k g][column c] and keeps D[row 4g + i][column c] in register i.  The order
+// of the summed index is free, so a D of one product is the B (or A) of the next without moving
+// a value between lanes: register i of lane group g is simply index 4g + i.
+constexpr int kMlpNodes = 16;                 // nodes per wave and pass
+constexpr int kHidTiles = NHID / 16;          // 16-row tiles of the hidden layer
+constexpr int kInSteps = (NIN + 3) / 4;       // four inputs per instruction
+constexpr int kInTiles = (NIN + 1 + 15) / 16; // 16-column tiles of the inputs and the bias
+static_assert(NHID % 16 == 0 && NOUT == 16, "tiles of the network");
+
+__device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
 // MLP forward per node and P_i = D_i^-1 (I + Delta_i); hidden activations kept for backward.
+// One lane per node walked the 2,624 products serially with every weight read from LDS: 31 us
+// for 35,937 nodes, about half a wave per SIMD.  As 44 matrix instructions per 16 nodes (under
+// 2 us of arithmetic) it takes 12.5 us: the latency of the weights, the inputs and tanh.
+constexpr int kFwdBlocks = 512;               // workgroups at most: each wave loads the weights once
 template <typename TM>
 __global__ __launch_bounds__(kBlock) void forward_kernel(int n, const float* __restrict__ feats,
                                                          const float* __restrict__ wts,
@@ -107,228 +137,479 @@ __global__ __launch_bounds__(kBlock) void forward_kernel(int n, const float* __r
                                                          const uint8_t* __restrict__ dmask,
                                                          float* __restrict__ hid, TM* __restrict__ P,
                                                          int32_t* flags) {
-    __shared__ float w[NW];
-    for (int q = threadIdx.x; q < NW; q += blockDim.x) w[q] = wts[q];
-    __syncthreads();
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    float x[NIN];
-    for (int q = 0; q < NIN; ++q) x[q] = feats[(size_t)i * NIN + q];
-    float y[NOUT];
-    for (int o = 0; o < NOUT; ++o) y[o] = w[OFF_B2 + o];
-    for (int h = 0; h < NHID; ++h) {
-        float z = w[OFF_B1 + h];
-        for (int q = 0; q < NIN; ++q) z += w[OFF_W1 + h * NIN + q] * x[q];
-        const float a = tanhf(z);
-        if (hid) hid[(size_t)i * NHID + h] = a;
-        for (int o = 0; o < NOUT; ++o) y[o] += w[OFF_W2 + o * NHID + h] * a;
-    }
-    const uint32_t dm = dmask[i];
-    float M[16];
-    for (int r = 0; r < 4; ++r)
-        for (int c = 0; c < 4; ++c) {
-            const bool masked = (dm & (1u << r)) || (dm & (1u << c));
-            M[r * 4 + c] = (r == c ? 1.f : 0.f) + (masked ? 0.f : y[r * 4 + c]);
+    __shared__ __align__(16) float sm[kBlock / 64][kMlpNodes][NOUT + 4];   // I + Delta of a wave's nodes
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int g = lane >> 4, c = lane & 15;
+    float w1[kHidTiles][kInSteps], w2[kHidTiles][4];
+    f32x4 b1[kHidTiles], b2;
+#pragma unroll
+    for (int t = 0; t < kHidTiles; ++t) {
+#pragma unroll
+        for (int k = 0; k < kInSteps; ++k) {
+            const int f = 4 * k + g;
+            w1[t][k] = f < NIN ? wts[OFF_W1 + (16 * t + c) * NIN + min(f, NIN - 1)] : 0.f;
         }
-    bool finite = true;
-    for (int r = 0; r < 4; ++r)
-        for (int c = 0; c < 4; ++c) {
-            float s = 0.f;
-            for (int k = 0; k < 4; ++k) s += dinv[(size_t)i * 16 + r * 4 + k] * M[k * 4 + c];
-            finite = finite && isfinite(s);
-            P[(size_t)i * 16 + r * 4 + c] = TM(s);
-        }
-    if (!finite) atomicAdd(&flags[3], 1);
-}
-
-// t = P r (node-local 4x4 products)
-__global__ void block_apply_kernel(int n, const float* __restrict__ P, const float* __restrict__ r,
-                                   float* __restrict__ t) {
-    const int tid = blockIdx.x * blockDim.x + threadIdx.x;
-    const int i = tid >> 2, q = tid & 3;
-    if (i >= n) return;
-    const float* p = P + (size_t)i * 16 + q * 4;
-    const float* v = r + (size_t)i * 4;
-    t[tid] = p[0] * v[0] + p[1] * v[1] + p[2] * v[2] + p[3] * v[3];
-}
-
-// y = b - A x (MODE 0) or y = A^T x (MODE 1, via the transposed-block map), FP32 vectors.
-template <typename TA, int MODE>
-__global__ void spmv_f32_kernel(int n, const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colidx,
-                                const int32_t* __restrict__ tpos, const TA* __restrict__ A,
-                                const float* __restrict__ x, const float* __restrict__ b, float* __restrict__ y) {
-    const int tid = blockIdx.x * blockDim.x + threadIdx.x;
-    const int row = tid >> 2, r = tid & 3;
-    if (row >= n) return;
-    float acc = 0.f;
-    for (int k = rowptr[row]; k < rowptr[row + 1]; ++k) {
-        const float* xv = x + (size_t)colidx[k] * 4;
-        if (MODE == 0) {
-            const TA* a = A + (size_t)k * 16 + r * 4;
-            acc += float(a[0]) * xv[0] + float(a[1]) * xv[1] + float(a[2]) * xv[2] + float(a[3]) * xv[3];
-        } else {
-            const TA* a = A + (size_t)tpos[k] * 16 + r;   // column r of the block (col, row)
-            acc += float(a[0]) * xv[0] + float(a[4]) * xv[1] + float(a[8]) * xv[2] + float(a[12]) * xv[3];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            w2[t][i] = wts[OFF_W2 + c * NHID + 16 * t + 4 * g + i];
+            b1[t][i] = wts[OFF_B1 + 16 * t + 4 * g + i];
         }
     }
-    y[tid] = MODE == 0 ? b[tid] - acc : acc;
-}
-
-// sums of squares of two vectors, per workgroup: part[b] and part[gridDim.x + b] (no atomics,
-// so that training is reproducible run to run; sumsq2_finalize_kernel adds them in order)
-__global__ __launch_bounds__(kBlock) void sumsq2_kernel(int n, const float* __restrict__ a,
-                                                        const float* __restrict__ b, double* __restrict__ part) {
-    double sa = 0.0, sb = 0.0;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-        sa += double(a[i]) * double(a[i]);
-        sb += double(b[i]) * double(b[i]);
-    }
-    for (int off = 32; off > 0; off >>= 1) {
-        sa += __shfl_down(sa, off, 64);
-        sb += __shfl_down(sb, off, 64);
-    }
-    __shared__ double ls[2][kBlock / 64];
-    if ((threadIdx.x & 63) == 0) {
-        ls[0][threadIdx.x >> 6] = sa;
-        ls[1][threadIdx.x >> 6] = sb;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double ta = 0.0, tb = 0.0;
-        for (int w = 0; w < kBlock / 64; ++w) {
-            ta += ls[0][w];
-            tb += ls[1][w];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) b2[i] = wts[OFF_B2 + 4 * g + i];
+    const int waves = gridDim.x * (kBlock / 64);
+    // every wave of the workgroup makes the same number of passes (the barriers below)
+    for (int64_t n0 = (int64_t)blockIdx.x * (kBlock / 64) * kMlpNodes; n0 < n; n0 += (int64_t)waves * kMlpNodes) {
+        const int64_t node = n0 + wave * kMlpNodes + c;
+        const bool live = node < n;
+        const size_t i0 = (size_t)(live ? node : n - 1);
+        float x[kInSteps];
+#pragma unroll
+        for (int k = 0; k < kInSteps; ++k) {
+            const int f = 4 * k + g;
+            x[k] = f < NIN ? feats[i0 * NIN + min(f, NIN - 1)] : 0.f;
         }
-        part[blockIdx.x] = ta;
-        part[gridDim.x + blockIdx.x] = tb;
-    }
-}
-
-// out[0], out[1] = the sums of the nb partials of sumsq2_kernel, in a fixed order (one
-// workgroup of kBlock threads: strided serial sums, then a pairwise tree in LDS)
-__global__ __launch_bounds__(kBlock) void sumsq2_finalize_kernel(int nb, const double* __restrict__ part,
-                                                                 double* __restrict__ out) {
-    __shared__ double ls[2][kBlock];
-    double sa = 0.0, sb = 0.0;
-    for (int i = threadIdx.x; i < nb; i += kBlock) {
-        sa += part[i];
-        sb += part[nb + i];
-    }
-    ls[0][threadIdx.x] = sa;
-    ls[1][threadIdx.x] = sb;
-    __syncthreads();
-    for (int h = kBlock / 2; h > 0; h >>= 1) {
-        if (threadIdx.x < h) {
-            ls[0][threadIdx.x] += ls[0][threadIdx.x + h];
-            ls[1][threadIdx.x] += ls[1][threadIdx.x + h];
+        const f32x4 dr = *reinterpret_cast<const f32x4*>(dinv + i0 * 16 + 4 * g);   // row g of D^-1
+        const uint32_t dm = dmask[i0];
+        f32x4 y = b2;
+#pragma unroll
+        for (int t = 0; t < kHidTiles; ++t) {
+            f32x4 z = b1[t];
+#pragma unroll
+            for (int k = 0; k < kInSteps; ++k) z = mfma4(w1[t][k], x[k], z);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) z[i] = tanhf(z[i]);
+            if (hid && live) *reinterpret_cast<f32x4*>(hid + i0 * NHID + 16 * t + 4 * g) = z;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) y = mfma4(w2[t][i], z[i], y);
+        }
+        // y: row g of the node's Delta
+        f32x4 m;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const bool masked = (dm & (1u << g)) || (dm & (1u << q));
+            m[q] = (g == q ? 1.f : 0.f) + (masked ? 0.f : y[q]);
+        }
+        *reinterpret_cast<f32x4*>(&sm[wave][c][4 * g]) = m;
+        __syncthreads();
+        float o[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const f32x4 mk = *reinterpret_cast<const f32x4*>(&sm[wave][c][4 * k]);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) o[q] += dr[k] * mk[q];
+        }
+        if (live) {
+            using V4 = typename Vec4<TM>::type;
+            *reinterpret_cast<V4*>(P + i0 * 16 + 4 * g) = V4{TM(o[0]), TM(o[1]), TM(o[2]), TM(o[3])};
+            if (!(isfinite(o[0]) && isfinite(o[1]) && isfinite(o[2]) && isfinite(o[3]))) atomicAdd(&flags[3], 1);
         }
         __syncthreads();
     }
-    if (threadIdx.x == 0) {
-        out[0] = ls[0][0];
-        out[1] = ls[1][0];
+}
+inline int forward_grid(int n) { return std::min(kFwdBlocks, grid_for(n, kMlpNodes * (kBlock / 64))); }
+
+// ------------------------------------------------------------------------ residual samples
+// The samples of a batch go through the matrix together, up to eight at a time, so that each of
+// A P r and A^T e reads it once for all of them: 20 + 17 us for eight samples at 35,937 nodes
+// (FP32), where a pass per sample took 8 x (12.5 + 12.6) us and four more launches a sample.  Vectors of a group are interleaved per node
+// as [node][dof][S], S = 1, 2, 4 or 8 the group's size rounded up: a block's column of S
+// samples is S adjacent 4-byte values per dof.  Eight lanes share a block row as in the
+// solver's SpMV: lane (q, r) takes row r of blocks q, q + 2, ...
+constexpr int kGroupMax = 8;
+constexpr int kRowLanes = 8;
+constexpr int kBatchUnroll = 4;               // blocks of a lane in flight
+constexpr int kBatchBlocks = 2048;            // workgroups at most: two sums a sample each
+static_assert((2 * kGroupMax) * (kBatchBlocks + 1) <= kRedBlocks * (kMaxRestart + 1), "batch sums exceed scratch");
+
+template <int I>
+__device__ __forceinline__ float quad_get(float v) {       // component I of a quad's four values
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), I * 0x55, 0xF, 0xF, false));
+}
+
+template <int S>
+__device__ __forceinline__ void load_group(const float* __restrict__ p, float (&v)[S]) {
+    if constexpr (S >= 4) {
+#pragma unroll
+        for (int k = 0; k < S / 4; ++k) {
+            const f32x4 x = reinterpret_cast<const f32x4*>(p)[k];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v[4 * k + q] = x[q];
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < S; ++k) v[k] = p[k];
+    }
+}
+template <int S>
+__device__ __forceinline__ void store_group(float* __restrict__ p, const float (&v)[S]) {
+    if constexpr (S >= 4) {
+#pragma unroll
+        for (int k = 0; k < S / 4; ++k)
+            reinterpret_cast<f32x4*>(p)[k] = f32x4{v[4 * k], v[4 * k + 1], v[4 * k + 2], v[4 * k + 3]};
+    } else {
+#pragma unroll
+        for (int k = 0; k < S; ++k) p[k] = v[k];
     }
 }
 
-// gdelta_i += scale * D_i^-T g_i r_i^T, scale = -2 / (S ||r||^2); loss += ||e||^2 / (S ||r||^2)
-__global__ void grad_delta_kernel(int n, const float* __restrict__ dinv, const float* __restrict__ g,
-                                  const float* __restrict__ r, const double* __restrict__ sums, int nbatch,
-                                  float* __restrict__ gdelta, float* __restrict__ loss) {
-    const int tid = blockIdx.x * blockDim.x + threadIdx.x;
-    const double rr = sums[1];
-    const float scale = rr > 0.0 ? float(-2.0 / (nbatch * rr)) : 0.f;
-    if (tid == 0 && rr > 0.0) loss[0] += float(sums[0] / (nbatch * rr));
-    const int i = tid >> 4, q = tid & 15;
-    if (i >= n) return;
-    const int row = q >> 2, col = q & 3;
-    const float* di = dinv + (size_t)i * 16;
-    const float* gi = g + (size_t)i * 4;
-    // (D^-T g)_row = sum_k D^-1[k][row] g_k
-    const float dg = di[row] * gi[0] + di[4 + row] * gi[1] + di[8 + row] * gi[2] + di[12 + row] * gi[3];
-    gdelta[(size_t)i * 16 + q] += scale * dg * r[(size_t)i * 4 + col];
+// t = P r for the group's samples (node-local 4x4 products); samples past nb are zero.
+template <int S>
+__global__ void group_apply_kernel(int n, int nb, const float* __restrict__ P, const float* __restrict__ r,
+                                   float* __restrict__ t) {
+    const int64_t tid = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (tid >= 4 * (int64_t)n) return;
+    const f32x4 p = *reinterpret_cast<const f32x4*>(P + tid * 4);
+    const size_t N = 4 * (size_t)n;
+    float x[S], o[S];
+#pragma unroll
+    for (int b = 0; b < S; ++b) x[b] = b < nb ? r[b * N + tid] : 0.f;
+#pragma unroll
+    for (int b = 0; b < S; ++b)
+        o[b] = p[0] * quad_get<0>(x[b]) + p[1] * quad_get<1>(x[b]) + p[2] * quad_get<2>(x[b]) +
+               p[3] * quad_get<3>(x[b]);
+    store_group<S>(t + tid * S, o);
 }
 
-// MLP backward over a chunk of nodes per workgroup; partial weight gradients per workgroup.
-constexpr int kBwdNodes = 64;
+// Sums of S values over the wave, as a reduce-scatter: lane l < S returns that of sample
+// bit-reversed l.  The order is fixed.
+template <int S>
+__device__ __forceinline__ double group_wave_sum(double (&v)[S]) {
+    const int lane = threadIdx.x & 63;
+    int off = 1;
+#pragma unroll
+    for (int w = S / 2; w >= 1; w >>= 1) {
+        const bool up = (lane & off) != 0;
+#pragma unroll
+        for (int i = 0; i < w; ++i) {
+            const double send = up ? v[i] : v[w + i], keep = up ? v[w + i] : v[i];
+            v[i] = keep + __shfl_xor(send, off, 64);
+        }
+        off <<= 1;
+    }
+    for (; off < 64; off <<= 1) v[0] += __shfl_xor(v[0], off, 64);
+    return v[0];
+}
+template <int S>
+__device__ __forceinline__ int group_sum_index(int lane) {
+    int s = 0;
+#pragma unroll
+    for (int w = S / 2, b = 0; w >= 1; w >>= 1, ++b) s += ((lane >> b) & 1) * w;
+    return s;
+}
+
+// e = r - A t for the group, and per workgroup the partial sums of e^2 (part[s][workgroup]) and
+// r^2 (part[S + s][workgroup]) of every sample s: no atomics, so that training is reproducible.
+template <typename TA, int S>
+__global__ __launch_bounds__(kBlock) void group_residual_kernel(int n, int nb, const int32_t* __restrict__ rowptr,
+                                                                const int32_t* __restrict__ colidx,
+                                                                const TA* __restrict__ A, const float* __restrict__ t,
+                                                                const float* __restrict__ rb, float* __restrict__ e,
+                                                                double* __restrict__ part) {
+    const int sub = threadIdx.x % kRowLanes, q = sub >> 2, r = sub & 3;
+    constexpr int Q = kRowLanes / 4;
+    const size_t N = 4 * (size_t)n;
+    double se[S], sr[S];
+#pragma unroll
+    for (int b = 0; b < S; ++b) se[b] = sr[b] = 0.0;
+    for (int row = (blockIdx.x * kBlock + threadIdx.x) / kRowLanes; row < n; row += gridDim.x * (kBlock / kRowLanes)) {
+        const int k1 = rowptr[row + 1];
+        float acc[S], rv[S];
+#pragma unroll
+        for (int b = 0; b < S; ++b) {
+            acc[b] = 0.f;
+            rv[b] = b < nb ? rb[b * N + 4 * (size_t)row + r] : 0.f;
+        }
+        for (int k0 = rowptr[row] + q; k0 < k1; k0 += kBatchUnroll * Q) {
+            int col[kBatchUnroll];
+            f32x4 a[kBatchUnroll];
+            float x[kBatchUnroll][S];
+#pragma unroll
+            for (int u = 0; u < kBatchUnroll; ++u) {
+                const int k = k0 + u * Q;
+                col[u] = k < k1 ? colidx[k] : -1;
+            }
+#pragma unroll
+            for (int u = 0; u < kBatchUnroll; ++u)
+                if (col[u] >= 0) {
+                    a[u] = load4(A + (size_t)(k0 + u * Q) * 16 + r * 4);
+                    load_group<S>(t + ((size_t)col[u] * 4 + r) * S, x[u]);
+                }
+#pragma unroll
+            for (int u = 0; u < kBatchUnroll; ++u)
+                if (col[u] >= 0) {                 // the four lanes of a quad agree
+#pragma unroll
+                    for (int b = 0; b < S; ++b)
+                        acc[b] += a[u][0] * quad_get<0>(x[u][b]) + a[u][1] * quad_get<1>(x[u][b]) +
+                                  a[u][2] * quad_get<2>(x[u][b]) + a[u][3] * quad_get<3>(x[u][b]);
+                }
+        }
+        float ev[S];
+#pragma unroll
+        for (int b = 0; b < S; ++b) {
+            const float other = __shfl_xor(acc[b], 4, 64);
+            ev[b] = b < nb ? rv[b] - (acc[b] + other) : 0.f;
+            if (q == 0) {
+                se[b] += double(ev[b]) * double(ev[b]);
+                sr[b] += double(rv[b]) * double(rv[b]);
+            }
+        }
+        if (q == 0) store_group<S>(e + (4 * (size_t)row + r) * S, ev);
+    }
+    __shared__ double ls[kBlock / 64][2 * S];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const double te = group_wave_sum<S>(se), tr = group_wave_sum<S>(sr);
+    if (lane < S) {
+        ls[wave][group_sum_index<S>(lane)] = te;
+        ls[wave][S + group_sum_index<S>(lane)] = tr;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2 * S) {
+        double v = 0.0;
+        for (int w = 0; w < kBlock / 64; ++w) v += ls[w][threadIdx.x];
+        part[(size_t)threadIdx.x * gridDim.x + blockIdx.x] = v;
+    }
+}
+
+// sums[i] = the nb partials of sum i in a fixed order (one workgroup a sum: strided serial
+// sums, then a pairwise tree in LDS)
+__global__ __launch_bounds__(kBlock) void group_sums_kernel(int nb, const double* __restrict__ part,
+                                                            double* __restrict__ sums) {
+    __shared__ double ls[kBlock];
+    const double* p = part + (size_t)blockIdx.x * nb;
+    double s = 0.0;
+    for (int i = threadIdx.x; i < nb; i += kBlock) s += p[i];
+    ls[threadIdx.x] = s;
+    __syncthreads();
+    for (int h = kBlock / 2; h > 0; h >>= 1) {
+        if (threadIdx.x < h) ls[threadIdx.x] += ls[threadIdx.x + h];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) sums[blockIdx.x] = ls[0];
+}
+
+// g = A^T e through the transposed-block map, and straight from it the gradient of the blocks:
+//   gdelta_i (+)= sum_s scale_s D_i^-T g_s r_s^T,  scale_s = -2 / (nbatch ||r_s||^2),
+// added to the earlier groups' unless first; workgroup 0 also adds the group's loss
+// sum_s ||e_s||^2 / (nbatch ||r_s||^2).  Lane r takes row r of a block, so that its own value of
+// e serves the block's four columns; the quad's partial columns meet once per block row.
+template <typename TA, int S>
+__global__ __launch_bounds__(kBlock) void group_grad_kernel(int n, int nb, const int32_t* __restrict__ rowptr,
+                                                            const int32_t* __restrict__ colidx,
+                                                            const int32_t* __restrict__ tpos,
+                                                            const TA* __restrict__ A, const float* __restrict__ e,
+                                                            const float* __restrict__ rb,
+                                                            const float* __restrict__ dinv,
+                                                            const double* __restrict__ sums, int nbatch, int first,
+                                                            float* __restrict__ gdelta, float* __restrict__ loss) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        float l = first ? 0.f : loss[0];
+        for (int b = 0; b < nb; ++b)
+            if (sums[S + b] > 0.0) l += float(sums[b] / (nbatch * sums[S + b]));
+        loss[0] = l;
+    }
+    const int sub = threadIdx.x % kRowLanes, q = sub >> 2, r = sub & 3;
+    constexpr int Q = kRowLanes / 4;
+    const size_t N = 4 * (size_t)n;
+    float scale[S];
+#pragma unroll
+    for (int b = 0; b < S; ++b) {
+        const double rr = b < nb ? sums[S + b] : 0.0;
+        scale[b] = rr > 0.0 ? float(-2.0 / (nbatch * rr)) : 0.f;
+    }
+    for (int row = (blockIdx.x * kBlock + threadIdx.x) / kRowLanes; row < n; row += gridDim.x * (kBlock / kRowLanes)) {
+        const int k1 = rowptr[row + 1];
+        float rv[S], di[4];
+#pragma unroll
+        for (int b = 0; b < S; ++b) rv[b] = b < nb ? rb[b * N + 4 * (size_t)row + r] : 0.f;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) di[k] = dinv[(size_t)row * 16 + 4 * k + r];
+        float acc[4][S];                           // this lane's part of column c
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int b = 0; b < S; ++b) acc[c][b] = 0.f;
+        for (int k0 = rowptr[row] + q; k0 < k1; k0 += kBatchUnroll * Q) {
+            int col[kBatchUnroll], tp[kBatchUnroll];
+            f32x4 a[kBatchUnroll];
+            float x[kBatchUnroll][S];
+#pragma unroll
+            for (int u = 0; u < kBatchUnroll; ++u) {
+                const int k = k0 + u * Q;
+                col[u] = k < k1 ? colidx[k] : -1;
+                tp[u] = k < k1 ? tpos[k] : 0;
+            }
+#pragma unroll
+            for (int u = 0; u < kBatchUnroll; ++u)
+                if (col[u] >= 0) {
+                    a[u] = load4(A + (size_t)tp[u] * 16 + r * 4);
+                    load_group<S>(e + ((size_t)col[u] * 4 + r) * S, x[u]);
+                }
+#pragma unroll
+            for (int u = 0; u < kBatchUnroll; ++u)
+                if (col[u] >= 0) {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+#pragma unroll
+                        for (int b = 0; b < S; ++b) acc[c][b] += a[u][c] * x[u][b];
+                }
+        }
+        // column c of the quad's four rows: a reduce-scatter, lane r keeps column r; then the
+        // two halves of the row
+        const bool x1 = (r & 1) != 0, x2 = (r & 2) != 0;
+        float gv[S];
+#pragma unroll
+        for (int b = 0; b < S; ++b) {
+            const float lo = (x2 ? acc[2][b] : acc[0][b]) + __shfl_xor(x2 ? acc[0][b] : acc[2][b], 2, 64);
+            const float hi = (x2 ? acc[3][b] : acc[1][b]) + __shfl_xor(x2 ? acc[1][b] : acc[3][b], 2, 64);
+            float v = (x1 ? hi : lo) + __shfl_xor(x1 ? lo : hi, 1, 64);
+            gv[b] = v + __shfl_xor(v, 4, 64);
+        }
+        // row r of the gradient block: (D^-T g)_r r^T (the halves hold the same values)
+        f32x4 o = {0.f, 0.f, 0.f, 0.f};
+        f32x4* dst = reinterpret_cast<f32x4*>(gdelta + (size_t)row * 16 + 4 * r);
+        if (!first) o = *dst;
+#pragma unroll
+        for (int b = 0; b < S; ++b) {
+            const float dg = di[0] * quad_get<0>(gv[b]) + di[1] * quad_get<1>(gv[b]) + di[2] * quad_get<2>(gv[b]) +
+                             di[3] * quad_get<3>(gv[b]);
+            const float r0 = quad_get<0>(rv[b]), r1 = quad_get<1>(rv[b]), r2 = quad_get<2>(rv[b]),
+                        r3 = quad_get<3>(rv[b]);
+            if (b < nb) {
+                const float s = scale[b] * dg;
+                o[0] += s * r0;
+                o[1] += s * r1;
+                o[2] += s * r2;
+                o[3] += s * r3;
+            }
+        }
+        if (q == 0) *dst = o;
+    }
+}
+
+// MLP backward, partial weight gradients per workgroup.  Both contractions are matrix products
+// over the nodes: gz = (gy W2) (1 - h^2) per node, then gW1 += gz^T [x 1] and gW2 += gy^T h, 64
+// instructions per 16 nodes and wave, the weight gradients staying in 48 accumulators.  (13 us for
+// 35,937 nodes; one thread per weight over nodes staged in LDS read two LDS words per product
+// and took 99 us.)  gz comes out as D[node 4g + i][hidden c], which is the A operand of the second
+// product as it stands.
+constexpr int kBwdNodes = kMlpNodes * (kBlock / 64);
 __global__ __launch_bounds__(kBlock) void backward_kernel(int n, const float* __restrict__ feats,
                                                           const float* __restrict__ hid,
                                                           const float* __restrict__ gdelta,
                                                           const uint8_t* __restrict__ dmask,
                                                           const float* __restrict__ wts, float* __restrict__ wpart) {
-    __shared__ float sx[kBwdNodes][NIN + 1];
-    __shared__ float sh[kBwdNodes][NHID + 1];
-    __shared__ float sgy[kBwdNodes][NOUT + 1];
-    __shared__ float sgz[kBwdNodes][NHID + 1];
-    float acc[(NW + kBlock - 1) / kBlock];
-    for (int q = 0; q < (NW + kBlock - 1) / kBlock; ++q) acc[q] = 0.f;
-    const int per_block = (n + gridDim.x - 1) / gridDim.x;
-    const int i0 = blockIdx.x * per_block, i1 = min(n, i0 + per_block);
-    for (int c0 = i0; c0 < i1; c0 += kBwdNodes) {
-        const int cn = min(kBwdNodes, i1 - c0);
-        // stage features, activations and the masked output gradient
-        for (int q = threadIdx.x; q < kBwdNodes * NIN; q += blockDim.x) {
-            const int a = q / NIN, f = q % NIN;
-            sx[a][f] = a < cn ? feats[(size_t)(c0 + a) * NIN + f] : 0.f;
-        }
-        for (int q = threadIdx.x; q < kBwdNodes * NHID; q += blockDim.x) {
-            const int a = q / NHID, h = q % NHID;
-            sh[a][h] = a < cn ? hid[(size_t)(c0 + a) * NHID + h] : 0.f;
-        }
-        for (int q = threadIdx.x; q < kBwdNodes * NOUT; q += blockDim.x) {
-            const int a = q / NOUT, o = q % NOUT;
-            float v = 0.f;
-            if (a < cn) {
-                const uint32_t dm = dmask[c0 + a];
-                const int rr = o >> 2, cc = o & 3;
-                v = ((dm & (1u << rr)) || (dm & (1u << cc))) ? 0.f : gdelta[(size_t)(c0 + a) * 16 + o];
-            }
-            sgy[a][o] = v;
-        }
-        __syncthreads();
-        // hidden gradient: gz = (W2^T gy) * (1 - h^2)
-        for (int q = threadIdx.x; q < kBwdNodes * NHID; q += blockDim.x) {
-            const int a = q / NHID, h = q % NHID;
-            float s = 0.f;
-            for (int o = 0; o < NOUT; ++o) s += wts[OFF_W2 + o * NHID + h] * sgy[a][o];
-            sgz[a][h] = s * (1.f - sh[a][h] * sh[a][h]);
-        }
-        __syncthreads();
-        // weight gradients: each thread owns a fixed set of weights
-        for (int q = 0; q < (NW + kBlock - 1) / kBlock; ++q) {
-            const int wi = q * kBlock + threadIdx.x;
-            if (wi >= NW) break;
-            float s = 0.f;
-            if (wi < OFF_B1) {
-                const int h = wi / NIN, f = wi % NIN;
-                for (int a = 0; a < cn; ++a) s += sgz[a][h] * sx[a][f];
-            } else if (wi < OFF_W2) {
-                const int h = wi - OFF_B1;
-                for (int a = 0; a < cn; ++a) s += sgz[a][h];
-            } else if (wi < OFF_B2) {
-                const int o = (wi - OFF_W2) / NHID, h = (wi - OFF_W2) % NHID;
-                for (int a = 0; a < cn; ++a) s += sgy[a][o] * sh[a][h];
-            } else {
-                const int o = wi - OFF_B2;
-                for (int a = 0; a < cn; ++a) s += sgy[a][o];
-            }
-            acc[q] += s;
-        }
-        __syncthreads();
+    __shared__ float lw[kBlock / 64][NW];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int g = lane >> 4, c = lane & 15;
+    float w2[kHidTiles][4];                        // W2[4g + s][16t + c]
+#pragma unroll
+    for (int t = 0; t < kHidTiles; ++t)
+#pragma unroll
+        for (int s = 0; s < 4; ++s) w2[t][s] = wts[OFF_W2 + (4 * g + s) * NHID + 16 * t + c];
+    f32x4 a1[kHidTiles][kInTiles], a2[kHidTiles];
+    float ab2 = 0.f;                               // sum of gy[., c] over this lane group's nodes
+#pragma unroll
+    for (int t = 0; t < kHidTiles; ++t) {
+        a2[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int f = 0; f < kInTiles; ++f) a1[t][f] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    for (int q = 0; q < (NW + kBlock - 1) / kBlock; ++q) {
-        const int wi = q * kBlock + threadIdx.x;
-        if (wi < NW) wpart[(size_t)blockIdx.x * NW + wi] = acc[q];
+    const int64_t step = (int64_t)gridDim.x * kBwdNodes;
+    for (int64_t n0 = (int64_t)blockIdx.x * kBwdNodes + wave * kMlpNodes; n0 < n; n0 += step) {
+        // gy of node n0 + c, outputs 4g .. 4g + 3 (zero past the last node)
+        f32x4 gyr = {0.f, 0.f, 0.f, 0.f};
+        if (n0 + c < n) {
+            gyr = *reinterpret_cast<const f32x4*>(gdelta + (size_t)(n0 + c) * 16 + 4 * g);
+            const uint32_t dm = dmask[n0 + c];
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+                if ((dm & (1u << g)) || (dm & (1u << s))) gyr[s] = 0.f;
+        }
+        // node n0 + 4g + i: output gradient c, hidden unit 16t + c, input 16f + c (the bias is
+        // an input of one)
+        float gyc[4], h[4][kHidTiles], x[4][kInTiles];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int64_t node = n0 + 4 * g + i;
+            const bool live = node < n;
+            const size_t nd = (size_t)(live ? node : n - 1);
+            const uint32_t dm = dmask[nd];
+            const bool off = !live || (dm & (1u << (c >> 2))) || (dm & (1u << (c & 3)));
+            const float gv = gdelta[nd * 16 + c];
+            gyc[i] = off ? 0.f : gv;
+#pragma unroll
+            for (int t = 0; t < kHidTiles; ++t) h[i][t] = hid[nd * NHID + 16 * t + c];
+#pragma unroll
+            for (int f = 0; f < kInTiles; ++f) {
+                const int k = 16 * f + c;
+                const float xv = feats[nd * NIN + min(k, NIN - 1)];
+                x[i][f] = k < NIN ? xv : (k == NIN ? 1.f : 0.f);
+            }
+            ab2 += gyc[i];
+        }
+#pragma unroll
+        for (int t = 0; t < kHidTiles; ++t) {
+            f32x4 gz = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int s = 0; s < 4; ++s) gz = mfma4(gyr[s], w2[t][s], gz);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float z = gz[i] * (1.f - h[i][t] * h[i][t]);
+#pragma unroll
+                for (int f = 0; f < kInTiles; ++f) a1[t][f] = mfma4(z, x[i][f], a1[t][f]);
+                a2[t] = mfma4(gyc[i], h[i][t], a2[t]);
+            }
+        }
+    }
+    ab2 += __shfl_xor(ab2, 16, 64);
+    ab2 += __shfl_xor(ab2, 32, 64);
+    float* l = lw[wave];
+#pragma unroll
+    for (int t = 0; t < kHidTiles; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int hd = 16 * t + 4 * g + i;     // row of a1
+#pragma unroll
+            for (int f = 0; f < kInTiles; ++f) {
+                const int k = 16 * f + c;
+                if (k < NIN) l[OFF_W1 + hd * NIN + k] = a1[t][f][i];
+                if (k == NIN) l[OFF_B1 + hd] = a1[t][f][i];
+            }
+            l[OFF_W2 + (4 * g + i) * NHID + 16 * t + c] = a2[t][i];
+        }
+    if (g == 0) l[OFF_B2 + c] = ab2;
+    __syncthreads();
+    for (int wi = threadIdx.x; wi < NW; wi += kBlock) {
+        float s = 0.f;
+#pragma unroll
+        for (int w = 0; w < kBlock / 64; ++w) s += lw[w][wi];
+        wpart[(size_t)blockIdx.x * NW + wi] = s;
     }
 }
 
-// grad = sum of the partials (fixed order); Adam update when lr > 0.
-__global__ void adam_kernel(int nparts, const float* __restrict__ wpart, float* __restrict__ wts,
-                            float* __restrict__ mstate, float* __restrict__ vstate, int step, float lr,
-                            float* __restrict__ grad_out) {
-    const int wi = blockIdx.x * blockDim.x + threadIdx.x;
-    if (wi >= NW) return;
+// grad = sum of the partials (fixed order); Adam update when lr > 0.  A workgroup takes 32
+// adjacent weights, eight threads a weight sharing its partials (one thread a weight was a
+// serial chain of 256 loads on eleven workgroups: 63 us, now 5 us).
+constexpr int kAdamWeights = 32, kAdamLanes = kBlock / kAdamWeights;
+__global__ __launch_bounds__(kBlock) void adam_kernel(int nparts, const float* __restrict__ wpart,
+                                                      float* __restrict__ wts, float* __restrict__ mstate,
+                                                      float* __restrict__ vstate, int step, float lr,
+                                                      float* __restrict__ grad_out) {
+    __shared__ float ls[kAdamLanes][kAdamWeights];
+    const int k = threadIdx.x % kAdamWeights, q = threadIdx.x / kAdamWeights;
+    const int wi = blockIdx.x * kAdamWeights + k;
+    float s = 0.f;
+    if (wi < NW) {
+#pragma unroll 8
+        for (int p = q; p < nparts; p += kAdamLanes) s += wpart[(size_t)p * NW + wi];
+    }
+    ls[q][k] = s;
+    __syncthreads();
+    if (q != 0 || wi >= NW) return;
     float g = 0.f;
-    for (int p = 0; p < nparts; ++p) g += wpart[(size_t)p * NW + wi];
+#pragma unroll
+    for (int p = 0; p < kAdamLanes; ++p) g += ls[p][k];
     if (grad_out) grad_out[wi] = g;
     if (!(lr > 0.f)) return;
     const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
@@ -340,12 +621,6 @@ __global__ void adam_kernel(int nparts, const float* __restrict__ wpart, float* 
     const float vh = v / (1.f - powf(b2, (float)step));
     wts[wi] -= lr * mh / (sqrtf(vh) + eps);
 }
-
-__global__ void zero_f32_kernel(float* p, size_t n) {
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
-        p[i] = 0.f;
-}
-
 
 __global__ void reset_pc_flags_kernel(int32_t* flags) {
     if (threadIdx.x == 0) {
@@ -368,6 +643,50 @@ int features(vms_ctx* c, const void* A, float* feats, float* dinv, hipStream_t s
     return check_hip(c, hipGetLastError(), "features launch");
 }
 
+// One group of samples (nb of the batch of nbatch, interleaved S to a node) through P, A and
+// A^T: t and e are scratch of 4 n S floats each.
+template <typename TA, int S>
+void launch_group(vms_ctx* c, const TA* A, int nb, int nbatch, int first, const float* r, const float* P,
+                  const float* dinv, float* t, float* e, float* gdelta, float* loss, hipStream_t s) {
+    const int n = c->n_nodes;
+    const int g = std::min(kBatchBlocks, grid_for((int64_t)kRowLanes * n));
+    double* part = c->red->partial;                        // reduction scratch: idle here
+    double* sums = part + (size_t)2 * S * g;
+    group_apply_kernel<S><<<grid_for(4 * (int64_t)n), kBlock, 0, s>>>(n, nb, P, r, t);
+    group_residual_kernel<TA, S><<<g, kBlock, 0, s>>>(n, nb, c->rowptr, c->colidx, A, t, r, e, part);
+    group_sums_kernel<<<2 * S, kBlock, 0, s>>>(g, part, sums);
+    group_grad_kernel<TA, S><<<g, kBlock, 0, s>>>(n, nb, c->rowptr, c->colidx, c->tpos, A, e, r, dinv, sums, nbatch,
+                                                  first, gdelta, loss);
+}
+
+// The batch in groups of at most eight samples.  The group's vectors live in the Krylov basis,
+// which holds nothing between solves; a context whose basis is too short for the group (a
+// restart length below 2 S - 1 in FP32) takes smaller groups, down to one sample at a time in
+// the context's own training vectors.
+template <typename TA>
+void launch_batch(vms_ctx* c, const TA* A, const float* r_batch, int nbatch, const float* P, const float* dinv,
+                  float* gdelta, float* loss, hipStream_t s) {
+    const size_t N = 4 * (size_t)c->n_nodes;
+    const size_t room = (size_t)(c->max_restart + 1) * sizeof(TA) / sizeof(float);   // FP32 vectors in the basis
+    int cap = kGroupMax;
+    while (cap > 1 && 2 * (size_t)cap > room) cap >>= 1;
+    for (int b0 = 0; b0 < nbatch; b0 += cap) {
+        const int nb = std::min(cap, nbatch - b0);
+        const float* r = r_batch + b0 * N;
+        int S = 1;
+        while (S < nb) S <<= 1;
+        float* t = S == 1 ? c->tvec : (float*)c->V;
+        float* e = t + N * S;
+        auto go = [&](auto sz) {
+            launch_group<TA, decltype(sz)::value>(c, A, nb, nbatch, b0 == 0, r, P, dinv, t, e, gdelta, loss, s);
+        };
+        if (S == 1) go(std::integral_constant<int, 1>{});
+        else if (S == 2) go(std::integral_constant<int, 2>{});
+        else if (S == 4) go(std::integral_constant<int, 4>{});
+        else go(std::integral_constant<int, 8>{});
+    }
+}
+
 }  // namespace
 
 int learned_blocks(vms_ctx* c, const void* A, const float* weights, void* Minv_out, int out_is_double,
@@ -377,10 +696,10 @@ int learned_blocks(vms_ctx* c, const void* A, const float* weights, void* Minv_o
     int rc = features(c, A, c->feats, c->gblk, s);   // gblk holds D^-1 here
     if (rc) return rc;
     if (out_is_double)
-        forward_kernel<double><<<grid_for(c->n_nodes), kBlock, 0, s>>>(c->n_nodes, c->feats, weights, c->gblk,
+        forward_kernel<double><<<forward_grid(c->n_nodes), kBlock, 0, s>>>(c->n_nodes, c->feats, weights, c->gblk,
                                                                       c->dmask, nullptr, (double*)Minv_out, c->flags);
     else
-        forward_kernel<float><<<grid_for(c->n_nodes), kBlock, 0, s>>>(c->n_nodes, c->feats, weights, c->gblk,
+        forward_kernel<float><<<forward_grid(c->n_nodes), kBlock, 0, s>>>(c->n_nodes, c->feats, weights, c->gblk,
                                                                      c->dmask, nullptr, (float*)Minv_out, c->flags);
     if ((rc = check_hip(c, hipGetLastError(), "learned blocks launch"))) return rc;
     int32_t h[4];
@@ -407,7 +726,7 @@ extern "C" int vms_pc_blocks(vms_ctx* c, const void* bsr_vals, const float* weig
         return check_hip(c, hipMemcpyAsync(P, c->gblk, (size_t)c->n_nodes * 16 * sizeof(float),
                                            hipMemcpyDeviceToDevice, s), "copy blocks");
     }
-    forward_kernel<float><<<grid_for(c->n_nodes), kBlock, 0, s>>>(c->n_nodes, c->feats, weights, c->gblk, c->dmask,
+    forward_kernel<float><<<forward_grid(c->n_nodes), kBlock, 0, s>>>(c->n_nodes, c->feats, weights, c->gblk, c->dmask,
                                                                  nullptr, P, c->flags);
     return check_hip(c, hipGetLastError(), "pc blocks launch");
 }
@@ -420,42 +739,21 @@ extern "C" int vms_pc_train_step(vms_ctx* c, const void* bsr_vals, const float* 
     if (lr > 0.f && (!adam_state || step < 1))
         return set_error(c, VMS_EINVAL, "vms_pc_train_step: Adam needs adam_state and step >= 1");
     const int n = c->n_nodes;
-    const int N = 4 * n;
     float* dinv = c->gblk;             // D^-1 blocks
     float* P = c->pblk;                // preconditioner blocks
-    float* t = c->tvec;                // P r
-    float* e = c->tvec + N;            // r - A P r
-    float* g = c->tvec + 2 * (size_t)N;  // A^T e
     float* gdelta = c->gdel;           // [n][16]
-    double* sums = c->rnorm + 4;       // the two FP64 sums of the loss
     float* loss = c->fscal;
     int rc = features(c, bsr_vals, c->feats, dinv, s);
     if (rc) return rc;
-    forward_kernel<float><<<grid_for(n), kBlock, 0, s>>>(n, c->feats, weights, dinv, c->dmask, c->hid, P, c->flags);
-    zero_f32_kernel<<<std::min(grid_for((int64_t)16 * n), 4096), kBlock, 0, s>>>(gdelta, (size_t)16 * n);
-    zero_f32_kernel<<<1, 64, 0, s>>>(loss, 1);
-    for (int b = 0; b < nbatch; ++b) {
-        const float* r = r_batch + (size_t)b * N;
-        block_apply_kernel<<<grid_for(N), kBlock, 0, s>>>(n, P, r, t);
-        if (c->prec == VMS_FP64) {
-            spmv_f32_kernel<double, 0><<<grid_for(N), kBlock, 0, s>>>(n, c->rowptr, c->colidx, c->tpos,
-                                                                     (const double*)bsr_vals, t, r, e);
-            spmv_f32_kernel<double, 1><<<grid_for(N), kBlock, 0, s>>>(n, c->rowptr, c->colidx, c->tpos,
-                                                                     (const double*)bsr_vals, e, nullptr, g);
-        } else {
-            spmv_f32_kernel<float, 0><<<grid_for(N), kBlock, 0, s>>>(n, c->rowptr, c->colidx, c->tpos,
-                                                                    (const float*)bsr_vals, t, r, e);
-            spmv_f32_kernel<float, 1><<<grid_for(N), kBlock, 0, s>>>(n, c->rowptr, c->colidx, c->tpos,
-                                                                    (const float*)bsr_vals, e, nullptr, g);
-        }
-        const int nb = std::min(grid_for(N), 1024);
-        sumsq2_kernel<<<nb, kBlock, 0, s>>>(N, e, r, c->red->partial);      // reduction scratch: idle here
-        sumsq2_finalize_kernel<<<1, kBlock, 0, s>>>(nb, c->red->partial, sums);
-        grad_delta_kernel<<<grid_for((int64_t)16 * n), kBlock, 0, s>>>(n, dinv, g, r, sums, nbatch, gdelta, loss);
-    }
+    forward_kernel<float><<<forward_grid(n), kBlock, 0, s>>>(n, c->feats, weights, dinv, c->dmask, c->hid, P,
+                                                             c->flags);
+    if (c->prec == VMS_FP64)
+        launch_batch<double>(c, (const double*)bsr_vals, r_batch, nbatch, P, dinv, gdelta, loss, s);
+    else
+        launch_batch<float>(c, (const float*)bsr_vals, r_batch, nbatch, P, dinv, gdelta, loss, s);
     const int nparts = std::min(kBwdBlocks, std::max(1, (n + kBwdNodes - 1) / kBwdNodes));
     backward_kernel<<<nparts, kBlock, 0, s>>>(n, c->feats, c->hid, gdelta, c->dmask, weights, c->wgrad);
-    adam_kernel<<<grid_for(NW), kBlock, 0, s>>>(nparts, c->wgrad, weights, adam_state,
+    adam_kernel<<<grid_for(NW, kAdamWeights), kBlock, 0, s>>>(nparts, c->wgrad, weights, adam_state,
                                                 adam_state ? adam_state + NW : nullptr, step, lr, grad_out);
     if (loss_out)
         if ((rc = check_hip(c, hipMemcpyAsync(loss_out, loss, sizeof(float), hipMemcpyDeviceToDevice, s), "loss")))
