@@ -738,62 +738,58 @@ __global__ __launch_bounds__(kDotThreads) void dots_kernel(int n_nodes, int j, c
     }
 }
 
-// Values the Givens rotations read from the cycle state, loaded ahead of the chain.
+// What the end of a column needs from the cycle state, loaded ahead.
 struct GivensCtx {
     double tol_abs;
     uint64_t* progress;
     unsigned gen;
+    int report;             // 1: publish the progress after every column; 0: only when the cycle stops
 };
 
 // Givens rotation of column jc (held in LDS, rows 0 .. jc+1), with the rotations of columns
 // 0 .. jc-1 in LDS (cl, sl) and gj the rotated right-hand side entry jc.  The rotated column
 // (rows 0 .. jc) goes to Rl in LDS, for the workgroup to store; the rotation, g, the residual
 // estimate, k and the done flag go to the cycle state, and the progress is published.
-// Returns 1 when the cycle stops.  Called by one thread, which issues no memory access in the
+// Returns 1 when the cycle stops.  Called by one whole wave, which issues no memory access in the
 // chain (inside a launch that streams vectors, every such access would queue behind the
-// stream); the LDS operands are fetched four at a time.
+// stream).  The chain x_{i+1} = c_i y_i - s_i x_i is what the update launch waits for, so lane i
+// holds rotation i and hands x_{i+1} to lane i + 1 by a DPP shift: a multiply, an FMA and the
+// shift per rotation (lane i's x is right, and stays so, from round i on).  One lane fetching
+// the operands from LDS took 65 ns a rotation, 1.3 us at j = 30 with ten kept vectors.
+// i0 > 0: rows 0 .. i0-1 of the column were already rotated (Rl) and x0 is row i0.
 __device__ int givens_column(int jc, const double* col, double* cl, double* sl, double gj, double* Rl,
                              const GivensCtx& gc, GmresState* gs, int done_val, int i0 = 0, double x0 = 0.0) {
-    // i0 > 0: rows 0 .. i0-1 of the column were already rotated (Rl) and x0 is row i0
+    const int lane = threadIdx.x & 63;
     double x = i0 > 0 ? x0 : col[0];
-    int i = i0;
-    for (; i + 4 <= jc; i += 4) {
-        double c4[4], s4[4], y4[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            c4[q] = cl[i + q];
-            s4[q] = sl[i + q];
-            y4[q] = col[i + q + 1];
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            Rl[i + q] = c4[q] * x + s4[q] * y4[q];
-            x = -s4[q] * x + c4[q] * y4[q];
-        }
-    }
-    for (; i < jc; ++i) {
-        const double yv = col[i + 1];
-        Rl[i] = cl[i] * x + sl[i] * yv;
-        x = -sl[i] * x + cl[i] * yv;
-    }
     const double hn = col[jc + 1];
+    for (int base = i0; base < jc; base += 64) {
+        const int i = base + lane, n = min(64, jc - base);
+        const bool on = lane < n;
+        const double c = on ? cl[i] : 0.0, s = on ? sl[i] : 0.0, y = on ? col[i + 1] : 0.0;
+        double xi = x;                                 // what enters rotation i
+        for (int k = 1; k < n; ++k) xi = wave_shift(fma(c, y, -(s * xi)), x);
+        if (on) Rl[i] = fma(c, xi, s * y);
+        x = read_lane(fma(c, y, -(s * xi)), n - 1);
+    }
     const double d = hypot(x, hn);
     const double cs = d > 0.0 ? x / d : 1.0;
     const double sn = d > 0.0 ? hn / d : 0.0;
     const double gnext = -sn * gj;
     const bool conv = fabs(gnext) <= gc.tol_abs;
     const bool breakdown = !(hn > 1e-300 * (fabs(d) + 1e-300)) || !isfinite(hn) || !isfinite(gnext);
-    Rl[jc] = d;
-    gs->cs[jc] = cs;
-    gs->sn[jc] = sn;
-    cl[jc] = cs;
-    sl[jc] = sn;
-    gs->g[jc] = cs * gj;
-    gs->gin[jc + 1] = gnext;
-    gs->k = jc + 1;
     const int stop = (conv || breakdown) ? 1 : 0;
-    if (stop) gs->done = done_val;
-    report_progress(gc.progress, gc.gen, jc + 1, stop);
+    if (lane == 0) {
+        Rl[jc] = d;
+        gs->cs[jc] = cs;
+        gs->sn[jc] = sn;
+        cl[jc] = cs;
+        sl[jc] = sn;
+        gs->g[jc] = cs * gj;
+        gs->gin[jc + 1] = gnext;
+        gs->k = jc + 1;
+        if (stop) gs->done = done_val;
+        if (stop || gc.report) report_progress(gc.progress, gc.gen, jc + 1, stop);
+    }
     return stop;
 }
 
@@ -886,21 +882,57 @@ __device__ __forceinline__ double group4_sum(double v) {
 //    residual estimate, k = j and, on convergence or breakdown, the done flag.
 //  * column j: H(0:j, j) = (c - H s) / rho with c = (t, c_j), H(j+1, j) = hh.  A zero hh means
 //    an invariant Krylov space: column j is final and closes the cycle.
-// Every value is loaded in one round before the first test, the columns 0 .. j-2 that H s needs
-// included (lane = row, wave w = the columns l = w mod 4, kFirst of them per lane; more in
-// batches).  Column j is written even when column j-1 closes the cycle: it lies beyond the
-// final basis and the next cycle rebuilds it.
+// Every value of the cycle state is loaded in one round (columns_load: the update issues it right
+// behind the loads of the step's partials, which it needs first), the columns 0 .. j-2 that H s needs included
+// (lane = row, wave w = the columns l = w mod 4, kColFirst of them per lane; more in batches).
+// Column j is written even when column j-1 closes the cycle: it lies beyond the final basis and
+// the next cycle rebuilds it.
 struct StepIn {
     const double* sums;     // s_i = sums[2i] (before the reorthogonalisation switch), t_i = sums[2i+1]
     double rho, cj, hh;
     int reorth;
 };
 
-__device__ void arnoldi_columns(int j, GmresState* gs, const StepIn* in) {
+constexpr int kColFirst = 12;                           // H loads per lane in the first round
+constexpr int kQtMax = (kDrMax + 1) * (kDrMax + 1);
+constexpr int kQtLoads = (kQtMax + kBlock - 1) / kBlock;
+struct ColLoads {
+    int dk;                 // vectors kept by deflated restarting
+    double qt[kQtLoads];    // Q^T of the kept block, spread over the threads
+    double beta, gprev, hprev;
+    double hp, cs_t, sn_t;  // H(tid, j-1); rotation tid
+    double hv[kColFirst];   // H(lane, wave + 4 q)
+    GivensCtx gc;
+};
+
+__device__ __forceinline__ ColLoads columns_load(int j, int dk, const GmresState* gs, bool last, int report) {
+    constexpr int ld = kMaxRestart + 1, kWaves = kBlock / 64;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    ColLoads c;
+    c.dk = dk;
+    c.beta = gs->beta;
+    c.gprev = j > 0 ? gs->gin[j - 1] : 0.0;
+    c.hprev = j > 0 ? gs->H[(size_t)(j - 1) * ld + j] : 0.0;
+    c.hp = tid < j ? gs->H[(size_t)(j - 1) * ld + tid] : 0.0;
+    c.cs_t = tid + 1 < j ? gs->cs[tid] : 0.0;
+    c.sn_t = tid + 1 < j ? gs->sn[tid] : 0.0;
+    const bool hs_on = !last && j > 1;
+#pragma unroll
+    for (int q = 0; q < kColFirst; ++q) {
+        const int l = wave + kWaves * q;
+        c.hv[q] = (hs_on && l <= j - 2 && lane <= j) ? gs->H[(size_t)l * ld + lane] : 0.0;
+    }
+    c.gc = GivensCtx{gs->tol_abs, gs->progress, gs->gen, report};
+    if (dk > 0)
+#pragma unroll
+        for (int q = 0; q < kQtLoads; ++q) c.qt[q] = gs->dr_qt[min(tid + kBlock * q, kQtMax - 1)];
+    return c;
+}
+
+__device__ void arnoldi_columns(int j, GmresState* gs, const StepIn* in, const ColLoads& c) {
     constexpr int ld = kMaxRestart + 1;
     constexpr int kWaves = kBlock / 64;
-    constexpr int kFirst = 12;                          // H loads per lane in the first round
-    constexpr int kBatch = 4;                           // then per batch
+    constexpr int kBatch = 4;                           // further H loads per batch
     static_assert(kMaxRestart <= 128 && kBlock >= 64 + kMaxRestart, "two row passes; rows on waves 1..");
     __shared__ double Hc[kMaxRestart + 2];              // column j-1, final
     __shared__ double colj[kMaxRestart + 2];            // column j
@@ -910,70 +942,59 @@ __device__ void arnoldi_columns(int j, GmresState* gs, const StepIn* in) {
     __shared__ double Rl[2][kMaxRestart + 1];           // rotated columns j-1 and j
     __shared__ double dr_v[kDrMax + 1];                 // deflated restarting: c, then Q^T c
     __shared__ double dr_x0;                            // row dk of a column after Q^T
+    __shared__ double qt[kQtMax];                       // Q^T of the kept block, column-major, ld dk + 1
     __shared__ int flags[1];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     // deflated restarting: columns 0 .. dk-1 of H are the kept block (rows 0 .. dk), set by the
     // host together with their rotated form (R) and Q^T; step dk starts the Arnoldi recurrence
-    const int dk = gs->dr_k;
+    const int dk = c.dk;
     const bool dr_first = dk > 0 && j == dk;
     auto rowmax = [&](int l) { return l < dk ? dk : l + 1; };   // last nonzero row of column l
     const int r = tid - 64;                             // row of column j (waves 1 ..)
     const bool last = in == nullptr;                    // the tail: column j-1 only
     const bool hs_on = !last && j > 1;                  // columns 0 .. j-2 take part in H s
-    const int done = in ? 0 : gs->done;                 // the fused update has tested it
     // a stop found by the update launch of step j is stored as j + 2, which that launch's other
     // workgroups read as "not yet stopped": they still write q_j, which the closing column needs
     const int done_val = in ? j + 2 : 1;
     const int reorth = in ? in->reorth : gs->reorth;
     const double rho = in ? in->rho : gs->rho, hh = in ? in->hh : gs->hh, cj = in ? in->cj : gs->cj;
-    const double gprev = j > 0 ? gs->gin[j - 1] : 0.0;
-    const double hprev = j > 0 ? gs->H[(size_t)(j - 1) * ld + j] : 0.0;
-    const GivensCtx gc{gs->tol_abs, gs->progress, gs->gen};
-    double s_t = 0.0, hp = 0.0, cs_t = 0.0, sn_t = 0.0, t_r = 0.0;
-    if (tid < j) {
-        s_t = in ? in->sums[2 * tid] : gs->scoef[tid];
-        hp = gs->H[(size_t)(j - 1) * ld + tid];
-    }
-    if (tid + 1 < j) {
-        cs_t = gs->cs[tid];
-        sn_t = gs->sn[tid];
-    }
+    const double gprev = c.gprev, hprev = c.hprev;
+    const GivensCtx gc = c.gc;
+    double s_t = 0.0, t_r = 0.0;
+    if (tid < j) s_t = in ? in->sums[2 * tid] : gs->scoef[tid];
     if (!last && r >= 0 && r < j) t_r = in->sums[2 * r + 1];
-    double hv[kFirst];
-#pragma unroll
-    for (int q = 0; q < kFirst; ++q) {
-        const int l = wave + kWaves * q;
-        hv[q] = (hs_on && l <= j - 2 && lane <= rowmax(l)) ? gs->H[(size_t)l * ld + lane] : 0.0;
-    }
-    if (done) return;                                   // uniform: written by an earlier launch
     if (tid < j) sv[tid] = reorth ? s_t : 0.0;
     if (tid + 1 < j) {
-        cl[tid] = cs_t;
-        sl[tid] = sn_t;
+        cl[tid] = c.cs_t;
+        sl[tid] = c.sn_t;
     }
+    if (dk > 0)
+#pragma unroll
+        for (int q = 0; q < kQtLoads; ++q)
+            if (tid + kBlock * q < kQtMax) qt[tid + kBlock * q] = c.qt[q];
     __syncthreads();
     if (j > 0 && tid <= j) {
         if (dr_first) {
             // column dk-1 is the kept block's last column: final as the host set it
-            Hc[tid] = gs->H[(size_t)(j - 1) * ld + tid];
+            Hc[tid] = tid < j ? c.hp : hprev;
         } else {
-            const double h = tid < j ? hp + hprev * sv[tid] : hprev * rho;
+            const double h = tid < j ? c.hp + hprev * sv[tid] : hprev * rho;
             Hc[tid] = h;
             gs->H[(size_t)(j - 1) * ld + tid] = h;
         }
     }
-    if (dr_first && tid <= dk) dr_v[tid] = gs->beta * (tid < dk ? sv[tid] : rho);
+    if (dr_first && tid <= dk) dr_v[tid] = c.beta * (tid < dk ? sv[tid] : rho);
     if (hs_on) {
         double acc[2] = {0.0, 0.0};
 #pragma unroll
-        for (int q = 0; q < kFirst; ++q) {
+        for (int q = 0; q < kColFirst; ++q) {
             const int l = wave + kWaves * q;
-            if (l <= j - 2) acc[0] += hv[q] * sv[l];
+            if (l <= j - 2) acc[0] += (lane <= rowmax(l) ? c.hv[q] : 0.0) * sv[l];
         }
         for (int p = 0; p < 2; ++p) {
             const int i = lane + 64 * p;
             if (i > j) break;
-            const int lbeg = wave + (p == 0 ? kWaves * kFirst : kWaves * (63 / kWaves));
+            const int lbeg = wave + (p == 0 ? kWaves * kColFirst : kWaves * (63 / kWaves));
             for (int l0 = lbeg; l0 <= j - 2; l0 += kWaves * kBatch) {
                 double hb[kBatch];
 #pragma unroll
@@ -998,7 +1019,8 @@ __device__ void arnoldi_columns(int j, GmresState* gs, const StepIn* in) {
         double t = 0.0;
         if (tid <= dk) {
             const double* src = dr_first ? dr_v : Hc;
-            for (int l = 0; l <= dk; ++l) t += gs->dr_qt[l * (dk + 1) + tid] * src[l];
+#pragma unroll 4
+            for (int l = 0; l <= dk; ++l) t += qt[l * (dk + 1) + tid] * src[l];
         }
         __syncthreads();
         if (tid <= dk) {
@@ -1015,25 +1037,29 @@ __device__ void arnoldi_columns(int j, GmresState* gs, const StepIn* in) {
         __syncthreads();
     }
     // wave 0: the rotation of column j-1;  waves 1 ..: column j
-    if (tid == 0) {
+    if (wave == 0) {
         int st = 0;
         if (dr_first) {
             // the kept block's residual estimate; the columns 0 .. dk-1 are done
-            gs->gin[dk] = dr_x0;
-            gs->k = dk;
             st = (fabs(dr_x0) <= gc.tol_abs || !(rho > 0.0) || !isfinite(dr_x0)) ? 1 : 0;
-            if (st) gs->done = done_val;
-            report_progress(gc.progress, gc.gen, dk, st);
+            if (lane == 0) {
+                gs->gin[dk] = dr_x0;
+                gs->k = dk;
+                if (st) gs->done = done_val;
+                if (st || gc.report) report_progress(gc.progress, gc.gen, dk, st);
+            }
         } else if (j > 0) {
             st = dk > 0 ? givens_column(j - 1, Hc, cl, sl, gprev, Rl[0], gc, gs, done_val, dk, dr_x0)
                         : givens_column(j - 1, Hc, cl, sl, gprev, Rl[0], gc, gs, done_val);
             if (!(rho > 0.0)) {
                 st = 1;                      // u_j vanished: column j-1 closes the cycle
-                gs->done = done_val;
-                report_progress(gc.progress, gc.gen, j, 1);
+                if (lane == 0) {
+                    gs->done = done_val;
+                    report_progress(gc.progress, gc.gen, j, 1);
+                }
             }
         }
-        flags[0] = st;
+        if (lane == 0) flags[0] = st;
     }
     const bool col_on = !last && rho > 0.0;
     if (col_on && r >= 0 && r <= j) {
@@ -1055,26 +1081,33 @@ __device__ void arnoldi_columns(int j, GmresState* gs, const StepIn* in) {
     if (dk > 0) {                                       // Q^T of the kept block on its rows 0 .. dk
         double t = 0.0;
         if (tid <= dk)
-            for (int l = 0; l <= dk; ++l) t += gs->dr_qt[l * (dk + 1) + tid] * colj[l];
+            for (int l = 0; l <= dk; ++l) t += qt[l * (dk + 1) + tid] * colj[l];
         __syncthreads();
         if (tid < dk) Rl[1][tid] = t;
         if (tid == dk) dr_x0 = t;
         __syncthreads();
     }
-    if (tid == 0) {
-        colj[j + 1] = 0.0;
+    if (tid == 0) colj[j + 1] = 0.0;
+    __syncthreads();
+    if (wave == 0) {
         const double gj = gs->gin[j];
         if (dk > 0) givens_column(j, colj, cl, sl, gj, Rl[1], gc, gs, done_val, dk, dr_x0);
         else givens_column(j, colj, cl, sl, gj, Rl[1], gc, gs, done_val);
-        gs->done = done_val;
-        report_progress(gc.progress, gc.gen, j + 1, 1);
+        if (lane == 0) {
+            gs->done = done_val;
+            report_progress(gc.progress, gc.gen, j + 1, 1);
+        }
     }
     __syncthreads();
     if (tid <= j) gs->R[(size_t)j * ld + tid] = Rl[1][tid];
 }
 
 // The tail of a cycle: column j-1 from the last vector's second pass.
-__global__ __launch_bounds__(kBlock) void columns_kernel(int j, GmresState* gs) { arnoldi_columns(j, gs, nullptr); }
+__global__ __launch_bounds__(kBlock) void columns_kernel(int j, int dk, GmresState* gs) {
+    const ColLoads c = columns_load(j, dk, gs, true, 1);
+    if (gs->done) return;
+    arnoldi_columns(j, gs, nullptr, c);
+}
 
 // ------------------------------------------------------------- fused step (3 launches per step)
 // The update launch forms the step's sums itself: every workgroup reads the dot partials
@@ -1086,7 +1119,7 @@ constexpr int kFusedChunks = 16;                                     // dot part
 constexpr int kFusedLanes = 4;                                       // lanes per slot
 constexpr int kFusedPer = kFusedChunks / kFusedLanes;                // partials per lane
 constexpr int kFusedSlots = kBlock / kFusedLanes;                    // slots per round
-constexpr int kFusedRounds = (2 * (kMaxRestart + 2) + kFusedSlots - 1) / kFusedSlots;
+constexpr int kFusedRounds = 2;                                      // rounds loaded ahead (62 steps)
 static_assert(kFusedChunks % kXcds == 0 && kFusedChunks <= kDotChunks, "fused dot chunks");
 // Large meshes: the dots write kWideChunks partials per slot (more workgroups streaming the
 // basis when j is small), slot_sum_kernel adds them, and the update reads one sum per slot.
@@ -1127,10 +1160,15 @@ struct StepOut {
     double svj;             // S(q_j)
 };
 
-// Returns false (uniformly) when the cycle is done.  Every thread of the workgroup calls it.
-__device__ __forceinline__ bool step_scalars(int j, int nchunks, const double* __restrict__ part, const GmresState* gs,
-                                             double eps_dot, StepLds& L, StepOut& o) {
-    const int tid = threadIdx.x, lane = tid & 63;
+// The loads of step_scalars, which a caller may follow with its own before it waits for them.
+struct StepLoads {
+    double pv[kFusedRounds][kFusedPer];
+    double svl, su;
+    int done, reorth;
+};
+__device__ __forceinline__ StepLoads step_load(int j, int nchunks, const double* __restrict__ part,
+                                               const GmresState* gs) {
+    const int tid = threadIdx.x;
     const int ns = 2 * (j + 2);
     const int grp = tid / kFusedLanes, sub = tid % kFusedLanes;
     // part[slot][0 .. nchunks) is contiguous (stride nchunks): lane sub of a slot reads its
@@ -1138,35 +1176,58 @@ __device__ __forceinline__ bool step_scalars(int j, int nchunks, const double* _
     // every load is unconditional (slot and chunk clamped to valid ones) and weighted 0 when
     // absent, since a load under a per-lane condition becomes a branch with a full wait.
     const int rounds = (ns + kFusedSlots - 1) / kFusedSlots;
-    double pv[kFusedRounds][kFusedPer];
+    StepLoads s;
 #pragma unroll
     for (int r = 0; r < kFusedRounds; ++r) {
         const int slot = grp + kFusedSlots * r;
         const size_t base = (size_t)min(slot, ns - 1) * nchunks;
 #pragma unroll
-        for (int c = 0; c < kFusedPer; ++c) pv[r][c] = 0.0;
+        for (int c = 0; c < kFusedPer; ++c) s.pv[r][c] = 0.0;
         if (r < rounds) {
 #pragma unroll
-            for (int c = 0; c < kFusedPer; ++c) {
-                const int ch = sub * kFusedPer + c;
-                const double wt = (slot < ns && ch < nchunks) ? 1.0 : 0.0;
-                pv[r][c] = wt * part[base + min(ch, nchunks - 1)];
-            }
+            for (int c = 0; c < kFusedPer; ++c) s.pv[r][c] = part[base + min(sub * kFusedPer + c, nchunks - 1)];
         }
     }
-    if (tid < j) L.svl[tid] = gs->svs[tid];
+    s.svl = gs->svs[min(tid, kMaxRestart)];
+    s.done = gs->done;
+    s.reorth = gs->reorth;
+    s.su = gs->su;
+    return s;
+}
+
+// Returns false (uniformly) when the cycle is done.  Every thread of the workgroup calls it.
+__device__ __forceinline__ bool step_scalars(int j, int nchunks, const double* __restrict__ part, const StepLoads& s,
+                                             double eps_dot, StepLds& L, StepOut& o) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int ns = 2 * (j + 2);
+    const int grp = tid / kFusedLanes, sub = tid % kFusedLanes;
+    if (tid < j) L.svl[tid] = s.svl;
     if (tid == 0) {
-        L.flags[0] = gs->done;
-        L.flags[1] = gs->reorth;
-        L.su = gs->su;
+        L.flags[0] = s.done;
+        L.flags[1] = s.reorth;
+        L.su = s.su;
     }
 #pragma unroll
     for (int r = 0; r < kFusedRounds; ++r) {
         double a = 0.0;
 #pragma unroll
-        for (int c = 0; c < kFusedPer; ++c) a += pv[r][c];
+        for (int c = 0; c < kFusedPer; ++c) {
+            const int slot = grp + kFusedSlots * r;
+            a += (slot < ns && sub * kFusedPer + c < nchunks) ? s.pv[r][c] : 0.0;
+        }
         a = group4_sum(a);
         const int slot = grp + kFusedSlots * r;
+        if (sub == 0 && slot < ns) L.sums[slot] = a;
+    }
+    for (int s0 = kFusedSlots * kFusedRounds; s0 < ns; s0 += kFusedSlots) {   // longer restarts
+        const int slot = s0 + grp;
+        double a = 0.0;
+#pragma unroll
+        for (int c = 0; c < kFusedPer; ++c) {
+            const int ch = sub * kFusedPer + c;
+            a += (slot < ns && ch < nchunks) ? part[(size_t)slot * nchunks + ch] : 0.0;
+        }
+        a = group4_sum(a);
         if (sub == 0 && slot < ns) L.sums[slot] = a;
     }
     __syncthreads();
@@ -1210,14 +1271,18 @@ __device__ __forceinline__ bool step_scalars(int j, int nchunks, const double* _
 // The vector rows are split in eighths of xrows rows, one per XCD: the rows whose dot products
 // the dots launch formed on that XCD, so that their reads here hit its L2.
 template <typename T, int R>
-__global__ __launch_bounds__(kBlock) void update_fused_kernel(int n, int xrows, int j, T* __restrict__ V,
+__global__ __launch_bounds__(kBlock, sizeof(T) * R > 8 ? 4 : 5) void update_fused_kernel(int n, int xrows, int j, T* __restrict__ V,
                                                               const T* __restrict__ w, int nchunks,
                                                               const double* __restrict__ part, GmresState* gs,
-                                                              double eps_dot) {
+                                                              double eps_dot, int dk, int report) {
     __shared__ StepLds L;
     StepOut o;
     if (blockIdx.x == 0) {
-        if (!step_scalars(j, nchunks, part, gs, eps_dot, L, o)) return;
+        // the launch lasts as long as this workgroup: its waves go first on their CU
+        __builtin_amdgcn_s_setprio(3);
+        const StepLoads sl = step_load(j, nchunks, part, gs);
+        const ColLoads c = columns_load(j, dk, gs, false, report);
+        if (!step_scalars(j, nchunks, part, sl, eps_dot, L, o)) return;
         if (threadIdx.x == 0) {
             gs->rho = o.rho;
             gs->cj = o.cj;
@@ -1226,7 +1291,7 @@ __global__ __launch_bounds__(kBlock) void update_fused_kernel(int n, int xrows, 
             gs->svs[j] = o.svj;
         }
         const StepIn in{L.sums, o.rho, o.cj, o.hh, L.flags[1]};
-        arnoldi_columns(j, gs, &in);
+        arnoldi_columns(j, gs, &in, c);
         return;
     }
     // R rows per thread, each row's loads coalesced across the workgroup; workgroup b runs on
@@ -1252,7 +1317,7 @@ __global__ __launch_bounds__(kBlock) void update_fused_kernel(int n, int xrows, 
     for (int q = 0; q < 8; ++q)
 #pragma unroll
         for (int r = 0; r < R; ++r) v0[q][r] = V[(size_t)min(q, max(j - 1, 0)) * N + ix[r]];
-    if (!step_scalars(j, nchunks, part, gs, eps_dot, L, o)) return;
+    if (!step_scalars(j, nchunks, part, step_load(j, nchunks, part, gs), eps_dot, L, o)) return;
     const bool reorth = L.flags[1] != 0;
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
@@ -1650,17 +1715,17 @@ int run_cycle(vms_ctx* c, const T* r0, const TM* Minv, TX* x, double tol_abs, in
                 const int nsum = wide ? 1 : nch;
                 if (sizeof(T) == 4 || wide)
                     update_fused_kernel<T, 2><<<1 + kXcds * grid_for(xrows, 2 * kBlock), kBlock, 0, st>>>(
-                        n, xrows, j, V, w, nsum, sums, c->gs, eps_dot);
+                        n, xrows, j, V, w, nsum, sums, c->gs, eps_dot, j0, lead ? 1 : 0);
                 else
                     update_fused_kernel<T, 1><<<1 + kXcds * grid_for(xrows, kBlock), kBlock, 0, st>>>(
-                        n, xrows, j, V, w, nsum, sums, c->gs, eps_dot);
+                        n, xrows, j, V, w, nsum, sums, c->gs, eps_dot, j0, lead ? 1 : 0);
             });
         }
         // the second pass of the last vector completes the last column
         dots_kernel<T><<<dim3(nch, steps_ + 2), kDotThreads, 0, st>>>(c->n_nodes, steps_, V, w, c->dmask, part,
                                                                       c->gs);
         reduce_kernel<<<1, kRedThreads, 0, st>>>(steps_, nch, part, c->gs, eps_dot);
-        columns_kernel<<<1, kBlock, 0, st>>>(steps_, c->gs);
+        columns_kernel<<<1, kBlock, 0, st>>>(steps_, j0, c->gs);
         return VMS_OK;
     };
     // With the phase timers on, every prof_every-th cycle is launched directly and every launch

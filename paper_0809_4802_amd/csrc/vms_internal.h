@@ -76,8 +76,8 @@ struct Vec4<float> {
 };
 
 // Lane exchanges of a double by DPP (two 32-bit moves; no LDS round trip).  CTRL: a
-// quad_perm pattern, or 0x140 (row_mirror: lane i <-> 15 - i in a row of 16) and 0x141
-// (row_half_mirror: lane i <-> 7 - i in a group of 8).  Every lane of the wave must be active.
+// quad_perm pattern, or 0x140 (row_mirror: lane i <-> 15 - i in a row of 16), 0x141
+// (row_half_mirror: lane i <-> 7 - i in a group of 8) and 0x138 (a shift by one lane).  Every lane of the wave must be active.
 template <int CTRL>
 __device__ __forceinline__ double dpp_mov(double v) {
     const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xF, 0xF, false);
@@ -88,6 +88,13 @@ __device__ __forceinline__ double dpp_mov(double v) {
 __device__ __forceinline__ double read_lane(double v, int l) {
     return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
                             __builtin_amdgcn_readlane(__double2loint(v), l));
+}
+
+// v of lane l to lane l + 1; lane 0 gets first.  Every lane of the wave must be active.
+__device__ __forceinline__ double wave_shift(double v, double first) {
+    const int lo = __builtin_amdgcn_update_dpp(__double2loint(first), __double2loint(v), 0x138, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp(__double2hiint(first), __double2hiint(v), 0x138, 0xF, 0xF, false);
+    return __hiloint2double(hi, lo);
 }
 
 // Sum over the eight lanes of an aligned group (every lane gets it).
