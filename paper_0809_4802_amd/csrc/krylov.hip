@@ -47,6 +47,182 @@ __global__ void fill_kernel(uint4* p, size_t n16) {
         p[i] = make_uint4(0u, 0u, 0u, 0u);
 }
 
+// Publishes the cycle's progress (completed columns k, done flag) to the host-mapped word.
+__device__ __forceinline__ void report_progress(uint64_t* progress, unsigned gen, int k, int done) {
+    const uint64_t word = ((uint64_t)gen << 32) | ((uint64_t)k << 1) | (uint64_t)(done ? 1 : 0);
+    __hip_atomic_store(progress, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+__device__ __forceinline__ void report_progress(GmresState* gs, int k, int done) {
+    report_progress(gs->progress, gs->gen, k, done);
+}
+
+// What the end of a column needs from the cycle state, loaded ahead.
+struct GivensCtx {
+    double tol_abs;
+    uint64_t* progress;
+    unsigned gen;
+    int report;             // 1: publish the progress after every column; 0: only when the cycle stops
+};
+
+// Givens rotation of column jc (held in LDS, rows 0 .. jc+1), with the rotations of columns
+// 0 .. jc-1 in LDS (cl, sl) and gj the rotated right-hand side entry jc.  The rotated column
+// (rows 0 .. jc) goes to Rl in LDS, for the workgroup to store; the rotation, g, the residual
+// estimate, k and the done flag go to the cycle state, and the progress is published.
+// Returns 1 when the cycle stops.  Called by one whole wave, which issues no memory access in the
+// chain (inside a launch that streams vectors, every such access would queue behind the
+// stream).  In the chain x_{i+1} = c_i y_i - s_i x_i lane i holds rotation i and hands x_{i+1} to
+// lane i + 1 by a DPP shift: a multiply, an FMA and the shift per rotation (lane i's x is right,
+// and stays so, from round i on).  One lane fetching the operands from LDS took 65 ns a rotation.
+// i0 > 0: rows 0 .. i0-1 of the column were already rotated (Rl) and x0 is row i0.
+__device__ int givens_column(int jc, const double* col, double* cl, double* sl, double gj, double* Rl,
+                             const GivensCtx& gc, GmresState* gs, int i0, double x0) {
+    const int lane = threadIdx.x & 63;
+    double x = i0 > 0 ? x0 : col[0];
+    const double hn = col[jc + 1];
+    for (int base = i0; base < jc; base += 64) {
+        const int i = base + lane, n = min(64, jc - base);
+        const bool on = lane < n;
+        const double c = on ? cl[i] : 0.0, s = on ? sl[i] : 0.0, y = on ? col[i + 1] : 0.0;
+        double xi = x;                                 // what enters rotation i
+        for (int k = 1; k < n; ++k) xi = wave_shift(fma(c, y, -(s * xi)), x);
+        if (on) Rl[i] = fma(c, xi, s * y);
+        x = read_lane(fma(c, y, -(s * xi)), n - 1);
+    }
+    const double d = hypot(x, hn);
+    const double cs = d > 0.0 ? x / d : 1.0;
+    const double sn = d > 0.0 ? hn / d : 0.0;
+    const double gnext = -sn * gj;
+    const bool conv = fabs(gnext) <= gc.tol_abs;
+    const bool breakdown = !(hn > 1e-300 * (fabs(d) + 1e-300)) || !isfinite(hn) || !isfinite(gnext);
+    const int stop = (conv || breakdown) ? 1 : 0;
+    if (lane == 0) {
+        Rl[jc] = d;
+        gs->cs[jc] = cs;
+        gs->sn[jc] = sn;
+        cl[jc] = cs;
+        sl[jc] = sn;
+        gs->g[jc] = cs * gj;
+        gs->gin[jc + 1] = gnext;
+        gs->k = jc + 1;
+        if (stop) gs->done = 1;
+        if (stop || gc.report) report_progress(gc.progress, gc.gen, jc + 1, stop);
+    }
+    return stop;
+}
+
+// The rotations that step j makes due, by one workgroup: column j-1 of H became final with the
+// update of step j (columns_close), and this rotates it, which gives the residual estimate, k = j
+// and, on convergence or breakdown, the done flag; a zero hh (an invariant Krylov space) makes
+// column j final too and closes the cycle there.  Nothing of the Arnoldi recurrence waits for it:
+// it runs as workgroup 0 of the next step's SpMV launch, the longest of the step's three (inside
+// the update it was the last to end, 1.2 us after the streaming workgroups at cavity 32^3).  A
+// stop it finds takes effect from that step's dots on; the columns and vectors formed meanwhile
+// lie beyond the final basis.  tail: the last vector's second pass (its norm in rho_m), with no
+// column j.  dk: the vectors kept by deflated restarting; columns 0 .. dk-1 of
+// H are the kept block (rows 0 .. dk), set by the host together with their rotated form (R) and
+// Q^T, and step dk starts the Arnoldi recurrence with the cycle's right-hand side c in dr_c.
+constexpr int kQtMax = (kDrMax + 1) * (kDrMax + 1);
+constexpr int kQtLoads = (kQtMax + kBlock - 1) / kBlock;
+__device__ void columns_rotate(int j, int dk, GmresState* gs, int report, bool tail = false) {
+    constexpr int ld = kMaxRestart + 1;
+    __shared__ double Hc[kMaxRestart + 2];              // the column
+    __shared__ double cl[kMaxRestart], sl[kMaxRestart];
+    __shared__ double Rl[kMaxRestart + 1];              // the column rotated
+    __shared__ double qt[kQtMax];                       // Q^T of the kept block, column-major, ld dk + 1
+    __shared__ double src[kDrMax + 1];                  // what it is applied to
+    __shared__ double dr_x0;                            // row dk of a column after Q^T
+    __shared__ int stop_l;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const bool dr_first = dk > 0 && j == dk;
+    const int jm = max(j - 1, 0);
+    // one round of loads, none under a condition of its own lane (indices clamped instead)
+    const int row = min(tid, ld - 1), rot = min(tid, kMaxRestart - 1);
+    const double h_t = gs->H[(size_t)jm * ld + row], cs_t = gs->cs[rot], sn_t = gs->sn[rot];
+    const double rho = tail ? gs->rho_m : gs->rho, hh = gs->hh, gprev = gs->gin[jm];
+    const int done = gs->done;
+    const GivensCtx gc{gs->tol_abs, gs->progress, gs->gen, report};
+    double c_t = 0.0, qt_t[kQtLoads];
+    if (dk > 0) {
+        c_t = gs->dr_c[min(tid, kDrMax)];
+#pragma unroll
+        for (int q = 0; q < kQtLoads; ++q) qt_t[q] = gs->dr_qt[min(tid + kBlock * q, kQtMax - 1)];
+    }
+    if (done) return;                                   // uniform: written by an earlier launch
+    if (tid <= j) Hc[tid] = h_t;
+    if (tid < j) {
+        cl[tid] = cs_t;
+        sl[tid] = sn_t;
+    }
+    if (dk > 0) {
+        if (tid <= dk) src[tid] = dr_first ? c_t : h_t;
+#pragma unroll
+        for (int q = 0; q < kQtLoads; ++q)
+            if (tid < kBlock && tid + kBlock * q < kQtMax) qt[tid + kBlock * q] = qt_t[q];
+    }
+    __syncthreads();
+    // Q^T of the kept block on rows 0 .. dk -- of the cycle's right-hand side at step dk, of
+    // column j-1 at later steps
+    auto apply_qt = [&](double* out) {
+        double t = 0.0;
+        if (tid <= dk) {
+#pragma unroll 4
+            for (int l = 0; l <= dk; ++l) t += qt[l * (dk + 1) + tid] * src[l];
+            if (tid < dk) out[tid] = t;
+            else dr_x0 = t;
+        }
+    };
+    if (dk > 0 && j >= dk) {
+        apply_qt(dr_first ? gs->g : Rl);
+        __syncthreads();
+    }
+    if (wave == 0) {
+        int st = 0;
+        if (dr_first) {
+            // the kept block's residual estimate; the columns 0 .. dk-1 are done
+            st = (fabs(dr_x0) <= gc.tol_abs || !(rho > 0.0) || !isfinite(dr_x0)) ? 1 : 0;
+            if (lane == 0) {
+                gs->gin[dk] = dr_x0;
+                gs->k = dk;
+                if (st) gs->done = 1;
+                if (st || gc.report) report_progress(gc.progress, gc.gen, dk, st);
+            }
+        } else if (j > 0) {
+            st = givens_column(j - 1, Hc, cl, sl, gprev, Rl, gc, gs, dk, dr_x0);
+            if (!(rho > 0.0)) {
+                st = 1;                      // u_j vanished: column j-1 closes the cycle
+                if (lane == 0) {
+                    gs->done = 1;
+                    report_progress(gc.progress, gc.gen, j, 1);
+                }
+            }
+        }
+        if (lane == 0) stop_l = st;
+    }
+    __syncthreads();
+    if (j > 0 && tid < j && !dr_first) gs->R[(size_t)(j - 1) * ld + tid] = Rl[tid];
+    if (tail || stop_l || !(rho > 0.0) || hh > 0.0) return;   // uniform
+    // the Krylov space is invariant: column j is final with a zero subdiagonal
+    __syncthreads();
+    if (tid <= j) Hc[tid] = gs->H[(size_t)j * ld + tid];
+    if (tid == j) Hc[j + 1] = 0.0;
+    if (dk > 0 && tid <= dk) src[tid] = gs->H[(size_t)j * ld + tid];
+    __syncthreads();
+    if (dk > 0) {
+        apply_qt(Rl);
+        __syncthreads();
+    }
+    if (wave == 0) {
+        givens_column(j, Hc, cl, sl, gs->gin[j], Rl, gc, gs, dk, dr_x0);
+        if (lane == 0) {
+            gs->done = 1;
+            report_progress(gc.progress, gc.gen, j + 1, 1);
+        }
+    }
+    __syncthreads();
+    if (tid <= j) gs->R[(size_t)j * ld + tid] = Rl[tid];
+}
+
 // ---------------------------------------------------------------------------------- SpMV
 // Eight lanes per block row.  Lane (q, r), q = 0, 1 and r = 0..3, owns output dof r and the
 // row's blocks q, q + 2, q + 4, ...: it reads row r of each (4 contiguous values) and the
@@ -77,18 +253,31 @@ __device__ __forceinline__ double quad_bcast(double v) {
 // component and the quad exchanges them by DPP, so that x is requested once per quad instead
 // of four times (as many bytes as the matrix block otherwise).  The four lanes share the row
 // and the block sequence, so a quad is active or inactive as a whole.
-template <typename TA, typename TX, typename TY, typename TACC, int MODE, typename TB = double>
+// ROT: the launch of Arnoldi step rot_j + 1, whose workgroup 0 makes the rotations that step rot_j
+// left due (columns_rotate); the others take the rows, XCD for XCD as without it.
+template <typename TA, typename TX, typename TY, typename TACC, int MODE, typename TB = double, bool ROT = false>
 __global__ __launch_bounds__(kBlock) void spmv_kernel(int n_rows, const int32_t* __restrict__ rowptr,
                                                       const int32_t* __restrict__ colidx,
                                                       const TA* __restrict__ A, const TX* __restrict__ x,
-                                                      const TB* __restrict__ b, TY* __restrict__ y,
-                                                      const int* __restrict__ done, const GmresState* gs) {
-    // a finished GMRES cycle (done != NULL and set) reads no blocks and stores nothing; the
-    // flag is read alongside the row bounds, which the block loads wait for anyway
-    const int skip = done ? *done : 0;
+                                                      const TB* __restrict__ b, TY* __restrict__ y, GmresState* gs,
+                                                      int rot_j = 0, int dk = 0, int report = 0) {
+    int slot;
+    if (ROT) {
+        if (blockIdx.x == 0) {
+            __builtin_amdgcn_s_setprio(3);
+            if (rot_j >= dk) columns_rotate(rot_j, dk, gs, report);
+            return;
+        }
+        const int g = gridDim.x - 1, q = blockIdx.x % kXcds;      // workgroup b runs on XCD b mod 8
+        slot = g <= kSpmvXcdMaxGrid ? q * (g / kXcds) + blockIdx.x / kXcds - (q == 0 ? 1 : 0) : blockIdx.x - 1;
+    } else {
+        slot = gridDim.x <= kSpmvXcdMaxGrid ? xcd_slot(blockIdx.x, gridDim.x) : blockIdx.x;
+    }
+    // a finished GMRES cycle reads no blocks and stores nothing; the flag is read alongside the
+    // row bounds, which the block loads wait for anyway
+    const int skip = ROT ? gs->done : 0;
     constexpr int Q = kSpmvLanes / 4;
     using VA = typename Vec4<TA>::type;
-    const int slot = gridDim.x <= kSpmvXcdMaxGrid ? xcd_slot(blockIdx.x, gridDim.x) : blockIdx.x;
     const int tid = slot * blockDim.x + threadIdx.x;
     const int row = tid / kSpmvLanes, sub = tid % kSpmvLanes;
     const int q = sub >> 2, r = sub & 3;
@@ -442,16 +631,6 @@ __global__ __launch_bounds__(kBlock) void full_coarse_setup_kernel(int nn, const
     }
 }
 
-// Publishes the cycle's progress (completed columns k, done flag) to the host-mapped word.
-__device__ __forceinline__ void report_progress(uint64_t* progress, unsigned gen, int k, int done) {
-    const uint64_t word = ((uint64_t)gen << 32) | ((uint64_t)k << 1) | (uint64_t)(done ? 1 : 0);
-    __hip_atomic_store(progress, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-}
-
-__device__ __forceinline__ void report_progress(GmresState* gs, int k, int done) {
-    report_progress(gs->progress, gs->gen, k, done);
-}
-
 // norm of a vector -> gs->beta, initialises the cycle (g = beta e_1, k = 0, done flag).
 template <typename T>
 __global__ __launch_bounds__(kBlock) void cycle_start_kernel(int n, const T* __restrict__ r,
@@ -535,12 +714,10 @@ void launch_dr_basis(int n, int mv, int kk, const double* P, int ldp, T* V, hipS
 }
 
 // Deflated restarting: the kept block of H and its factors from the packed upload into the
-// cycle state (columns 0 .. kk-1 of H and R, zero below their last row), and dr_k = kk.  kk = 0
-// only switches deflation off.  One workgroup.
+// cycle state (columns 0 .. kk-1 of H and R, zero below their last row).  One workgroup.
 __global__ __launch_bounds__(kBlock) void dr_load_kernel(int kk, const double* __restrict__ up, GmresState* gs) {
     constexpr int ld = kMaxRestart + 1;
     const int tid = threadIdx.x;
-    if (tid == 0) gs->dr_k = kk;
     for (int e = tid; e < kk * ld; e += blockDim.x) {
         const int col = e / ld, row = e % ld;
         gs->H[e] = row <= kk ? up[kDrOffH + col * (kk + 1) + row] : 0.0;
@@ -639,10 +816,11 @@ __global__ void precond_apply_kernel(int n_nodes, const TM* __restrict__ Minv, c
 //                = q_j . w, and the provisional subdiagonal of column j is
 //                hh = sqrt(w . w - |c|^2) / rho (Pythagoras).  Then q_j = (u_j - Q s) / rho over
 //                V[j] and u_{j+1} = (w - Q t - c_j q_j) / (rho hh) to V[j+1].  Workgroup 0
-//                instead does the Hessenberg columns (arnoldi_columns): column j-1 becomes final,
+//                instead does the Hessenberg columns (columns_close): column j-1 becomes final,
 //                H(0:j-1, j-1) += hh' s and H(j, j-1) = hh' rho (hh': its provisional
-//                subdiagonal), with its Givens rotation, residual estimate and done flag; then
-//                H(0:j, j) = (c - H s) / rho and H(j+1, j) = hh.
+//                subdiagonal), and H(0:j, j) = (c - H s) / rho, H(j+1, j) = hh.  The Givens
+//                rotation of column j-1, the residual estimate and the done flag follow in
+//                workgroup 0 of the next step's spmv (columns_rotate).
 // Three launches per step (a separate one-workgroup reduction cost more than every update
 // workgroup summing the partials of kFusedChunks chunks again).  The tail of a cycle, the
 // second pass of the last vector, is dots + reduce_kernel + columns_kernel.
@@ -738,70 +916,132 @@ __global__ __launch_bounds__(kDotThreads) void dots_kernel(int n_nodes, int j, c
     }
 }
 
-// What the end of a column needs from the cycle state, loaded ahead.
-struct GivensCtx {
-    double tol_abs;
-    uint64_t* progress;
-    unsigned gen;
-    int report;             // 1: publish the progress after every column; 0: only when the cycle stops
+// The Hessenberg bookkeeping of step j, for one workgroup of kBlock threads.  It needs the
+// step's sums, and nothing of the Arnoldi recurrence waits for it, so it runs as workgroup 0 of
+// the update launch, with the sums that workgroup formed in LDS (in), and, for the cycle's
+// tail, as a launch of its own after reduce_kernel (in = nullptr: column j-1 only, inputs from
+// the cycle state).
+//  * u_j's second pass makes column j-1 final: H(0:j-1, j-1) += hh' s and H(j, j-1) = hh' rho,
+//    hh' being the provisional subdiagonal stored at step j-1; columns_rotate takes it from there.
+//  * column j: H(0:j, j) = (c - H s) / rho with c = (t, c_j), H(j+1, j) = hh.  A zero hh means
+//    an invariant Krylov space: column j is final and closes the cycle.
+//  * at the first step of a deflated cycle, c = beta (s, rho) is the least-squares right-hand side.
+// Every value of the cycle state is loaded in one round (columns_load: the update issues it right
+// behind the loads of the step's partials, which it needs first), the columns 0 .. j-2 that H s
+// needs included (lane = row, wave w = the columns l = w mod 4, kColFirst of them per lane; more in
+// batches).  No load stands under a condition of its own lane, which would become a branch with a
+// full wait: the indices are clamped, the values selected.
+struct StepIn {
+    const double* sums;     // s_i = sums[2i] (before the reorthogonalisation switch), t_i = sums[2i+1]
+    double rho, cj, hh;
+    int reorth;
 };
 
-// Givens rotation of column jc (held in LDS, rows 0 .. jc+1), with the rotations of columns
-// 0 .. jc-1 in LDS (cl, sl) and gj the rotated right-hand side entry jc.  The rotated column
-// (rows 0 .. jc) goes to Rl in LDS, for the workgroup to store; the rotation, g, the residual
-// estimate, k and the done flag go to the cycle state, and the progress is published.
-// Returns 1 when the cycle stops.  Called by one whole wave, which issues no memory access in the
-// chain (inside a launch that streams vectors, every such access would queue behind the
-// stream).  The chain x_{i+1} = c_i y_i - s_i x_i is what the update launch waits for, so lane i
-// holds rotation i and hands x_{i+1} to lane i + 1 by a DPP shift: a multiply, an FMA and the
-// shift per rotation (lane i's x is right, and stays so, from round i on).  One lane fetching
-// the operands from LDS took 65 ns a rotation, 1.3 us at j = 30 with ten kept vectors.
-// i0 > 0: rows 0 .. i0-1 of the column were already rotated (Rl) and x0 is row i0.
-__device__ int givens_column(int jc, const double* col, double* cl, double* sl, double gj, double* Rl,
-                             const GivensCtx& gc, GmresState* gs, int done_val, int i0 = 0, double x0 = 0.0) {
-    const int lane = threadIdx.x & 63;
-    double x = i0 > 0 ? x0 : col[0];
-    const double hn = col[jc + 1];
-    for (int base = i0; base < jc; base += 64) {
-        const int i = base + lane, n = min(64, jc - base);
-        const bool on = lane < n;
-        const double c = on ? cl[i] : 0.0, s = on ? sl[i] : 0.0, y = on ? col[i + 1] : 0.0;
-        double xi = x;                                 // what enters rotation i
-        for (int k = 1; k < n; ++k) xi = wave_shift(fma(c, y, -(s * xi)), x);
-        if (on) Rl[i] = fma(c, xi, s * y);
-        x = read_lane(fma(c, y, -(s * xi)), n - 1);
-    }
-    const double d = hypot(x, hn);
-    const double cs = d > 0.0 ? x / d : 1.0;
-    const double sn = d > 0.0 ? hn / d : 0.0;
-    const double gnext = -sn * gj;
-    const bool conv = fabs(gnext) <= gc.tol_abs;
-    const bool breakdown = !(hn > 1e-300 * (fabs(d) + 1e-300)) || !isfinite(hn) || !isfinite(gnext);
-    const int stop = (conv || breakdown) ? 1 : 0;
-    if (lane == 0) {
-        Rl[jc] = d;
-        gs->cs[jc] = cs;
-        gs->sn[jc] = sn;
-        cl[jc] = cs;
-        sl[jc] = sn;
-        gs->g[jc] = cs * gj;
-        gs->gin[jc + 1] = gnext;
-        gs->k = jc + 1;
-        if (stop) gs->done = done_val;
-        if (stop || gc.report) report_progress(gc.progress, gc.gen, jc + 1, stop);
-    }
-    return stop;
+constexpr int kColFirst = 12;                           // H loads per lane in the first round
+struct ColLoads {
+    double beta, hprev;
+    double hp;              // H(tid, j-1)
+    double hv[kColFirst];   // H(lane, wave + 4 q)
+};
+
+__device__ __forceinline__ ColLoads columns_load(int j, const GmresState* gs, bool last) {
+    constexpr int ld = kMaxRestart + 1, kWaves = kBlock / 64;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int jm = max(j - 1, 0);
+    ColLoads c;
+    c.beta = gs->beta;
+    c.hprev = gs->H[(size_t)jm * ld + j];
+    c.hp = gs->H[(size_t)jm * ld + min(tid, ld - 1)];
+    if (!last && j > 1)
+#pragma unroll
+        for (int q = 0; q < kColFirst; ++q) c.hv[q] = gs->H[(size_t)min(wave + kWaves * q, j - 2) * ld + lane];
+    return c;
 }
 
+__device__ void columns_close(int j, int dk, GmresState* gs, const StepIn* in, const ColLoads& c) {
+    constexpr int ld = kMaxRestart + 1;
+    constexpr int kWaves = kBlock / 64;
+    constexpr int kBatch = 4;                           // further H loads per batch
+    static_assert(kMaxRestart <= 128 && kBlock >= 64 + kMaxRestart, "two row passes; rows on waves 1..");
+    __shared__ double Hc[kMaxRestart + 2];              // column j-1, final
+    __shared__ double sv[kMaxRestart];                  // s
+    __shared__ double hpart[kWaves][kMaxRestart];       // H s, per column class
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const bool dr_first = dk > 0 && j == dk;
+    auto rowmax = [&](int l) { return l < dk ? dk : l + 1; };   // last nonzero row of column l
+    const int r = tid - 64;                             // row of column j (waves 1 ..)
+    const bool last = in == nullptr;                    // the tail: column j-1 only
+    const bool hs_on = !last && j > 1;                  // columns 0 .. j-2 take part in H s
+    const int reorth = in ? in->reorth : gs->reorth;
+    const double rho = in ? in->rho : gs->rho_m, hh = in ? in->hh : 0.0, cj = in ? in->cj : 0.0;
+    double s_t = 0.0, t_r = 0.0;
+    if (tid < j) s_t = in ? in->sums[2 * tid] : gs->scoef[tid];
+    if (!last && r >= 0 && r < j) t_r = in->sums[2 * r + 1];
+    if (tid < j) sv[tid] = reorth ? s_t : 0.0;
+    __syncthreads();
+    if (j > 0 && tid <= j) {
+        if (dr_first) {
+            // column dk-1 is the kept block's last column: final as the host set it
+            Hc[tid] = tid < j ? c.hp : c.hprev;
+            gs->dr_c[tid] = c.beta * (tid < dk ? sv[tid] : rho);
+        } else {
+            const double h = tid < j ? c.hp + c.hprev * sv[tid] : c.hprev * rho;
+            Hc[tid] = h;
+            gs->H[(size_t)(j - 1) * ld + tid] = h;
+        }
+    }
+    if (last) return;
+    if (hs_on) {
+        double acc[2] = {0.0, 0.0};
+#pragma unroll
+        for (int q = 0; q < kColFirst; ++q) {
+            const int l = wave + kWaves * q;
+            if (l <= j - 2) acc[0] += (lane <= rowmax(l) ? c.hv[q] : 0.0) * sv[l];
+        }
+        for (int p = 0; p < 2; ++p) {
+            const int i = lane + 64 * p;
+            if (i > j) break;
+            const int lbeg = wave + (p == 0 ? kWaves * kColFirst : kWaves * (63 / kWaves));
+            for (int l0 = lbeg; l0 <= j - 2; l0 += kWaves * kBatch) {
+                double hb[kBatch];
+#pragma unroll
+                for (int q = 0; q < kBatch; ++q) {
+                    const int l = l0 + kWaves * q;
+                    hb[q] = (l <= j - 2 && i <= rowmax(l)) ? gs->H[(size_t)l * ld + i] : 0.0;
+                }
+#pragma unroll
+                for (int q = 0; q < kBatch; ++q) {
+                    const int l = l0 + kWaves * q;
+                    if (l <= j - 2) acc[p] += hb[q] * sv[l];
+                }
+            }
+        }
+        if (lane <= j) hpart[wave][lane] = acc[0];
+        if (lane + 64 <= j) hpart[wave][lane + 64] = acc[1];
+    }
+    __syncthreads();
+    if (rho > 0.0 && r >= 0 && r <= j) {
+        double hs = 0.0;
+        if (j > 0 && reorth) {
+            if (hs_on)
+                for (int w = 0; w < kWaves; ++w) hs += hpart[w][r];
+            hs += Hc[r] * sv[j - 1];
+        }
+        const double h = ((r < j ? t_r : cj) - hs) / rho;
+        gs->H[(size_t)j * ld + r] = h;
+        if (r == j) gs->H[(size_t)j * ld + j + 1] = hh;
+    }
+}
 
 // The tail of a cycle (one workgroup of kRedThreads): the dot slots of the last vector u_m are
 // summed (eight lanes per slot, eight chunks each, loaded in one predicated round), and one wave
-// forms rho (the norm of u_m after its second pass), S(q_m) and s, which arnoldi_columns needs
+// forms rho (the norm of u_m after its second pass), S(q_m) and s, which columns_close needs
 // to make column m-1 final.  eps_dot: relative accuracy of the dot products (precision of the
 // stored vectors); a squared norm that cancels below eps_dot times its input is a numerical
-// breakdown.  A vanished or non-finite rho is stored as 0, which makes arnoldi_columns close
+// breakdown.  A vanished or non-finite rho is stored as 0, which makes columns_rotate close
 // the cycle at column m-1.  (Inside a cycle the update launch forms the same sums itself,
-// step_scalars below.)
+// step_scalars below.)  Workgroup 1 makes the rotations that the last step left due; it reads
+// nothing that workgroup 0 writes.
 constexpr int kRedThreads = 1024;
 constexpr int kSlotLanes = 8;                               // lanes per dot slot
 constexpr int kSlotChunks = 64 / kSlotLanes;                // chunks per lane
@@ -810,7 +1050,11 @@ constexpr int kSlotRounds = (2 * (kMaxRestart + 2) + kSlotGroups - 1) / kSlotGro
 static_assert(kDotChunks <= 64, "a slot has at most 64 chunks");
 
 __global__ __launch_bounds__(kRedThreads) void reduce_kernel(int j, int nchunks, const double* __restrict__ part,
-                                                             GmresState* gs, double eps_dot) {
+                                                             GmresState* gs, double eps_dot, int dk, int report) {
+    if (blockIdx.x == 1) {
+        columns_rotate(j - 1, dk, gs, report);
+        return;
+    }
     __shared__ double sums[2 * (kMaxRestart + 2)];
     __shared__ double svl[kMaxRestart + 1];
     __shared__ double su_l;
@@ -863,7 +1107,7 @@ __global__ __launch_bounds__(kRedThreads) void reduce_kernel(int j, int nchunks,
     double rho = j > 0 ? (r2 > eps_dot * sums[2 * j] ? sqrt(r2) : 0.0) : 1.0;
     if (!(rho > 0.0) || !isfinite(rho)) rho = 0.0;
     gs->svs[j] = j == 0 ? su_l : (rho > 0.0 ? (su_l - a[1]) / rho : 0.0);     // S(q_j)
-    gs->rho = rho;
+    gs->rho_m = rho;
 }
 
 // Sum over the four lanes of an aligned group (every lane gets it; all lanes active).
@@ -872,241 +1116,13 @@ __device__ __forceinline__ double group4_sum(double v) {
     return v + dpp_mov<0x4E>(v);
 }
 
-// The Hessenberg bookkeeping of step j, for one workgroup of kBlock threads.  It needs the
-// step's sums, and nothing of the Arnoldi recurrence waits for it, so it runs as workgroup 0 of
-// the update launch, with the sums that workgroup formed in LDS (in), and, for the cycle's
-// tail, as a launch of its own after reduce_kernel (in = nullptr: column j-1 only, inputs from
-// the cycle state).
-//  * u_j's second pass makes column j-1 final: H(0:j-1, j-1) += hh' s and H(j, j-1) = hh' rho,
-//    hh' being the provisional subdiagonal stored at step j-1; its Givens rotation gives the
-//    residual estimate, k = j and, on convergence or breakdown, the done flag.
-//  * column j: H(0:j, j) = (c - H s) / rho with c = (t, c_j), H(j+1, j) = hh.  A zero hh means
-//    an invariant Krylov space: column j is final and closes the cycle.
-// Every value of the cycle state is loaded in one round (columns_load: the update issues it right
-// behind the loads of the step's partials, which it needs first), the columns 0 .. j-2 that H s needs included
-// (lane = row, wave w = the columns l = w mod 4, kColFirst of them per lane; more in batches).
-// Column j is written even when column j-1 closes the cycle: it lies beyond the final basis and
-// the next cycle rebuilds it.
-struct StepIn {
-    const double* sums;     // s_i = sums[2i] (before the reorthogonalisation switch), t_i = sums[2i+1]
-    double rho, cj, hh;
-    int reorth;
-};
-
-constexpr int kColFirst = 12;                           // H loads per lane in the first round
-constexpr int kQtMax = (kDrMax + 1) * (kDrMax + 1);
-constexpr int kQtLoads = (kQtMax + kBlock - 1) / kBlock;
-struct ColLoads {
-    int dk;                 // vectors kept by deflated restarting
-    double qt[kQtLoads];    // Q^T of the kept block, spread over the threads
-    double beta, gprev, hprev;
-    double hp, cs_t, sn_t;  // H(tid, j-1); rotation tid
-    double hv[kColFirst];   // H(lane, wave + 4 q)
-    GivensCtx gc;
-};
-
-__device__ __forceinline__ ColLoads columns_load(int j, int dk, const GmresState* gs, bool last, int report) {
-    constexpr int ld = kMaxRestart + 1, kWaves = kBlock / 64;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    ColLoads c;
-    c.dk = dk;
-    c.beta = gs->beta;
-    c.gprev = j > 0 ? gs->gin[j - 1] : 0.0;
-    c.hprev = j > 0 ? gs->H[(size_t)(j - 1) * ld + j] : 0.0;
-    c.hp = tid < j ? gs->H[(size_t)(j - 1) * ld + tid] : 0.0;
-    c.cs_t = tid + 1 < j ? gs->cs[tid] : 0.0;
-    c.sn_t = tid + 1 < j ? gs->sn[tid] : 0.0;
-    const bool hs_on = !last && j > 1;
-#pragma unroll
-    for (int q = 0; q < kColFirst; ++q) {
-        const int l = wave + kWaves * q;
-        c.hv[q] = (hs_on && l <= j - 2 && lane <= j) ? gs->H[(size_t)l * ld + lane] : 0.0;
-    }
-    c.gc = GivensCtx{gs->tol_abs, gs->progress, gs->gen, report};
-    if (dk > 0)
-#pragma unroll
-        for (int q = 0; q < kQtLoads; ++q) c.qt[q] = gs->dr_qt[min(tid + kBlock * q, kQtMax - 1)];
-    return c;
-}
-
-__device__ void arnoldi_columns(int j, GmresState* gs, const StepIn* in, const ColLoads& c) {
-    constexpr int ld = kMaxRestart + 1;
-    constexpr int kWaves = kBlock / 64;
-    constexpr int kBatch = 4;                           // further H loads per batch
-    static_assert(kMaxRestart <= 128 && kBlock >= 64 + kMaxRestart, "two row passes; rows on waves 1..");
-    __shared__ double Hc[kMaxRestart + 2];              // column j-1, final
-    __shared__ double colj[kMaxRestart + 2];            // column j
-    __shared__ double sv[kMaxRestart];                  // s
-    __shared__ double cl[kMaxRestart], sl[kMaxRestart];
-    __shared__ double hpart[kWaves][kMaxRestart];       // H s, per column class
-    __shared__ double Rl[2][kMaxRestart + 1];           // rotated columns j-1 and j
-    __shared__ double dr_v[kDrMax + 1];                 // deflated restarting: c, then Q^T c
-    __shared__ double dr_x0;                            // row dk of a column after Q^T
-    __shared__ double qt[kQtMax];                       // Q^T of the kept block, column-major, ld dk + 1
-    __shared__ int flags[1];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    // deflated restarting: columns 0 .. dk-1 of H are the kept block (rows 0 .. dk), set by the
-    // host together with their rotated form (R) and Q^T; step dk starts the Arnoldi recurrence
-    const int dk = c.dk;
-    const bool dr_first = dk > 0 && j == dk;
-    auto rowmax = [&](int l) { return l < dk ? dk : l + 1; };   // last nonzero row of column l
-    const int r = tid - 64;                             // row of column j (waves 1 ..)
-    const bool last = in == nullptr;                    // the tail: column j-1 only
-    const bool hs_on = !last && j > 1;                  // columns 0 .. j-2 take part in H s
-    // a stop found by the update launch of step j is stored as j + 2, which that launch's other
-    // workgroups read as "not yet stopped": they still write q_j, which the closing column needs
-    const int done_val = in ? j + 2 : 1;
-    const int reorth = in ? in->reorth : gs->reorth;
-    const double rho = in ? in->rho : gs->rho, hh = in ? in->hh : gs->hh, cj = in ? in->cj : gs->cj;
-    const double gprev = c.gprev, hprev = c.hprev;
-    const GivensCtx gc = c.gc;
-    double s_t = 0.0, t_r = 0.0;
-    if (tid < j) s_t = in ? in->sums[2 * tid] : gs->scoef[tid];
-    if (!last && r >= 0 && r < j) t_r = in->sums[2 * r + 1];
-    if (tid < j) sv[tid] = reorth ? s_t : 0.0;
-    if (tid + 1 < j) {
-        cl[tid] = c.cs_t;
-        sl[tid] = c.sn_t;
-    }
-    if (dk > 0)
-#pragma unroll
-        for (int q = 0; q < kQtLoads; ++q)
-            if (tid + kBlock * q < kQtMax) qt[tid + kBlock * q] = c.qt[q];
-    __syncthreads();
-    if (j > 0 && tid <= j) {
-        if (dr_first) {
-            // column dk-1 is the kept block's last column: final as the host set it
-            Hc[tid] = tid < j ? c.hp : hprev;
-        } else {
-            const double h = tid < j ? c.hp + hprev * sv[tid] : hprev * rho;
-            Hc[tid] = h;
-            gs->H[(size_t)(j - 1) * ld + tid] = h;
-        }
-    }
-    if (dr_first && tid <= dk) dr_v[tid] = c.beta * (tid < dk ? sv[tid] : rho);
-    if (hs_on) {
-        double acc[2] = {0.0, 0.0};
-#pragma unroll
-        for (int q = 0; q < kColFirst; ++q) {
-            const int l = wave + kWaves * q;
-            if (l <= j - 2) acc[0] += (lane <= rowmax(l) ? c.hv[q] : 0.0) * sv[l];
-        }
-        for (int p = 0; p < 2; ++p) {
-            const int i = lane + 64 * p;
-            if (i > j) break;
-            const int lbeg = wave + (p == 0 ? kWaves * kColFirst : kWaves * (63 / kWaves));
-            for (int l0 = lbeg; l0 <= j - 2; l0 += kWaves * kBatch) {
-                double hb[kBatch];
-#pragma unroll
-                for (int q = 0; q < kBatch; ++q) {
-                    const int l = l0 + kWaves * q;
-                    hb[q] = (l <= j - 2 && i <= rowmax(l)) ? gs->H[(size_t)l * ld + i] : 0.0;
-                }
-#pragma unroll
-                for (int q = 0; q < kBatch; ++q) {
-                    const int l = l0 + kWaves * q;
-                    if (l <= j - 2) acc[p] += hb[q] * sv[l];
-                }
-            }
-        }
-        if (lane <= j) hpart[wave][lane] = acc[0];
-        if (lane + 64 <= j) hpart[wave][lane + 64] = acc[1];
-    }
-    __syncthreads();
-    // deflated restarting: Q^T of the kept block on rows 0 .. dk -- of the cycle's right-hand
-    // side c = beta (s, rho) at step dk, of column j-1 at later steps
-    if (dk > 0 && j >= dk && !(j == dk && last)) {
-        double t = 0.0;
-        if (tid <= dk) {
-            const double* src = dr_first ? dr_v : Hc;
-#pragma unroll 4
-            for (int l = 0; l <= dk; ++l) t += qt[l * (dk + 1) + tid] * src[l];
-        }
-        __syncthreads();
-        if (tid <= dk) {
-            if (dr_first) {
-                gs->dr_c[tid] = dr_v[tid];
-                if (tid < dk) gs->g[tid] = t;
-                else dr_x0 = t;
-            } else if (tid < dk) {
-                Rl[0][tid] = t;
-            } else {
-                dr_x0 = t;
-            }
-        }
-        __syncthreads();
-    }
-    // wave 0: the rotation of column j-1;  waves 1 ..: column j
-    if (wave == 0) {
-        int st = 0;
-        if (dr_first) {
-            // the kept block's residual estimate; the columns 0 .. dk-1 are done
-            st = (fabs(dr_x0) <= gc.tol_abs || !(rho > 0.0) || !isfinite(dr_x0)) ? 1 : 0;
-            if (lane == 0) {
-                gs->gin[dk] = dr_x0;
-                gs->k = dk;
-                if (st) gs->done = done_val;
-                if (st || gc.report) report_progress(gc.progress, gc.gen, dk, st);
-            }
-        } else if (j > 0) {
-            st = dk > 0 ? givens_column(j - 1, Hc, cl, sl, gprev, Rl[0], gc, gs, done_val, dk, dr_x0)
-                        : givens_column(j - 1, Hc, cl, sl, gprev, Rl[0], gc, gs, done_val);
-            if (!(rho > 0.0)) {
-                st = 1;                      // u_j vanished: column j-1 closes the cycle
-                if (lane == 0) {
-                    gs->done = done_val;
-                    report_progress(gc.progress, gc.gen, j, 1);
-                }
-            }
-        }
-        if (lane == 0) flags[0] = st;
-    }
-    const bool col_on = !last && rho > 0.0;
-    if (col_on && r >= 0 && r <= j) {
-        double hs = 0.0;
-        if (j > 0 && reorth) {
-            if (hs_on)
-                for (int w = 0; w < kWaves; ++w) hs += hpart[w][r];
-            hs += Hc[r] * sv[j - 1];
-        }
-        const double h = ((r < j ? t_r : cj) - hs) / rho;
-        colj[r] = h;
-        gs->H[(size_t)j * ld + r] = h;
-        if (r == j) gs->H[(size_t)j * ld + j + 1] = hh;
-    }
-    __syncthreads();
-    if (j > 0 && tid < j && !dr_first) gs->R[(size_t)(j - 1) * ld + tid] = Rl[0][tid];
-    if (!(col_on && !flags[0] && !(hh > 0.0))) return;  // uniform
-    // the Krylov space is invariant: column j is final with a zero subdiagonal
-    if (dk > 0) {                                       // Q^T of the kept block on its rows 0 .. dk
-        double t = 0.0;
-        if (tid <= dk)
-            for (int l = 0; l <= dk; ++l) t += qt[l * (dk + 1) + tid] * colj[l];
-        __syncthreads();
-        if (tid < dk) Rl[1][tid] = t;
-        if (tid == dk) dr_x0 = t;
-        __syncthreads();
-    }
-    if (tid == 0) colj[j + 1] = 0.0;
-    __syncthreads();
-    if (wave == 0) {
-        const double gj = gs->gin[j];
-        if (dk > 0) givens_column(j, colj, cl, sl, gj, Rl[1], gc, gs, done_val, dk, dr_x0);
-        else givens_column(j, colj, cl, sl, gj, Rl[1], gc, gs, done_val);
-        if (lane == 0) {
-            gs->done = done_val;
-            report_progress(gc.progress, gc.gen, j + 1, 1);
-        }
-    }
-    __syncthreads();
-    if (tid <= j) gs->R[(size_t)j * ld + tid] = Rl[1][tid];
-}
-
-// The tail of a cycle: column j-1 from the last vector's second pass.
+// The tail of a cycle: column j-1 from the last vector's second pass, and its rotation.
 __global__ __launch_bounds__(kBlock) void columns_kernel(int j, int dk, GmresState* gs) {
-    const ColLoads c = columns_load(j, dk, gs, true, 1);
+    const ColLoads c = columns_load(j, gs, true);
     if (gs->done) return;
-    arnoldi_columns(j, gs, nullptr, c);
+    columns_close(j, dk, gs, nullptr, c);
+    __syncthreads();
+    columns_rotate(j, dk, gs, 1, true);
 }
 
 // ------------------------------------------------------------- fused step (3 launches per step)
@@ -1114,7 +1130,7 @@ __global__ __launch_bounds__(kBlock) void columns_kernel(int j, int dk, GmresSta
 // (kFusedChunks per slot, four lanes per slot) and forms rho, c_j, hh exactly as the reduction
 // kernel does, in the same order everywhere, so all workgroups agree bitwise.  The basis loads
 // of the first batch are issued before, and wait out, that work.  Workgroup 0 also stores the
-// free-pressure sums S(q_j), S(u_{j+1}) for later steps and runs arnoldi_columns from LDS.
+// free-pressure sums S(q_j), S(u_{j+1}) for later steps and runs columns_close from LDS.
 constexpr int kFusedChunks = 16;                                     // dot partials per slot
 constexpr int kFusedLanes = 4;                                       // lanes per slot
 constexpr int kFusedPer = kFusedChunks / kFusedLanes;                // partials per lane
@@ -1231,10 +1247,7 @@ __device__ __forceinline__ bool step_scalars(int j, int nchunks, const double* _
         if (sub == 0 && slot < ns) L.sums[slot] = a;
     }
     __syncthreads();
-    // stopped by an earlier launch (cycle start: 1; the update of step j' < j: j' + 2); a stop
-    // that workgroup 0 of this launch publishes (j + 2) does not count, since q_j is still due
-    const int dw = L.flags[0];
-    if (dw != 0 && dw <= j + 1) return false;
+    if (L.flags[0]) return false;              // the cycle stopped in an earlier launch
     // every wave forms the scalars itself (the wave sums leave them in every lane), so that no
     // second barrier is needed; all lanes and workgroups do the same operations in the same order
     const int reorth = L.flags[1];
@@ -1274,14 +1287,14 @@ template <typename T, int R>
 __global__ __launch_bounds__(kBlock, sizeof(T) * R > 8 ? 4 : 5) void update_fused_kernel(int n, int xrows, int j, T* __restrict__ V,
                                                               const T* __restrict__ w, int nchunks,
                                                               const double* __restrict__ part, GmresState* gs,
-                                                              double eps_dot, int dk, int report) {
+                                                              double eps_dot, int dk) {
     __shared__ StepLds L;
     StepOut o;
     if (blockIdx.x == 0) {
         // the launch lasts as long as this workgroup: its waves go first on their CU
         __builtin_amdgcn_s_setprio(3);
         const StepLoads sl = step_load(j, nchunks, part, gs);
-        const ColLoads c = columns_load(j, dk, gs, false, report);
+        const ColLoads c = columns_load(j, gs, false);
         if (!step_scalars(j, nchunks, part, sl, eps_dot, L, o)) return;
         if (threadIdx.x == 0) {
             gs->rho = o.rho;
@@ -1291,7 +1304,7 @@ __global__ __launch_bounds__(kBlock, sizeof(T) * R > 8 ? 4 : 5) void update_fuse
             gs->svs[j] = o.svj;
         }
         const StepIn in{L.sums, o.rho, o.cj, o.hh, L.flags[1]};
-        arnoldi_columns(j, gs, &in, c);
+        columns_close(j, dk, gs, &in, c);
         return;
     }
     // R rows per thread, each row's loads coalesced across the workgroup; workgroup b runs on
@@ -1693,13 +1706,15 @@ int run_cycle(vms_ctx* c, const T* r0, const TM* Minv, TX* x, double tol_abs, in
                                                                               c->dmask, c->zfull, c->gs, z);
                 });
                 timed(VMS_PH_SPMV, spmv_bytes, j, st, [&] {
-                    spmv_kernel<TM, T, T, T, 0><<<spmv_grid(c->n_nodes), kBlock, 0, st>>>(
-                        c->n_nodes, c->rowptr, c->colidx, Amat, z, (const double*)nullptr, w, &c->gs->done, c->gs);
+                    spmv_kernel<TM, T, T, T, 0, double, true><<<1 + spmv_grid(c->n_nodes), kBlock, 0, st>>>(
+                        c->n_nodes, c->rowptr, c->colidx, Amat, z, (const double*)nullptr, w, c->gs, j - 1, j0,
+                        lead ? 1 : 0);
                 });
             } else {
                 timed(VMS_PH_SPMV, spmv_bytes, j, st, [&] {
-                    spmv_kernel<TM, T, T, T, 2, TM><<<spmv_grid(c->n_nodes), kBlock, 0, st>>>(
-                        c->n_nodes, c->rowptr, c->colidx, AP, V + (size_t)j * n, Az, w, &c->gs->done, c->gs);
+                    spmv_kernel<TM, T, T, T, 2, TM, true><<<1 + spmv_grid(c->n_nodes), kBlock, 0, st>>>(
+                        c->n_nodes, c->rowptr, c->colidx, AP, V + (size_t)j * n, Az, w, c->gs, j - 1, j0,
+                        lead ? 1 : 0);
                 });
             }
             timed(VMS_PH_DOTS, (j + 2) * vb, j, st, [&] {
@@ -1715,16 +1730,16 @@ int run_cycle(vms_ctx* c, const T* r0, const TM* Minv, TX* x, double tol_abs, in
                 const int nsum = wide ? 1 : nch;
                 if (sizeof(T) == 4 || wide)
                     update_fused_kernel<T, 2><<<1 + kXcds * grid_for(xrows, 2 * kBlock), kBlock, 0, st>>>(
-                        n, xrows, j, V, w, nsum, sums, c->gs, eps_dot, j0, lead ? 1 : 0);
+                        n, xrows, j, V, w, nsum, sums, c->gs, eps_dot, j0);
                 else
                     update_fused_kernel<T, 1><<<1 + kXcds * grid_for(xrows, kBlock), kBlock, 0, st>>>(
-                        n, xrows, j, V, w, nsum, sums, c->gs, eps_dot, j0, lead ? 1 : 0);
+                        n, xrows, j, V, w, nsum, sums, c->gs, eps_dot, j0);
             });
         }
         // the second pass of the last vector completes the last column
         dots_kernel<T><<<dim3(nch, steps_ + 2), kDotThreads, 0, st>>>(c->n_nodes, steps_, V, w, c->dmask, part,
                                                                       c->gs);
-        reduce_kernel<<<1, kRedThreads, 0, st>>>(steps_, nch, part, c->gs, eps_dot);
+        reduce_kernel<<<2, kRedThreads, 0, st>>>(steps_, nch, part, c->gs, eps_dot, j0, lead ? 1 : 0);
         columns_kernel<<<1, kBlock, 0, st>>>(steps_, j0, c->gs);
         return VMS_OK;
     };
@@ -1846,7 +1861,7 @@ int dr_restart(vms_ctx* c, int m, int j0, int deflate, hipStream_t s, int* kk) {
                        "read cycle state");
     if (!rc) rc = check_hip(c, hipStreamSynchronize(s), "sync");
     if (rc) return rc;
-    const double rho = h->rho;
+    const double rho = h->rho_m;
     if (!(rho > 0.0) || !std::isfinite(rho)) return VMS_OK;
     // Hbar (m+1) x m, entries below each column's last row cleared: the kept block's columns end
     // at row j0, an Arnoldi column j at row j + 1
@@ -1885,16 +1900,8 @@ int dr_restart(vms_ctx* c, int m, int j0, int deflate, hipStream_t s, int* kk) {
     dr_load_kernel<<<1, kBlock, 0, s>>>(k, c->dr_p, c->gs);
     const int n = 4 * c->n_nodes;
     launch_dr_basis<T>(n, mp, k, c->dr_p, mp, basis_vectors<T>(c, 0), s);
-    c->dr_k_dev = k;
     *kk = k;
     return check_hip(c, hipGetLastError(), "deflation launch");
-}
-
-// Switch deflated restarting off for the next cycle.
-void dr_off(vms_ctx* c, hipStream_t s) {
-    if (c->dr_k_dev == 0) return;
-    dr_load_kernel<<<1, kBlock, 0, s>>>(0, c->dr_p, c->gs);
-    c->dr_k_dev = 0;
 }
 
 }  // namespace
@@ -1915,10 +1922,10 @@ int launch_spmv(vms_ctx* c, const void* A, const void* x, void* y, hipStream_t s
     const int n = 4 * c->n_nodes;
     if (c->prec == VMS_FP64)
         spmv_kernel<double, double, double, double, 0><<<spmv_grid(c->n_nodes), kBlock, 0, s>>>(
-            c->n_nodes, c->rowptr, c->colidx, (const double*)A, (const double*)x, (const double*)nullptr, (double*)y, nullptr, nullptr);
+            c->n_nodes, c->rowptr, c->colidx, (const double*)A, (const double*)x, (const double*)nullptr, (double*)y, nullptr);
     else
         spmv_kernel<float, float, float, float, 0><<<spmv_grid(c->n_nodes), kBlock, 0, s>>>(
-            c->n_nodes, c->rowptr, c->colidx, (const float*)A, (const float*)x, (const double*)nullptr, (float*)y, nullptr, nullptr);
+            c->n_nodes, c->rowptr, c->colidx, (const float*)A, (const float*)x, (const double*)nullptr, (float*)y, nullptr);
     return check_hip(c, hipGetLastError(), "spmv launch");
 }
 
@@ -1962,7 +1969,7 @@ int launch_ap_setup(vms_ctx* c, const void* A, hipStream_t s) {
         if (c->zfull)
             spmv_kernel<double, double, double, double, 0><<<spmv_grid(c->n_nodes), kBlock, 0, s>>>(
                 c->n_nodes, c->rowptr, c->colidx, (const double*)A, c->zfull, (const double*)nullptr,
-                (double*)c->Az, nullptr, nullptr);
+                (double*)c->Az, nullptr);
         else
             coarse_column_kernel<double><<<grid_for(4 * (int64_t)c->n_nodes), kBlock, 0, s>>>(
                 c->n_nodes, c->rowptr, c->colidx, (const double*)A, c->dmask, (double*)c->Az);
@@ -1972,7 +1979,7 @@ int launch_ap_setup(vms_ctx* c, const void* A, hipStream_t s) {
         if (c->zfull)
             spmv_kernel<float, double, float, double, 0><<<spmv_grid(c->n_nodes), kBlock, 0, s>>>(
                 c->n_nodes, c->rowptr, c->colidx, (const float*)A, c->zfull, (const double*)nullptr,
-                (float*)c->Az, nullptr, nullptr);
+                (float*)c->Az, nullptr);
         else
             coarse_column_kernel<float><<<grid_for(4 * (int64_t)c->n_nodes), kBlock, 0, s>>>(
                 c->n_nodes, c->rowptr, c->colidx, (const float*)A, c->dmask, (float*)c->Az);
@@ -1985,10 +1992,10 @@ static int true_residual(vms_ctx* c, const void* A, const double* b, const doubl
     const int n = 4 * c->n_nodes;
     if (c->prec == VMS_FP64)
         spmv_kernel<double, double, double, double, 1><<<spmv_grid(c->n_nodes), kBlock, 0, s>>>(
-            c->n_nodes, c->rowptr, c->colidx, (const double*)A, x, b, c->r64, nullptr, nullptr);
+            c->n_nodes, c->rowptr, c->colidx, (const double*)A, x, b, c->r64, nullptr);
     else
         spmv_kernel<float, double, double, double, 1><<<spmv_grid(c->n_nodes), kBlock, 0, s>>>(
-            c->n_nodes, c->rowptr, c->colidx, (const float*)A, x, b, c->r64, nullptr, nullptr);
+            c->n_nodes, c->rowptr, c->colidx, (const float*)A, x, b, c->r64, nullptr);
     launch_norm<double>(c, n, c->r64, 0, s);
     return read_scalar(c, 0, rn, s);
 }
@@ -2092,7 +2099,6 @@ int gmres_solve(vms_ctx* c, const void* A, const double* b, double* x, const vms
     bool dr_ready = false;         // the last cycle ran all its steps: its basis can be deflated
     bool dr_live = deflate > 0;    // deflation still in use in this solve
     double rn_start = 0.0;         // true residual before the cycle in flight
-    dr_off(c, s);
     for (;;) {
         if ((rc = true_residual(c, A, b, x, &rn, s))) return rc;      // synchronises
         int last_k = -1;
@@ -2151,7 +2157,6 @@ int gmres_solve(vms_ctx* c, const void* A, const double* b, double* x, const vms
             if (rc) return rc;
             dr_ready = false;
         }
-        if (kk == 0) dr_off(c, s);
         j0 = kk;
         rn_start = rn;
         if (j0 > 0 &&
@@ -2207,7 +2212,7 @@ int gmres_solve(vms_ctx* c, const void* A, const double* b, double* x, const vms
                                                   cap - iters, cgs2, s)))
                     return rc;
                 spmv_kernel<float, float, float, float, 1, float><<<spmv_grid(c->n_nodes), kBlock, 0, s>>>(
-                    c->n_nodes, c->rowptr, c->colidx, (const float*)A, d, rr, q, nullptr, nullptr);
+                    c->n_nodes, c->rowptr, c->colidx, (const float*)A, d, rr, q, nullptr);
                 launch_norm<float>(c, n, q, 2, s);
                 double qn = 0.0;
                 if ((rc = read_scalar(c, 2, &qn, s))) return rc;     // synchronises

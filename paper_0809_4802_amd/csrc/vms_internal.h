@@ -132,21 +132,19 @@ struct GmresState {
     double su;                     // sum of the free pressure entries of u_j
     double st;                     // sum of the free pressure entries of the correction V y
     double rho;                    // norm of u_j after its second pass
+    double rho_m;                  // the same of a cycle's last vector
     double cj;                     // q_j . w
     double hh;                     // provisional subdiagonal of column j (norm estimate of u_{j+1})
     int reorth;                    // 0: one Gram-Schmidt pass; otherwise a delayed second pass
     int k;                         // Arnoldi steps completed in this cycle
-    int done;                      // 0 while the cycle runs; nonzero once it stopped (converged or
-                                   // breakdown), later kernels idle: 1 when the cycle start or the
-                                   // tail stopped it, j + 2 when the update launch of step j did
-                                   // (its other workgroups still finish step j)
+    int done;                      // 0 while the cycle runs; 1 once it stopped (converged or
+                                   // breakdown), later kernels idle
     unsigned counter;              // arrival counter of last-block reductions
     unsigned gen;                  // cycle number (host-assigned) reported with the progress word
     uint64_t* progress;            // host-mapped progress word: gen << 32 | k << 1 | done
-    // deflated restarting: the cycle starts with dr_k kept vectors V[0 .. dr_k-1], whose
-    // columns of H (rows 0 .. dr_k) and R the host set; dr_qt is Q^T of the QR factors of that
-    // (dr_k + 1) x dr_k block (column-major), dr_c the cycle's least-squares right-hand side
-    int dr_k;
+    // deflated restarting: the cycle starts with dk kept vectors V[0 .. dk-1], whose
+    // columns of H (rows 0 .. dk) and R the host set; dr_qt is Q^T of the QR factors of that
+    // (dk + 1) x dk block (column-major), dr_c the cycle's least-squares right-hand side
     double dr_qt[(kDrMax + 1) * (kDrMax + 1)];
     double dr_c[kDrMax + 1];
 };
@@ -248,7 +246,6 @@ struct vms_ctx {
     double* dr_p = nullptr;              // [kDrUpload] device copy of the packed upload
     void* dr_pinned = nullptr;           // pinned host [kDrStagingBytes]: a GmresState read back
                                          // (kDrStateBytes), then the packed upload
-    int dr_k_dev = 0;                    // the dr_k last written to the device state
     int64_t prof_cycles = 0;             // cycles seen while the phase timers are on
     bool prof_force = false;             // a sampled cycle: every launch of a timed phase is timed
 
