@@ -11,8 +11,6 @@
 #include <cstring>
 #include <vector>
 
-#include <map>
-
 #include "vms_internal.h"
 
 namespace {
@@ -126,7 +124,7 @@ static void free_all(vms_ctx* c) {
         c->full = nullptr;
     }
     void* ptrs[] = {c->full_cc, c->full_epos, c->zfull, c->xyz4, c->tets, c->dmask, c->dlist, c->rowptr, c->colidx, c->diagpos,
-                    c->tpos, c->tile_meta, c->tile_nodes, c->items, c->bmask, c->tile_part, c->A, c->rhs, c->du, c->rnorm, c->flags,
+                    c->tpos, c->tile_meta, c->tile_nodes, c->items, c->bmask, c->tile_part, c->rtile_meta, c->rtile_nodes, c->ritems, c->n2e_ptr, c->A, c->rhs, c->du, c->rnorm, c->flags,
                     c->V, c->w, c->z, c->d, c->r, c->Minv, c->AP, c->Az, c->x64, c->r64, c->gs, c->red,
                     c->feats, c->hid, c->pblk, c->gblk, c->gdel, c->tvec, c->wgrad, c->fscal, c->dr_p,
                     c->V64, c->w64, c->z64};
@@ -374,24 +372,33 @@ extern "C" int vms_create(const vms_mesh_desc* mesh, const vms_create_opts* opts
     for (int64_t i = 0; i < 4 * ne; ++i) n2e_ptr[tets[i] + 1]++;
     for (int64_t i = 0; i < nn; ++i) n2e_ptr[i + 1] += n2e_ptr[i];
     n2e.resize(n2e_ptr[nn]);
+    std::vector<int32_t> n2e_pos(4 * ne);         // where vertex a of element e lists it
     {
         std::vector<int32_t> fill(n2e_ptr.begin(), n2e_ptr.end() - 1);
         for (int64_t e = 0; e < ne; ++e)
-            for (int a = 0; a < 4; ++a) n2e[fill[tets[4 * e + a]]++] = (int32_t)e;
+            for (int a = 0; a < 4; ++a) {
+                const int32_t q = fill[tets[4 * e + a]]++;
+                n2e[q] = (int32_t)e;
+                n2e_pos[4 * e + a] = q;
+            }
     }
     // rows of the block pattern: sorted unique neighbours (including self)
     std::vector<int32_t> rowptr(nn + 1, 0), colidx;
     colidx.reserve(16 * nn);
-    std::vector<int32_t> scratch;
+    std::vector<int32_t> scratch, seen(nn, -1);
     for (int64_t i = 0; i < nn; ++i) {
         scratch.clear();
-        for (int32_t k = n2e_ptr[i]; k < n2e_ptr[i + 1]; ++k) {
-            const int32_t* t = &tets[4 * (int64_t)n2e[k]];
-            scratch.insert(scratch.end(), t, t + 4);
-        }
-        if (scratch.empty()) scratch.push_back((int32_t)i);   // isolated node: diagonal only
+        seen[i] = (int32_t)i;
+        scratch.push_back((int32_t)i);
+        for (int32_t k = n2e_ptr[i]; k < n2e_ptr[i + 1]; ++k)
+            for (int a = 0; a < 4; ++a) {
+                const int32_t v = tets[4 * (int64_t)n2e[k] + a];
+                if (seen[v] != (int32_t)i) {
+                    seen[v] = (int32_t)i;
+                    scratch.push_back(v);
+                }
+            }
         std::sort(scratch.begin(), scratch.end());
-        scratch.erase(std::unique(scratch.begin(), scratch.end()), scratch.end());
         colidx.insert(colidx.end(), scratch.begin(), scratch.end());
         rowptr[i + 1] = (int32_t)colidx.size();
     }
@@ -440,7 +447,9 @@ extern "C" int vms_create(const vms_mesh_desc* mesh, const vms_create_opts* opts
     items.reserve(4 * ne);
     size_t lds_max = 0, lds_max_tr = 0;
     {
-        std::vector<int32_t> stamp(nn, -1), loc(nn, 0), cand, halo;
+        std::vector<int32_t> stamp(nn, -1), hstamp(nn, -1), loc(nn, 0), cand, halo, rem;
+        std::vector<std::pair<int32_t, int>> cnt;
+        std::vector<std::vector<Quad>> row_quads[2];      // per row: the quads that share an edge, the others
         int64_t r0 = 0;
         int32_t tile = 0;
         while (r0 < nn) {
@@ -454,14 +463,8 @@ extern "C" int vms_create(const vms_mesh_desc* mesh, const vms_create_opts* opts
             int32_t ndist = 0;
             while (r1 < nn && r1 - r0 < kTileNodes && rowptr[r1 + 1] - rowptr[r0] <= max_blocks) {
                 cand.clear();
-                if (stamp[r1] != tile) cand.push_back((int32_t)r1);
-                for (int32_t k = n2e_ptr[r1]; k < n2e_ptr[r1 + 1]; ++k)
-                    for (int a = 0; a < 4; ++a) {
-                        const int32_t v = tets[4 * (int64_t)n2e[k] + a];
-                        if (stamp[v] != tile) cand.push_back(v);
-                    }
-                std::sort(cand.begin(), cand.end());
-                cand.erase(std::unique(cand.begin(), cand.end()), cand.end());
+                for (int32_t k = rowptr[r1]; k < rowptr[r1 + 1]; ++k)      // the node and its neighbours
+                    if (stamp[colidx[k]] != tile) cand.push_back(colidx[k]);
                 if (ndist + (int64_t)cand.size() > kTileMaxNodes) break;
                 for (int32_t v : cand) stamp[v] = tile;
                 ndist += (int32_t)cand.size();
@@ -476,14 +479,15 @@ extern "C" int vms_create(const vms_mesh_desc* mesh, const vms_create_opts* opts
             halo.clear();
             for (int64_t i = r0; i < r1; ++i) {
                 loc[i] = (int32_t)(i - r0);
-                for (int32_t k = n2e_ptr[i]; k < n2e_ptr[i + 1]; ++k)
-                    for (int a = 0; a < 4; ++a) {
-                        const int32_t v = tets[4 * (int64_t)n2e[k] + a];
-                        if (v < r0 || v >= r1) halo.push_back(v);
+                for (int32_t k = rowptr[i]; k < rowptr[i + 1]; ++k) {
+                    const int32_t v = colidx[k];
+                    if ((v < r0 || v >= r1) && hstamp[v] != tile) {
+                        hstamp[v] = tile;
+                        halo.push_back(v);
                     }
+                }
             }
             std::sort(halo.begin(), halo.end());
-            halo.erase(std::unique(halo.begin(), halo.end()), halo.end());
             for (size_t j = 0; j < halo.size(); ++j) loc[halo[j]] = (int32_t)(r1 - r0 + (int64_t)j);
             for (int64_t i = r0; i < r1; ++i) tnodes.push_back((int32_t)i);
             tnodes.insert(tnodes.end(), halo.begin(), halo.end());
@@ -500,67 +504,63 @@ extern "C" int vms_create(const vms_mesh_desc* mesh, const vms_create_opts* opts
             // add into different rows.
             // Without quads (quads == false) every quad holds one item: the items of the owned rows
             // go round-robin (the r-th element of every owned row, then the (r+1)-th, ...).
-            std::vector<std::vector<Quad>> row_quads(r1 - r0);
-            int32_t rounds = 0;
+            size_t rounds[2] = {0, 0};
+            for (auto& rq : row_quads) {
+                rq.resize(r1 - r0);
+                for (auto& qs : rq) qs.clear();
+            }
             for (int64_t i = r0; i < r1; ++i) {
-                auto& qs = row_quads[i - r0];
-                std::vector<int32_t> rem(n2e.begin() + n2e_ptr[i], n2e.begin() + n2e_ptr[i + 1]);
+                if (!quads) {
+                    for (int32_t k = n2e_ptr[i]; k < n2e_ptr[i + 1]; ++k)
+                        row_quads[1][i - r0].push_back(Quad{{n2e[k]}, 1, -1});
+                    rounds[1] = std::max(rounds[1], row_quads[1][i - r0].size());
+                    continue;
+                }
+                rem.assign(n2e.begin() + n2e_ptr[i], n2e.begin() + n2e_ptr[i + 1]);
                 while (!rem.empty()) {
                     Quad q{};
                     q.j = -1;
-                    if (!quads) {
-                        q.e[0] = rem.front();
-                        q.n = 1;
-                        rem.erase(rem.begin());
-                        qs.push_back(q);
-                        continue;
-                    }
                     if (rem.size() >= 4) {
-                        // the neighbour shared by the most remaining elements
-                        std::map<int32_t, int> cnt;
+                        // the neighbour shared by the most remaining elements (the smallest of them)
+                        cnt.clear();
                         for (int32_t e : rem)
                             for (int b = 0; b < 4; ++b) {
                                 const int32_t v = tets[4 * (int64_t)e + b];
-                                if (v != i) cnt[v]++;
+                                if (v == i) continue;
+                                size_t p = 0;
+                                while (p < cnt.size() && cnt[p].first != v) ++p;
+                                if (p == cnt.size()) cnt.push_back({v, 0});
+                                cnt[p].second++;
                             }
                         int32_t best = -1;
                         int bc = 0;
                         for (auto& kv : cnt)
-                            if (kv.second > bc) best = kv.first, bc = kv.second;
+                            if (kv.second > bc || (kv.second == bc && kv.first < best)) best = kv.first, bc = kv.second;
                         if (bc >= 4) q.j = best;
                     }
                     int taken = 0;
-                    for (size_t k = 0; k < rem.size() && taken < 4;) {
+                    size_t left = 0;
+                    for (size_t k = 0; k < rem.size(); ++k) {
                         const int32_t e = rem[k];
-                        bool has = q.j < 0;
-                        for (int b = 0; b < 4 && !has; ++b) has = tets[4 * (int64_t)e + b] == q.j;
-                        if (has) {
-                            q.e[taken++] = e;
-                            rem.erase(rem.begin() + k);
-                        } else {
-                            ++k;
-                        }
+                        bool has = taken < 4 && q.j < 0;
+                        for (int b = 0; b < 4 && taken < 4 && !has; ++b) has = tets[4 * (int64_t)e + b] == q.j;
+                        if (has) q.e[taken++] = e;
+                        else rem[left++] = e;
                     }
+                    rem.resize(left);
                     q.n = taken;
+                    auto& qs = row_quads[q.j >= 0 ? 0 : 1][i - r0];
                     qs.push_back(q);
+                    rounds[q.j >= 0 ? 0 : 1] = std::max(rounds[q.j >= 0 ? 0 : 1], qs.size());
                 }
-                rounds = std::max(rounds, (int32_t)qs.size());
             }
             const int32_t b0 = rowptr[r0];
             for (int kind = 0; kind < 2; ++kind) {
-                for (int32_t r = 0; r < rounds; ++r)
+                for (size_t r = 0; r < rounds[kind]; ++r)
                     for (int64_t i = r0; i < r1; ++i) {
                         // kind 0: the r-th quad of row i that shares an edge; kind 1: the r-th other one
-                        const auto& qs = row_quads[i - r0];
-                        int32_t seen = -1;
-                        const Quad* qp = nullptr;
-                        for (const Quad& cand : qs)
-                            if ((cand.j >= 0) == (kind == 0) && ++seen == r) {
-                                qp = &cand;
-                                break;
-                            }
-                        if (!qp) continue;
-                        const Quad& q = *qp;
+                        if (r >= row_quads[kind][i - r0].size()) continue;
+                        const Quad& q = row_quads[kind][i - r0][r];
                         for (int m = 0; m < (quads ? 4 : 1); ++m) {
                             const bool dummy = m >= q.n;
                             const int32_t e = q.e[dummy ? 0 : m];
@@ -611,6 +611,93 @@ extern "C" int vms_create(const vms_mesh_desc* mesh, const vms_create_opts* opts
     c->tile_lds = lds_max;
     c->tile_lds_tr = lds_max_tr;
 
+    // Residual tiles: contiguous node ranges, as large as their element rows, their staged nodes and
+    // the cap on owned nodes allow.  Owned nodes first in the local numbering, then the others as
+    // they are met.  An item's vertices: owned ones first, as an even permutation; the items with
+    // most owned vertices first, so that the lanes of a wave have alike numbers of rows.
+    std::vector<int4> rmeta;
+    std::vector<int32_t> rnodes;
+    std::vector<uint4> ritems;
+    size_t rlds[2] = {};
+    {
+        std::vector<int32_t> nstamp(nn, -1), loc(nn, 0), estamp(ne, -1), fresh;
+        std::vector<uint4> sorted[4];
+        int64_t r0 = 0;
+        for (int32_t tile = 0; r0 < nn; ++tile) {
+            int64_t r1 = r0;
+            int32_t ntn = 0;
+            while (r1 < nn && r1 - r0 < kResidualNodes &&
+                   (r1 == r0 || n2e_ptr[r1 + 1] - n2e_ptr[r0] <= kResidualSlots)) {
+                fresh.clear();
+                for (int32_t k = rowptr[r1]; k < rowptr[r1 + 1]; ++k)      // the node and its neighbours
+                    if (nstamp[colidx[k]] != tile) fresh.push_back(colidx[k]);
+                if (ntn + (int64_t)fresh.size() > kTileMaxNodes) break;
+                for (int32_t v : fresh) nstamp[v] = tile;
+                ntn += (int32_t)fresh.size();
+                ++r1;
+            }
+            if (n2e_ptr[r1] - n2e_ptr[r0] >= kNoSlot) {
+                free_all(c);
+                delete c;
+                return set_error(nullptr, VMS_EINVAL, "vms_create: node " + std::to_string(r0) +
+                                                          " has more elements than a tile's records number");
+            }
+            const int32_t nbase = (int32_t)rnodes.size(), ibase = (int32_t)ritems.size();
+            for (int64_t i = r0; i < r1; ++i) {
+                loc[i] = (int32_t)(i - r0);
+                rnodes.push_back((int32_t)i);
+            }
+            for (int64_t i = r0; i < r1; ++i)
+                for (int32_t k = n2e_ptr[i]; k < n2e_ptr[i + 1]; ++k) {
+                    const int32_t e = n2e[k];
+                    if (estamp[e] == tile) continue;
+                    estamp[e] = tile;
+                    const int32_t* t = &tets[4 * (int64_t)e];
+                    bool own[4];
+                    int count = 0, ord[4], m = 0;
+                    for (int a = 0; a < 4; ++a) {
+                        own[a] = t[a] >= r0 && t[a] < r1;
+                        count += own[a];
+                        if (!own[a] && nstamp[t[a]] == tile) {     // met for the first time
+                            nstamp[t[a]] = -2 - tile;
+                            loc[t[a]] = (int32_t)rnodes.size() - nbase;
+                            rnodes.push_back(t[a]);
+                        }
+                    }
+                    for (int a = 0; a < 4; ++a)
+                        if (own[a]) ord[m++] = a;
+                    for (int a = 0; a < 4; ++a)
+                        if (!own[a]) ord[m++] = a;
+                    int inv = 0;
+                    for (int a = 0; a < 4; ++a)
+                        for (int b = a + 1; b < 4; ++b) inv += ord[a] > ord[b];
+                    if (inv & 1) std::swap(ord[count >= 3 ? 0 : 2], ord[count >= 3 ? 1 : 3]);
+                    uint32_t l = 0, slot[4];
+                    for (int a = 0; a < 4; ++a) {
+                        const int32_t v = t[ord[a]];
+                        l |= (uint32_t)loc[v] << (8 * a);
+                        slot[a] = 0xffffu;
+                        if (own[ord[a]]) slot[a] = (uint32_t)(n2e_pos[4 * (int64_t)e + ord[a]] - n2e_ptr[r0]);
+                    }
+                    sorted[count - 1].push_back(make_uint4((uint32_t)e | (own[0] ? 0x80000000u : 0u), l,
+                                                           slot[0] | (slot[1] << 16), slot[2] | (slot[3] << 16)));
+                }
+            for (int q = 3; q >= 0; --q) {
+                ritems.insert(ritems.end(), sorted[q].begin(), sorted[q].end());
+                sorted[q].clear();
+            }
+            const int32_t slots = n2e_ptr[r1] - n2e_ptr[r0];
+            rmeta.push_back(make_int4((int32_t)r0, (int32_t)r1, nbase, (int32_t)rnodes.size() - nbase));
+            rmeta.push_back(make_int4(ibase, (int32_t)ritems.size(), n2e_ptr[r0], slots));
+            for (int x = 0; x < 2; ++x)
+                rlds[x] = std::max(rlds[x], 32 * ((size_t)std::min(slots, kResidualSlots) +
+                                                  (rnodes.size() - nbase) * (2 + x)));
+            r0 = r1;
+        }
+    }
+    c->n_rtiles = (int32_t)(rmeta.size() / 2);
+    std::copy(rlds, rlds + 2, c->rtile_lds);
+
     std::vector<double> xyz4(4 * nn);
     for (int64_t i = 0; i < nn; ++i) {
         xyz4[4 * i + 0] = xyz[3 * i + 0];
@@ -633,7 +720,12 @@ extern "C" int vms_create(const vms_mesh_desc* mesh, const vms_create_opts* opts
     TRY(dev_alloc(c, &c->tile_nodes, tnodes.size() * sizeof(int32_t), "alloc tile nodes"));
     TRY(dev_alloc(c, &c->items, items.size() * sizeof(uint4), "alloc tile items"));
     TRY(dev_alloc(c, &c->bmask, c->nb * sizeof(uint16_t), "alloc block masks"));
-    TRY(dev_alloc(c, &c->tile_part, 2 * (size_t)c->n_tiles * sizeof(double), "alloc tile partials"));
+    TRY(dev_alloc(c, &c->tile_part, 2 * (size_t)std::max(c->n_tiles, c->n_rtiles) * sizeof(double),
+                  "alloc tile partials"));
+    TRY(dev_alloc(c, &c->rtile_meta, rmeta.size() * sizeof(int4), "alloc residual tiles"));
+    TRY(dev_alloc(c, &c->rtile_nodes, rnodes.size() * sizeof(int32_t), "alloc residual tile nodes"));
+    TRY(dev_alloc(c, &c->ritems, ritems.size() * sizeof(uint4), "alloc residual tile items"));
+    TRY(dev_alloc(c, &c->n2e_ptr, (nn + 1) * sizeof(int32_t), "alloc node-element pointers"));
     TRY(dev_alloc(c, &c->A, c->nb * 16 * es, "alloc A"));
     TRY(dev_alloc(c, &c->rhs, N * sizeof(double), "alloc rhs"));
     TRY(dev_alloc(c, &c->du, N * sizeof(double), "alloc du"));
@@ -707,6 +799,11 @@ extern "C" int vms_create(const vms_mesh_desc* mesh, const vms_create_opts* opts
                 bm[k] = (uint16_t)((dmask[colidx[k]] & 0xFu) | ((dmask[i] & 0xFu) << 4) | (colidx[k] == i ? 0x100u : 0u));
         TRY(check_hip(c, hipMemcpy(c->bmask, bm.data(), c->nb * sizeof(uint16_t), hipMemcpyHostToDevice), "upload"));
     }
+    TRY(check_hip(c, hipMemcpy(c->rtile_meta, rmeta.data(), rmeta.size() * sizeof(int4), hipMemcpyHostToDevice), "upload"));
+    TRY(check_hip(c, hipMemcpy(c->rtile_nodes, rnodes.data(), rnodes.size() * sizeof(int32_t), hipMemcpyHostToDevice),
+                  "upload"));
+    TRY(check_hip(c, hipMemcpy(c->ritems, ritems.data(), ritems.size() * sizeof(uint4), hipMemcpyHostToDevice), "upload"));
+    TRY(check_hip(c, hipMemcpy(c->n2e_ptr, n2e_ptr.data(), (nn + 1) * sizeof(int32_t), hipMemcpyHostToDevice), "upload"));
     TRY(check_hip(c, tile_kernels_configure(c), "configure tile kernels"));
     TRY(check_hip(c, hipMemset(c->red, 0, sizeof(RedScratch)), "clear"));
     TRY(check_hip(c, hipMemset(c->gs, 0, sizeof(GmresState)), "clear"));

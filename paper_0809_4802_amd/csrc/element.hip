@@ -360,11 +360,10 @@ __device__ __forceinline__ void atomic_add(T* p, T v) {
 // condensed block computed exactly once.  Each tile also leaves two partial sums of the Newton
 // residual norm (its free residual rows squared, and |R_f|^2 of the elements whose first
 // vertex it owns), which a one-workgroup kernel adds in a fixed order.
-//   CONDENSE = true : K* into Aval, -R* into rhs, R_cp into rglob (if not null), partials
-//   CONDENSE = false: R_cp into rglob (if not null), partials (residual only)
-//   SCHUR = false (with CONDENSE): the coarse blocks without condensation, K_cc into Aval at the
-//   blocks' places in the uncondensed pattern and -R_cp into rhs (the node-node part of the
-//   uncondensed system, whose node rows come first)
+//   SCHUR = true : K* into Aval, -R* into rhs, R_cp into rglob (if not null), partials
+//   SCHUR = false: the coarse blocks without condensation, K_cc into Aval at the blocks' places in
+//   the uncondensed pattern and -R_cp into rhs (the node-node part of the uncondensed system,
+//   whose node rows come first)
 #ifndef VMS_TILE_THREADS
 #define VMS_TILE_THREADS 256
 #endif
@@ -531,7 +530,7 @@ __device__ __forceinline__ void add_blocks(const BlockFactors<T>& F, TACC* __res
     }
 }
 
-template <typename T, typename TACC, bool CONDENSE, bool SCHUR = true, int NT = kTileThreads>
+template <typename T, typename TACC, bool SCHUR = true, int NT = kTileThreads>
 __global__ __launch_bounds__(NT, VMS_TILE_WAVES_PER_SIMD) void tile_kernel(
     ElemArgs args, TileArgs ta, T* __restrict__ Aval, double* __restrict__ rhs, double* __restrict__ rglob,
     double* __restrict__ tile_part) {
@@ -543,7 +542,7 @@ __global__ __launch_bounds__(NT, VMS_TILE_WAVES_PER_SIMD) void tile_kernel(
     const int4 m0 = ta.meta[2 * t], m1 = ta.meta[2 * t + 1];
     const int n0 = m0.x, nn = m0.y - m0.x, b0 = m0.z, nbk = m0.w;
     TACC* blk = reinterpret_cast<TACC*>(smem);
-    const size_t off = CONDENSE ? align16((size_t)nbk * kLdsBlockStride * sizeof(TACC)) : 0;
+    const size_t off = align16((size_t)nbk * kLdsBlockStride * sizeof(TACC));
     double* rr = reinterpret_cast<double*>(smem + off);
     double* rg = rr + (size_t)nn * 4;
     // the tile's nodes: coordinates, state and (transient) previous state, one double4 each
@@ -568,15 +567,15 @@ __global__ __launch_bounds__(NT, VMS_TILE_WAVES_PER_SIMD) void tile_kernel(
 #pragma unroll
     for (int q = 0; q < kPre; ++q) {
         const int kb = threadIdx.x + q * (int)blockDim.x;
-        bm_pre[q] = (CONDENSE && kb < nbk) ? ta.bmask[b0 + kb] : 0u;
+        bm_pre[q] = kb < nbk ? ta.bmask[b0 + kb] : 0u;
         place_pre[q] = (!SCHUR && kb < nbk) ? ta.place[b0 + kb] : 0;
     }
     const uint32_t dm_pre = (int)threadIdx.x < nn * 4 ? args.dmask[n0 + (threadIdx.x >> 2)] : 0u;
     // zero the staged rows (blocks, then rhs and residual rows), 16 bytes per store; the block
     // region is padded to 16 bytes
     {
-        const int nz = (CONDENSE ? (int)(off / 16) : 0) + nn * 4;
-        double2* z = reinterpret_cast<double2*>(CONDENSE ? smem : smem + off);
+        const int nz = (int)(off / 16) + nn * 4;
+        double2* z = reinterpret_cast<double2*>(smem);
         for (int i = threadIdx.x; i < nz; i += blockDim.x) z[i] = make_double2(0.0, 0.0);
     }
     __syncthreads();
@@ -713,7 +712,6 @@ __global__ __launch_bounds__(NT, VMS_TILE_WAVES_PER_SIMD) void tile_kernel(
             for (int r = 0; r < 4; ++r)
                 if (live) atomic_add(&rg[4 * la + r], Rc[r]);
         }
-        if (!CONDENSE) continue;
 
         // Y = K_cf(0) K_ff^-1 (FP64, stored in T) and R*_0; zero without condensation
         double Yd[4][3] = {};
@@ -828,24 +826,22 @@ __global__ __launch_bounds__(NT, VMS_TILE_WAVES_PER_SIMD) void tile_kernel(
         add_blocks<QUADS, T, TACC>(F, blk, slot, live, share1, ql);
     }
     __syncthreads();
-    if (CONDENSE) {
-        // write the rows once, a block per thread, eliminating the Dirichlet dofs: zero rows and
-        // columns, unit diagonal
-        for (int q = 0, kb = threadIdx.x; kb < nbk; ++q, kb += blockDim.x) {
-            const uint32_t bm = q < kPre ? bm_pre[q] : ta.bmask[b0 + kb];
-            const TACC* src = blk + (size_t)kb * kLdsBlockStride;
-            const size_t place = SCHUR ? (size_t)b0 + kb : (size_t)(q < kPre ? place_pre[q] : ta.place[b0 + kb]);
-            T* dst = Aval + place * 16;
+    // write the rows once, a block per thread, eliminating the Dirichlet dofs: zero rows and
+    // columns, unit diagonal
+    for (int q = 0, kb = threadIdx.x; kb < nbk; ++q, kb += blockDim.x) {
+        const uint32_t bm = q < kPre ? bm_pre[q] : ta.bmask[b0 + kb];
+        const TACC* src = blk + (size_t)kb * kLdsBlockStride;
+        const size_t place = SCHUR ? (size_t)b0 + kb : (size_t)(q < kPre ? place_pre[q] : ta.place[b0 + kb]);
+        T* dst = Aval + place * 16;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                T v[4];
+        for (int r = 0; r < 4; ++r) {
+            T v[4];
 #pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    v[c] = T(src[4 * r + c]);
-                    if (((bm >> (4 + r)) | (bm >> c)) & 1u) v[c] = ((bm & 0x100u) && r == c) ? T(1) : T(0);
-                }
-                store4(dst + 4 * r, v);
+            for (int c = 0; c < 4; ++c) {
+                v[c] = T(src[4 * r + c]);
+                if (((bm >> (4 + r)) | (bm >> c)) & 1u) v[c] = ((bm & 0x100u) && r == c) ? T(1) : T(0);
             }
+            store4(dst + 4 * r, v);
         }
     }
     double rg2 = 0.0;
@@ -855,7 +851,7 @@ __global__ __launch_bounds__(NT, VMS_TILE_WAVES_PER_SIMD) void tile_kernel(
         const double rv = fixed ? 0.0 : rg[i];
         rg2 += rv * rv;
         if (rglob) rglob[4 * (size_t)n0 + i] = rv;
-        if (CONDENSE) rhs[4 * (size_t)n0 + i] = fixed ? 0.0 : rr[i];
+        rhs[4 * (size_t)n0 + i] = fixed ? 0.0 : rr[i];
     }
     rg2 = wave_sum(rg2);
     rf2 = wave_sum(rf2);
@@ -868,6 +864,222 @@ __global__ __launch_bounds__(NT, VMS_TILE_WAVES_PER_SIMD) void tile_kernel(
         double s = 0.0;
 #pragma unroll
         for (int w = 0; w < NT / 64; ++w) s += wsum[w][threadIdx.x];
+        tile_part[2 * (size_t)t + threadIdx.x] = s;
+    }
+}
+
+// Residual alone: R_cp into rglob (if not null) and the partial sums of its norm.  The tiles are
+// this kernel's own: a contiguous node range whose elements all compute once each (one item per
+// element and tile, in place of one per element and owned vertex as in the assembly: half as many
+// for 32 nodes) and which stage their nodes and every row they contribute in LDS.  With the
+// shared terms collected, a row costs one 3x3 product:
+//   R_c,a = c0 + G (m0 v_a + 2 nu |T| g_a) + m0 q_a - ((W + C beta / 2) . g_a) beta - |T|/4 (sum p) g_a,
+//   c0 = G (B1 beta + m0 sum v) - th B1 beta + m0 sum q,   q = (v - v^n) / dt - f.
+// Each row goes to its own slot, a node's slots side by side, and the nodes then sum theirs in
+// order: no atomics, and the same bits on every run.  Backward step of 218,400 elements with a body
+// force 23 us (FP64; 33 us as a form of the assembly kernel, 42 us with its one-wave tiles), cube
+// 48^3 transient 43 us (60 and 71); bound by the latency of its few rounds of loads and FP64 chains.
+constexpr int kResThreads = kResidualThreads;
+struct ResidualArgs {
+    const int4* __restrict__ meta;        // per tile: (n0, n1, node base, nodes), (item0, item1, slot base, slots)
+    const int32_t* __restrict__ nodes;
+    const uint4* __restrict__ items;      // x: element (bit 31: the tile owns its vertex 0); y: local nodes,
+                                          // owned ones first, orientation kept; z, w: their slots (0xffff: none)
+    const int32_t* __restrict__ n2e_ptr;  // a node's first slot, over the whole mesh
+};
+
+__global__ __launch_bounds__(kResThreads, 3) void residual_kernel(ElemArgs args, ResidualArgs ta,
+                                                                  double* __restrict__ rglob,
+                                                                  double* __restrict__ tile_part) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ double wsum[kResThreads / 64][2];
+    const int t = blockIdx.x;
+    const int4 m0_ = ta.meta[2 * t], m1 = ta.meta[2 * t + 1];
+    const int n0 = m0_.x, nn = m0_.y - m0_.x, ntn = m0_.w, slot0 = m1.z;
+    const int slots = min(m1.w, kResidualSlots);
+    double4* rows = reinterpret_cast<double4*>(smem);
+    double4* sx = rows + slots;
+    double4* su = sx + ntn;
+    double4* sq = su + ntn;                  // (v - v^n) / dt - f, where there is any of it
+    const bool transient = args.u_prev != nullptr && args.inv_dt != 0.0;
+    const bool extra = transient || args.body != nullptr;
+    const double nu = args.nu, inv_dt = transient ? args.inv_dt : 0.0;
+    for (int i = threadIdx.x; i < ntn; i += kResThreads) {
+        const int g = ta.nodes[m0_.z + i];
+        const double4 u = reinterpret_cast<const double4*>(args.u)[g];
+        sx[i] = args.xyz4[g];
+        su[i] = u;
+        if (extra) {
+            double q[3] = {0.0, 0.0, 0.0};
+            if (transient) {
+                const double4 up = reinterpret_cast<const double4*>(args.u_prev)[g];
+                q[0] = inv_dt * (u.x - up.x);
+                q[1] = inv_dt * (u.y - up.y);
+                q[2] = inv_dt * (u.z - up.z);
+            }
+            if (args.body)
+#pragma unroll
+                for (int c = 0; c < 3; ++c) q[c] -= args.body[3 * (size_t)g + c];
+            sq[i] = make_double4(q[0], q[1], q[2], 0.0);
+        }
+    }
+    // this thread's residual entry (a node's four entries on adjacent lanes) and its slots
+    static_assert(4 * kResidualNodes <= kResThreads, "one residual entry per thread");
+    const bool entry = (int)threadIdx.x < 4 * nn;
+    const int node = n0 + min((int)threadIdx.x >> 2, nn - 1), comp = threadIdx.x & 3;
+    const int q0 = ta.n2e_ptr[node] - slot0, q1 = entry ? ta.n2e_ptr[node + 1] - slot0 : q0;
+    const uint32_t dm = args.dmask[node];
+    double acc = 0.0, rf2 = 0.0;
+    // one pass, but for a tile whose single node has more elements than the LDS holds rows of
+    for (int first = 0; first == 0 || first < m1.w; first += kResidualSlots) {
+        uint4 rec_next = m1.x + (int)threadIdx.x < m1.y ? ta.items[m1.x + threadIdx.x] : make_uint4(0, 0, 0, 0);
+        __syncthreads();
+        for (int k = m1.x + threadIdx.x; k < m1.y; k += kResThreads) {
+            const uint4 rec = rec_next;
+            if (k + kResThreads < m1.y) rec_next = ta.items[k + kResThreads];
+            const int e = (int)(rec.x & 0x7fffffffu);
+            const double* bp = args.beta + 3 * (size_t)e;
+            const double be[3] = {bp[0], bp[1], bp[2]};
+            const int nl[4] = {(int)(rec.y & 255u), (int)((rec.y >> 8) & 255u), (int)((rec.y >> 16) & 255u),
+                               (int)(rec.y >> 24)};
+            // the slots of this pass; none (-1) for vertices of other tiles
+            int slot[4] = {(int)(rec.z & 0xffffu), (int)(rec.z >> 16), (int)(rec.w & 0xffffu), (int)(rec.w >> 16)};
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+                const int q = slot[a] - first;
+                slot[a] = (slot[a] != kNoSlot && q >= 0 && q < slots) ? q : -1;
+            }
+            double g[4][3], det;
+            {
+                double X[4][3], J[3][3];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const double4 x = sx[nl[q]];
+                    X[q][0] = x.x;
+                    X[q][1] = x.y;
+                    X[q][2] = x.z;
+                }
+#pragma unroll
+                for (int i = 0; i < 3; ++i)
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) J[i][c] = X[c + 1][i] - X[0][i];
+                const double c00 = J[1][1] * J[2][2] - J[1][2] * J[2][1];
+                const double c01 = J[1][2] * J[2][0] - J[1][0] * J[2][2];
+                const double c02 = J[1][0] * J[2][1] - J[1][1] * J[2][0];
+                det = J[0][0] * c00 + J[0][1] * c01 + J[0][2] * c02;
+                if (!(det > 0.0)) {
+                    // a degenerate element is flagged and contributes nothing
+                    flag_element(args, 0, e);
+#pragma unroll
+                    for (int a = 0; a < 4; ++a)
+                        if (slot[a] >= 0) rows[slot[a]] = make_double4(0.0, 0.0, 0.0, 0.0);
+                    continue;
+                }
+                const double id = 1.0 / det;
+                g[1][0] = c00 * id;
+                g[1][1] = (J[0][2] * J[2][1] - J[0][1] * J[2][2]) * id;
+                g[1][2] = (J[0][1] * J[1][2] - J[0][2] * J[1][1]) * id;
+                g[2][0] = c01 * id;
+                g[2][1] = (J[0][0] * J[2][2] - J[0][2] * J[2][0]) * id;
+                g[2][2] = (J[0][2] * J[1][0] - J[0][0] * J[1][2]) * id;
+                g[3][0] = c02 * id;
+                g[3][1] = (J[0][1] * J[2][0] - J[0][0] * J[2][1]) * id;
+                g[3][2] = (J[0][0] * J[1][1] - J[0][1] * J[1][0]) * id;
+#pragma unroll
+                for (int i = 0; i < 3; ++i) g[0][i] = -(g[1][i] + g[2][i] + g[3][i]);
+            }
+            const double vol = det * (1.0 / 6.0);
+            const double B1 = kB1 * vol, Bm = kB * vol, Cm = kC * vol, m0 = vol * (1.0 / 20.0);
+            double G[3][3] = {}, gp[3] = {}, vs[3] = {}, ps = 0.0, qs[3] = {};
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const double4 uu = su[nl[q]];
+                const double vq[3] = {uu.x, uu.y, uu.z};
+#pragma unroll
+                for (int i = 0; i < 3; ++i) {
+#pragma unroll
+                    for (int j = 0; j < 3; ++j) G[i][j] += vq[i] * g[q][j];
+                    gp[i] += uu.w * g[q][i];
+                    vs[i] += vq[i];
+                }
+                ps += uu.w;
+                if (extra) {
+                    const double4 qq = sq[nl[q]];
+                    qs[0] += qq.x;
+                    qs[1] += qq.y;
+                    qs[2] += qq.z;
+                }
+            }
+            const double th = G[0][0] + G[1][1] + G[2][2];
+            double Wv[3];
+#pragma unroll
+            for (int i = 0; i < 3; ++i) Wv[i] = B1 * vs[i];
+            if ((rec.x >> 31) && first == 0) {
+                // the fine-scale residual, counted in the norm by the tile that owns vertex 0
+                double gg = 0.0;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) gg += g[q][0] * g[q][0] + g[q][1] * g[q][1] + g[q][2] * g[q][2];
+                const double Kb = kKb * vol * gg;
+#pragma unroll
+                for (int i = 0; i < 3; ++i) {
+                    const double Rf = G[i][0] * Wv[0] + G[i][1] * Wv[1] + G[i][2] * Wv[2] +
+                                      Cm * (G[i][0] * be[0] + G[i][1] * be[1] + G[i][2] * be[2] - 0.5 * th * be[i]) +
+                                      2.0 * nu * Kb * be[i] + Bm * gp[i] + B1 * qs[i];
+                    rf2 += Rf * Rf;
+                }
+            }
+            double c0[3], Wb[3];
+            const double n2v = 2.0 * nu * vol, pv = 0.25 * vol * ps;
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                Wb[i] = Wv[i] + 0.5 * Cm * be[i];
+                c0[i] = G[i][0] * (B1 * be[0] + m0 * vs[0]) + G[i][1] * (B1 * be[1] + m0 * vs[1]) +
+                        G[i][2] * (B1 * be[2] + m0 * vs[2]) - th * B1 * be[i] + m0 * qs[i];
+            }
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+                if (slot[a] < 0) continue;
+                const double4 uu = su[nl[a]];
+                double q[3] = {0.0, 0.0, 0.0};
+                if (extra) {
+                    const double4 qq = sq[nl[a]];
+                    q[0] = qq.x;
+                    q[1] = qq.y;
+                    q[2] = qq.z;
+                }
+                const double x[3] = {m0 * uu.x + n2v * g[a][0], m0 * uu.y + n2v * g[a][1], m0 * uu.z + n2v * g[a][2]};
+                const double wg = Wb[0] * g[a][0] + Wb[1] * g[a][1] + Wb[2] * g[a][2];
+                double R[3];
+#pragma unroll
+                for (int i = 0; i < 3; ++i)
+                    R[i] = c0[i] + (G[i][0] * x[0] + G[i][1] * x[1] + G[i][2] * x[2]) + m0 * q[i] - wg * be[i] -
+                           pv * g[a][i];
+                rows[slot[a]] = make_double4(R[0], R[1], R[2],
+                                             -th * vol * 0.25 + Bm * (be[0] * g[a][0] + be[1] * g[a][1] + be[2] * g[a][2]));
+            }
+        }
+        __syncthreads();
+        // the entries' slots in order, four in flight
+        const double* r = reinterpret_cast<const double*>(rows) + comp;
+        const int end = min(q1 - first, slots);
+#pragma unroll 4
+        for (int q = max(q0 - first, 0); q < end; ++q) acc += r[4 * q];
+        __syncthreads();
+    }
+    if ((dm >> comp) & 1u) acc = 0.0;
+    double rg2 = entry ? acc * acc : 0.0;
+    if (rglob && entry) rglob[4 * (size_t)n0 + threadIdx.x] = acc;
+    rg2 = wave_sum(rg2);
+    rf2 = wave_sum(rf2);
+    if ((threadIdx.x & 63) == 0) {
+        wsum[threadIdx.x >> 6][0] = rg2;
+        wsum[threadIdx.x >> 6][1] = rf2;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2) {
+        double s = 0.0;
+#pragma unroll
+        for (int w = 0; w < kResThreads / 64; ++w) s += wsum[w][threadIdx.x];
         tile_part[2 * (size_t)t + threadIdx.x] = s;
     }
 }
@@ -1089,16 +1301,16 @@ ElemArgs make_args(vms_ctx* c, const double* u, const double* u_prev, const doub
     return a;
 }
 
-// Launches tile_kernel<T, TACC, CONDENSE, SCHUR> at the context's tile width (256 threads, or one
+// Launches tile_kernel<T, TACC, SCHUR> at the context's tile width (256 threads, or one
 // wavefront in deterministic contexts).
-template <typename T, typename TACC, bool CONDENSE, bool SCHUR = true>
+template <typename T, typename TACC, bool SCHUR = true>
 void launch_tiles(const vms_ctx* c, const ElemArgs& a, const TileArgs& ta, size_t lds, T* Aval, double* rhs,
                   double* rglob, double* part, hipStream_t s) {
     if (c->tile_threads == kTileThreadsDet)
-        tile_kernel<T, TACC, CONDENSE, SCHUR, kTileThreadsDet><<<c->n_tiles, kTileThreadsDet, lds, s>>>(
+        tile_kernel<T, TACC, SCHUR, kTileThreadsDet><<<c->n_tiles, kTileThreadsDet, lds, s>>>(
             a, ta, Aval, rhs, rglob, part);
     else
-        tile_kernel<T, TACC, CONDENSE, SCHUR, kTileThreads><<<c->n_tiles, kTileThreads, lds, s>>>(a, ta, Aval, rhs,
+        tile_kernel<T, TACC, SCHUR, kTileThreads><<<c->n_tiles, kTileThreads, lds, s>>>(a, ta, Aval, rhs,
                                                                                                  rglob, part);
 }
 
@@ -1117,22 +1329,30 @@ TileArgs tile_args(vms_ctx* c) {
     return t;
 }
 
+ResidualArgs residual_args(vms_ctx* c) {
+    ResidualArgs t;
+    t.meta = c->rtile_meta;
+    t.nodes = c->rtile_nodes;
+    t.items = c->ritems;
+    t.n2e_ptr = c->n2e_ptr;
+    return t;
+}
+
 }  // namespace
 
 hipError_t tile_kernels_configure(vms_ctx* c) {
     const int lds = (int)std::max(c->tile_lds, c->tile_lds_tr);
     const void* fns[] = {
-        (const void*)tile_kernel<double, double, true, true, kTileThreads>,
-        (const void*)tile_kernel<float, MixedAcc, true, true, kTileThreads>,
-        (const void*)tile_kernel<double, double, false, true, kTileThreads>,
-        (const void*)tile_kernel<double, double, true, false, kTileThreads>,
-        (const void*)tile_kernel<float, MixedAcc, true, false, kTileThreads>,
-        (const void*)tile_kernel<double, double, true, true, kTileThreadsDet>,
-        (const void*)tile_kernel<float, MixedAcc, true, true, kTileThreadsDet>,
-        (const void*)tile_kernel<double, double, false, true, kTileThreadsDet>,
-        (const void*)tile_kernel<double, double, true, false, kTileThreadsDet>,
-        (const void*)tile_kernel<float, MixedAcc, true, false, kTileThreadsDet>};
-    hipError_t e = hipSuccess;
+        (const void*)tile_kernel<double, double, true, kTileThreads>,
+        (const void*)tile_kernel<float, MixedAcc, true, kTileThreads>,
+        (const void*)tile_kernel<double, double, false, kTileThreads>,
+        (const void*)tile_kernel<float, MixedAcc, false, kTileThreads>,
+        (const void*)tile_kernel<double, double, true, kTileThreadsDet>,
+        (const void*)tile_kernel<float, MixedAcc, true, kTileThreadsDet>,
+        (const void*)tile_kernel<double, double, false, kTileThreadsDet>,
+        (const void*)tile_kernel<float, MixedAcc, false, kTileThreadsDet>};
+    hipError_t e = hipFuncSetAttribute((const void*)residual_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)c->rtile_lds[1]);
     for (const void* f : fns)
         if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     return e;
@@ -1216,11 +1436,11 @@ int launch_full_assemble(vms_ctx* c, const double* u, const double* u_prev, cons
     ElemArgs a = make_args(c, u, u_prev, beta, nu, inv_dt, body);
     const int g = grid_for(c->n_elems, kRawElems);
     if (c->prec == VMS_FP64) {
-        launch_tiles<double, double, true, false>(c, a, tile_args(c), tile_lds_of(c, a), (double*)vals, rhs, nullptr,
+        launch_tiles<double, double, false>(c, a, tile_args(c), tile_lds_of(c, a), (double*)vals, rhs, nullptr,
                                                   c->tile_part, s);
         full_element_kernel<double><<<g, kRawThreads, 0, s>>>(a, c->n_nodes, c->full_epos, (double*)vals, rhs);
     } else {
-        launch_tiles<float, MixedAcc, true, false>(c, a, tile_args(c), tile_lds_of(c, a), (float*)vals, rhs, nullptr,
+        launch_tiles<float, MixedAcc, false>(c, a, tile_args(c), tile_lds_of(c, a), (float*)vals, rhs, nullptr,
                                                    c->tile_part, s);
         full_element_kernel<float><<<g, kRawThreads, 0, s>>>(a, c->n_nodes, c->full_epos, (float*)vals, rhs);
     }
@@ -1250,9 +1470,9 @@ static int launch_condense_in(vms_ctx* c, const double* u, const double* u_prev,
                        (double)c->nb * 16 * es + 32.0 * nn * (rglob ? 2.0 : 1.0);
     PhaseScope ph(c, VMS_PH_CONDENSE, alg, s);
     if (c->prec == VMS_FP64)
-        launch_tiles<double, double, true>(c, a, tile_args(c), tile_lds_of(c, a), (double*)A, rhs, rglob, tile_part, s);
+        launch_tiles<double, double>(c, a, tile_args(c), tile_lds_of(c, a), (double*)A, rhs, rglob, tile_part, s);
     else
-        launch_tiles<float, MixedAcc, true>(c, a, tile_args(c), tile_lds_of(c, a), (float*)A, rhs, rglob, tile_part, s);
+        launch_tiles<float, MixedAcc>(c, a, tile_args(c), tile_lds_of(c, a), (float*)A, rhs, rglob, tile_part, s);
     return check_hip(c, hipGetLastError(), "condense launch");
 }
 
@@ -1271,19 +1491,23 @@ int launch_residual(vms_ctx* c, const double* u, const double* u_prev, const dou
         PhaseScope ph(c, VMS_PH_RESIDUAL,
                       ne * 40.0 + nn * (56.0 + (a.u_prev ? 24.0 : 0.0) + (body ? 24.0 : 0.0)) +
                           (rglob ? 32.0 * nn : 0.0), s);
-        launch_tiles<double, double, false>(c, a, tile_args(c), tile_lds_of(c, a), (double*)nullptr, nullptr, rglob,
-                                            c->tile_part, s);
+        const int extra = (a.u_prev != nullptr && a.inv_dt != 0.0) || body ? 1 : 0;
+        residual_kernel<<<c->n_rtiles, kResThreads, c->rtile_lds[extra], s>>>(a, residual_args(c), rglob, c->tile_part);
     }
     return check_hip(c, hipGetLastError(), "residual launch");
 }
 
-static int launch_norm_finalize_in(vms_ctx* c, const double* tile_part, double* out, hipStream_t s) {
-    norm_finalize_kernel<<<1, kFinThreads, 0, s>>>(c->n_tiles, tile_part, out);
+static int launch_norm_finalize_in(vms_ctx* c, int n_tiles, const double* tile_part, double* out, hipStream_t s) {
+    norm_finalize_kernel<<<1, kFinThreads, 0, s>>>(n_tiles, tile_part, out);
     return check_hip(c, hipGetLastError(), "norm launch");
 }
 
 int launch_norm_finalize(vms_ctx* c, double* out, hipStream_t s) {
-    return launch_norm_finalize_in(c, c->tile_part, out, s);
+    return launch_norm_finalize_in(c, c->n_tiles, c->tile_part, out, s);
+}
+
+int launch_residual_norm(vms_ctx* c, double* out, hipStream_t s) {
+    return launch_norm_finalize_in(c, c->n_rtiles, c->tile_part, out, s);
 }
 
 // ---- scratch of the no-allocation entry point -----------------------------------------
@@ -1398,7 +1622,7 @@ extern "C" int vms_condense_assemble_noalloc(vms_ctx* c, const double* u, const 
     rc = launch_condense_in(c, u, dt > 0 ? u_prev : nullptr, beta, 1.0 / Re, dt > 0 ? 1.0 / dt : 0.0, body,
                             bsr_vals, rhs, nullptr, flags, part, s);
     if (rc) return rc;
-    if (rnorm) return launch_norm_finalize_in(c, part, rnorm, s);
+    if (rnorm) return launch_norm_finalize_in(c, c->n_tiles, part, rnorm, s);
     return VMS_OK;
 }
 
@@ -1422,7 +1646,7 @@ extern "C" int vms_residual(vms_ctx* c, const double* u, const double* u_prev, c
     if (rc) return rc;
     rc = launch_residual(c, u, dt > 0 ? u_prev : nullptr, beta, 1.0 / Re, dt > 0 ? 1.0 / dt : 0.0, body, rglob, s);
     if (rc) return rc;
-    if (rnorm) return launch_norm_finalize(c, rnorm, s);
+    if (rnorm) return launch_residual_norm(c, rnorm, s);
     return VMS_OK;
 }
 

@@ -44,7 +44,7 @@ extern "C" int vms_newton_step(vms_ctx* c, double* u, double* beta, const double
     }
     if ((rc = vms_recover_update(c, u, beta, u_prev, Re, dt, body, c->du, s))) return rc;
     if ((rc = launch_residual(c, u, up, beta, nu, inv_dt, body, nullptr, s))) return rc;
-    if ((rc = launch_norm_finalize(c, c->rnorm + 1, s))) return rc;
+    if ((rc = launch_residual_norm(c, c->rnorm + 1, s))) return rc;
     if ((rc = check_hip(c, hipMemcpyAsync(&inf.rnorm_after, c->rnorm + 1, sizeof(double), hipMemcpyDeviceToHost, s),
                         "read rnorm")))
         return rc;
@@ -108,7 +108,7 @@ extern "C" int vms_full_newton_step(vms_ctx* c, double* u, double* beta, const d
     }
     if ((rc = launch_full_update(c, f->du, u, beta, s))) return rc;
     if ((rc = launch_residual(c, u, up, beta, nu, inv_dt, body, nullptr, s))) return rc;
-    if ((rc = launch_norm_finalize(c, c->rnorm + 1, s))) return rc;
+    if ((rc = launch_residual_norm(c, c->rnorm + 1, s))) return rc;
     if ((rc = check_hip(c, hipMemcpyAsync(&inf.rnorm_after, c->rnorm + 1, sizeof(double), hipMemcpyDeviceToHost, s),
                         "read rnorm")))
         return rc;

@@ -31,6 +31,13 @@ constexpr int kDrUpload = kDrOffSvs + kDrMax;
 #define VMS_DOT_CHUNKS 64          // upper bound on the workgroups (partials) per GMRES dot slot
 #endif
 constexpr int kTileNodes = 64;           // max nodes owned by one assembly tile
+// Tiles of the residual alone.  Measured at 41,400 nodes with a body force, 195,000 nodes transient:
+// 256 threads and 32 nodes 22.8 and 43.2 us, 24 nodes 26.1 and 53, 64 nodes 24 and 45, 128 threads 27
+// and 49 (the registers allow three waves a SIMD; a bound of four spills: 25 and 47).
+constexpr int kResidualThreads = 256;     // threads per tile
+constexpr int kResidualNodes = 32;        // max nodes owned by one
+constexpr int kResidualSlots = 2048;      // max element rows staged by one (64 KB)
+constexpr int kNoSlot = 0xffff;           // slot of a vertex that the tile does not own
 constexpr int kTileMaxNodes = 255;       // max nodes staged by one tile (8-bit local numbers)
 #ifndef VMS_TILE_BLOCKS_FP64
 #define VMS_TILE_BLOCKS_FP64 280
@@ -193,7 +200,17 @@ struct vms_ctx {
     uint4* items = nullptr;          // [4 n_elems]
     uint16_t* bmask = nullptr;       // [nb] Dirichlet bits of the column node (0..3) and the row
                                      // node (4..7), bit 8 on diagonal blocks
-    double* tile_part = nullptr;     // [n_tiles][2] partial sums of the residual norm
+    double* tile_part = nullptr;     // [max(n_tiles, n_rtiles)][2] partial sums of the residual norm
+    // tiles of the residual alone (element.hip, residual_kernel): its own node ranges, one item per
+    // element and tile, and a slot per element and vertex, those of a node side by side
+    int32_t n_rtiles = 0;
+    int4* rtile_meta = nullptr;      // [n_rtiles][2]: (first node, end node, first staged node, staged nodes),
+                                     // (first item, end item, first slot, slots)
+    int32_t* rtile_nodes = nullptr;  // [staged nodes of all residual tiles]
+    uint4* ritems = nullptr;
+    int32_t* n2e_ptr = nullptr;      // [n_nodes + 1] elements at the nodes before
+    size_t rtile_lds[2] = {};        // dynamic LDS bytes of the largest residual tile; [1]: with a previous
+                                     // velocity or a body force
     int32_t tile_threads = 256;      // threads per assembly tile (64: deterministic context)
     size_t tile_lds = 0;             // dynamic LDS bytes of the largest tile (steady)
     size_t tile_lds_tr = 0;          // same with the previous velocity staged (transient)
@@ -323,7 +340,8 @@ int launch_condense(vms_ctx* ctx, const double* u, const double* u_prev, const d
                     double* rglob, hipStream_t s);
 int launch_residual(vms_ctx* ctx, const double* u, const double* u_prev, const double* beta,
                     double nu, double inv_dt, const double* body, double* rglob, hipStream_t s);
-int launch_norm_finalize(vms_ctx* ctx, double* out, hipStream_t s);
+int launch_norm_finalize(vms_ctx* ctx, double* out, hipStream_t s);    // after launch_condense
+int launch_residual_norm(vms_ctx* ctx, double* out, hipStream_t s);    // after launch_residual
 int check_element_flags(vms_ctx* ctx, hipStream_t s);
 // Resolves this device's address of the no-allocation entry point's static scratch (once per
 // device; called by vms_create with the context's device current).
