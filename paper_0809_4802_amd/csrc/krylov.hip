@@ -631,33 +631,46 @@ __global__ __launch_bounds__(kBlock) void full_coarse_setup_kernel(int nn, const
     }
 }
 
-// norm of a vector -> gs->beta, initialises the cycle (g = beta e_1, k = 0, done flag).
+// A cycle's initial residual r: per workgroup the partial sums of its squares and of its free
+// pressure entries (added by cycle_v0_kernel, so that no workgroup has to wait for the last one).
+// With r64, r is first formed as r64 scaled (FP32 cycles start from the FP64 residual scaled to
+// one); with x_save, the iterate is kept there before a deflated cycle.
 template <typename T>
-__global__ __launch_bounds__(kBlock) void cycle_start_kernel(int n, const T* __restrict__ r,
-                                                             const uint8_t* __restrict__ dmask, RedScratch* red,
-                                                             GmresState* gs, double tol_abs, int reorth,
-                                                             unsigned gen) {
+__global__ __launch_bounds__(kBlock) void cycle_norm_kernel(int n, const double* __restrict__ r64, double scale,
+                                                            T* __restrict__ r, const double* __restrict__ x,
+                                                            double* __restrict__ x_save,
+                                                            const uint8_t* __restrict__ dmask, RedScratch* red) {
     __shared__ double lds[(kBlock / 64) * 2];
     double v[2] = {0.0, 0.0};
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-        const double x = double(r[i]);
-        v[0] += x * x;
-        if (free_pressure(dmask, i)) v[1] += x;
+        if (r64) r[i] = T(r64[i] * scale);
+        if (x_save) x_save[i] = x[i];
+        const double e = double(r[i]);
+        v[0] += e * e;
+        if (free_pressure(dmask, i)) v[1] += e;
     }
     block_sum<2>(v, lds);
     if (threadIdx.x == 0) {
         red->partial[blockIdx.x] = v[0];
         red->partial[kRedBlocks + blockIdx.x] = v[1];
     }
+}
+
+// Starts the cycle from the nparts partials: its norm to gs->beta, g = beta e_1, k = 0, the done
+// flag (workgroup 0), and V[0] = r / beta (V0 = V + j0 n for a deflated cycle).  Every workgroup
+// adds the partials itself, in the same order.
+template <typename T>
+__global__ __launch_bounds__(kBlock) void cycle_v0_kernel(int n, const T* __restrict__ r, T* __restrict__ V0,
+                                                          int nparts, const RedScratch* red, GmresState* gs,
+                                                          double tol_abs, int reorth, unsigned gen) {
     __shared__ double tot[2];
-    const bool last = arrive_last(&red->counter);
-    if (last) {
-        __threadfence();
-        reduce_partials(red->partial, kRedBlocks, 2, gridDim.x, tot);
-        __syncthreads();
-    }
-    if (last && threadIdx.x == 0) {
-        const double nrm = sqrt(tot[0]);
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    const double e = i < n ? double(r[i]) : 0.0;
+    reduce_partials(red->partial, kRedBlocks, 2, nparts, tot);
+    __syncthreads();
+    const double nrm = sqrt(tot[0]);
+    if (i < n) V0[i] = nrm > 0.0 ? T(e / nrm) : T(0);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
         gs->su = nrm > 0.0 ? tot[1] / nrm : 0.0;
         gs->beta = nrm;
         gs->g[0] = nrm;
@@ -668,7 +681,6 @@ __global__ __launch_bounds__(kBlock) void cycle_start_kernel(int n, const T* __r
         gs->norm = nrm;
         gs->reorth = reorth;
         gs->gen = gen;
-        red->counter = 0u;
         report_progress(gs, 0, gs->done);
     }
 }
@@ -725,15 +737,6 @@ __global__ __launch_bounds__(kBlock) void dr_load_kernel(int kk, const double* _
     }
     for (int e = tid; e < (kk + 1) * (kk + 1); e += blockDim.x) gs->dr_qt[e] = up[kDrOffQt + e];
     for (int e = tid; e < kk; e += blockDim.x) gs->svs[e] = up[kDrOffSvs + e];
-}
-
-// V[0] = r / beta (V0 = V + j0 n for a deflated cycle)
-template <typename T>
-__global__ void cycle_v0_kernel(int n, const T* __restrict__ r, T* __restrict__ V0, const GmresState* gs) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const double b = gs->beta;
-    V0[i] = b > 0.0 ? T(double(r[i]) / b) : T(0);
 }
 
 // A P for the Arnoldi steps: block (i, b) times the preconditioner block of node b, so that
@@ -1429,6 +1432,31 @@ __global__ __launch_bounds__(kBlock) void backsub_kernel(GmresState* gs) {
     }
 }
 
+// The same for restart lengths up to 64, by one wave: lane l holds row l of the triangle, so that
+// an elimination step is two lane reads, a multiply and an FMA with no memory access in the chain
+// (the staged form reads its operands from LDS in every step: 10 us for 50 columns, 4 us so).
+constexpr int kBacksubLanes = 64;
+__global__ __launch_bounds__(kBacksubLanes) void backsub_wave_kernel(GmresState* gs) {
+    constexpr int ld = kMaxRestart + 1;
+    const int l = threadIdx.x;
+    double row[kBacksubLanes];
+#pragma unroll
+    for (int col = 0; col < kBacksubLanes; ++col) row[col] = gs->R[(size_t)col * ld + l];
+    const double diag = gs->R[(size_t)l * ld + l], gl = gs->g[l];
+    const int k = gs->k;
+    double g = l < k ? gl : 0.0, y = 0.0;
+    const double rinv = 1.0 / diag;
+#pragma unroll
+    for (int col = kBacksubLanes - 1; col >= 0; --col) {
+        if (col < k) {
+            const double yc = read_lane(g, col) * read_lane(rinv, col);
+            if (l == col) y = yc;
+            if (l < col) g -= row[col] * yc;
+        }
+    }
+    if (l < k) gs->y[l] = y;
+}
+
 // t = sum_{i<k} y_i V_i
 template <typename T>
 __global__ __launch_bounds__(kBlock) void combine_kernel(int n, const T* __restrict__ V, const GmresState* gs,
@@ -1454,11 +1482,12 @@ __global__ __launch_bounds__(kBlock) void combine_kernel(int n, const T* __restr
     t[idx] = T(sacc);
 }
 
-// gs->st = sum of the free pressure entries of t (for the coarse term of P t)
+// Partial sums of the free pressure entries of t (for the coarse term of P t; added by
+// precond_accumulate_kernel)
 template <typename T>
 __global__ __launch_bounds__(kBlock) void free_pressure_sum_kernel(int n_nodes, const T* __restrict__ t,
                                                                    const uint8_t* __restrict__ dmask,
-                                                                   RedScratch* red, GmresState* gs) {
+                                                                   RedScratch* red, const GmresState* gs) {
     if (gs->k == 0) return;
     __shared__ double lds[kBlock / 64];
     double v[1] = {0.0};
@@ -1466,39 +1495,40 @@ __global__ __launch_bounds__(kBlock) void free_pressure_sum_kernel(int n_nodes, 
         if (!(dmask[i] & 8u)) v[0] += double(t[4 * (size_t)i + 3]);
     block_sum<1>(v, lds);
     if (threadIdx.x == 0) red->partial[blockIdx.x] = v[0];
-    if (!arrive_last(&red->counter)) return;
-    __threadfence();
-    __shared__ double tot;
-    reduce_partials(red->partial, kRedBlocks, 1, gridDim.x, &tot);
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        gs->st = tot;
-        red->counter = 0u;
-    }
 }
 
 // x += xscale P t = xscale (Minv t + z kappa (1_p^T t))  (x in TX: double for the FP64 solution,
 // float for an inner correction; xscale is the norm of the residual an FP32 cycle was given
 // scaled to one).  z is the indicator of the free pressure dofs 1_p, or the explicit vector zvec.
+// Every workgroup adds the nparts partials of 1_p^T t itself, in the same order.
 template <typename TM, typename T, typename TX>
-__global__ void precond_accumulate_kernel(int n_nodes, const TM* __restrict__ Minv, const T* __restrict__ t,
-                                          const uint8_t* __restrict__ dmask, const double* __restrict__ zvec,
-                                          const GmresState* gs, double xscale, TX* __restrict__ x) {
+__global__ __launch_bounds__(kBlock) void precond_accumulate_kernel(int n_nodes, const TM* __restrict__ Minv,
+                                                                    const T* __restrict__ t,
+                                                                    const uint8_t* __restrict__ dmask,
+                                                                    const double* __restrict__ zvec,
+                                                                    const GmresState* gs, int nparts,
+                                                                    const RedScratch* red, double xscale,
+                                                                    TX* __restrict__ x) {
     if (gs->k == 0) return;
+    __shared__ double st;
     const int tid = blockIdx.x * blockDim.x + threadIdx.x;
-    const int node = tid >> 2, r = tid & 3;
-    if (node >= n_nodes) return;
+    const int node = min(tid >> 2, n_nodes - 1), r = tid & 3;
     using M4 = typename Vec4<TM>::type;
     using V4 = typename Vec4<T>::type;
     const M4 m = *reinterpret_cast<const M4*>(Minv + (size_t)node * 16 + r * 4);
     const V4 v = *reinterpret_cast<const V4*>(t + 4 * (size_t)node);
+    const TX x0 = x[4 * (size_t)node + r];
+    const uint32_t dm = dmask[node];
+    reduce_partials(red->partial, kRedBlocks, 1, nparts, &st);
+    __syncthreads();
+    if ((tid >> 2) >= n_nodes) return;
     double s = double(m.x) * double(v.x) + double(m.y) * double(v.y) + double(m.z) * double(v.z) +
                double(m.w) * double(v.w);
     if (zvec)
-        s += gs->kappa * gs->st * zvec[4 * (size_t)node + r];
-    else if (r == 3 && !(dmask[node] & 8u))
-        s += gs->kappa * gs->st;
-    x[4 * (size_t)node + r] = TX(double(x[4 * (size_t)node + r]) + xscale * s);
+        s += gs->kappa * st * zvec[4 * (size_t)node + r];
+    else if (r == 3 && !(dm & 8u))
+        s += gs->kappa * st;
+    x[4 * (size_t)node + r] = TX(double(x0) + xscale * s);
 }
 
 // FP64 norm of a vector of any precision into out (device) via partials.
@@ -1622,7 +1652,8 @@ int wait_progress(vms_ctx* c, uint32_t gen, int need, hipStream_t s) {
 
 // Launches one GMRES(m) cycle on A d = r0 with right preconditioner Minv, adding the Krylov
 // correction xscale Minv (V y) (+ coarse term) to x (double or float).  r0 is the cycle's initial
-// residual (precision T).  The host follows the device's progress through the mapped word,
+// residual (precision T), formed here as r64 scaled when r64 is given; x_save receives x as it is
+// before the cycle.  The host follows the device's progress through the mapped word,
 // keeps at most kLeadSteps steps queued ahead of it and stops issuing steps once the cycle has
 // converged; nothing here synchronises the stream.  finish_cycle gives the number of steps
 // once the caller has synchronised.
@@ -1645,8 +1676,9 @@ T* basis_vectors(vms_ctx* c, int which) {
 // matrix, its A P blocks, A z and the preconditioner blocks, TX that of the iterate x.
 // With TM != T the steps apply P and A (Amat) in two passes instead of the stored A P blocks.
 template <typename T, typename TX, typename TM = T>
-int run_cycle(vms_ctx* c, const T* r0, const TM* Minv, TX* x, double tol_abs, int m, int budget, int cgs2,
-              hipStream_t s, double xscale = 1.0, int j0 = 0, const TM* Amat = nullptr) {
+int run_cycle(vms_ctx* c, T* r0, const TM* Minv, TX* x, double tol_abs, int m, int budget, int cgs2,
+              hipStream_t s, double xscale = 1.0, int j0 = 0, const TM* Amat = nullptr, const double* r64 = nullptr,
+              double r64_scale = 1.0, double* x_save = nullptr) {
     constexpr bool split = !std::is_same<TM, T>::value;
     if (split && !Amat) return set_error(c, VMS_EINVAL, "gmres: no matrix for the split operator");
     const int n = 4 * c->n_nodes;
@@ -1659,9 +1691,12 @@ int run_cycle(vms_ctx* c, const T* r0, const TM* Minv, TX* x, double tol_abs, in
     const int pbit = sizeof(T) == 8 ? 1 : 0;
     const uint32_t gen = ++c->cycle_gen;
     c->cycle_timed.clear();
-    cycle_start_kernel<T><<<red_grid(n), kBlock, 0, s>>>(n, r0, c->dmask, c->red, c->gs, tol_abs, cgs2, gen);
+    const double* x_old = nullptr;
+    if constexpr (std::is_same<TX, double>::value) x_old = x;
+    cycle_norm_kernel<T><<<red_grid(n), kBlock, 0, s>>>(n, r64, r64_scale, r0, x_old, x_save, c->dmask, c->red);
     // a deflated cycle puts the residual after the kept vectors and runs steps j0 .. m-1
-    cycle_v0_kernel<T><<<grid_for(n), kBlock, 0, s>>>(n, r0, V + (size_t)j0 * n, c->gs);
+    cycle_v0_kernel<T><<<grid_for(n), kBlock, 0, s>>>(n, r0, V + (size_t)j0 * n, red_grid(n), c->red, c->gs, tol_abs,
+                                                      cgs2, gen);
     const int steps = std::min(m - j0, budget);
     const double vb = (double)n * sizeof(T);      // bytes of one Krylov vector
     // algorithmic bytes of the Arnoldi SpMV: blocks and column indices, row pointers, the input
@@ -1820,11 +1855,14 @@ int run_cycle(vms_ctx* c, const T* r0, const TM* Minv, TX* x, double tol_abs, in
         if (rc) return rc;
     }
     // y = R^{-1} g on the device
-    backsub_kernel<<<1, kBlock, 0, s>>>(c->gs);
+    if (m <= kBacksubLanes)
+        backsub_wave_kernel<<<1, kBacksubLanes, 0, s>>>(c->gs);
+    else
+        backsub_kernel<<<1, kBlock, 0, s>>>(c->gs);
     combine_kernel<T><<<xcd_round(grid_for(n)), kBlock, 0, s>>>(n, V, c->gs, z);
     free_pressure_sum_kernel<T><<<red_grid(c->n_nodes), kBlock, 0, s>>>(c->n_nodes, z, c->dmask, c->red, c->gs);
-    precond_accumulate_kernel<TM, T, TX><<<grid_for(n), kBlock, 0, s>>>(c->n_nodes, Minv, z, c->dmask, c->zfull, c->gs,
-                                                                    xscale, x);
+    precond_accumulate_kernel<TM, T, TX><<<grid_for(n), kBlock, 0, s>>>(
+        c->n_nodes, Minv, z, c->dmask, c->zfull, c->gs, red_grid(c->n_nodes), c->red, xscale, x);
     return check_hip(c, hipGetLastError(), "gmres cycle launch");
 }
 
@@ -2159,23 +2197,21 @@ int gmres_solve(vms_ctx* c, const void* A, const double* b, double* x, const vms
         }
         j0 = kk;
         rn_start = rn;
-        if (j0 > 0 &&
-            (rc = check_hip(c, hipMemcpyAsync(c->x64, x, sizeof(double) * n, hipMemcpyDeviceToDevice, s), "save iterate")))
-            return rc;
+        double* x_save = j0 > 0 ? c->x64 : nullptr;
         // while the learned blocks are on trial, no cycle runs past half of the budget, so that
         // the switch to block-Jacobi above happens there
         const int cap = using_learned ? learned_budget : max_iters;
         if (c->prec == VMS_FP64) {
             // one restart cycle on the FP64 residual; the true residual is recomputed above
-            if ((rc = run_cycle<double, double>(c, c->r64, (const double*)c->Minv, x, tol, m, cap - iters,
-                                                cgs2, s, 1.0, j0)))
+            if ((rc = run_cycle<double, double, double>(c, c->r64, (const double*)c->Minv, x, tol, m, cap - iters,
+                                                cgs2, s, 1.0, j0, nullptr, nullptr, 1.0, x_save)))
                 return rc;
             pending = true;
         } else if (basis64) {
             // the same on the FP32-stored matrix and preconditioner, applied one after the other
             // (the stored A P blocks are rounded products, not the operator the residual sees)
             if ((rc = run_cycle<double, double, float>(c, c->r64, (const float*)c->Minv, x, tol, m, cap - iters,
-                                                       cgs2, s, 1.0, j0, (const float*)A)))
+                                                       cgs2, s, 1.0, j0, (const float*)A, nullptr, 1.0, x_save)))
                 return rc;
             pending = true;
         } else if (!sweeps) {
@@ -2185,10 +2221,8 @@ int gmres_solve(vms_ctx* c, const void* A, const double* b, double* x, const vms
             // residual recomputed in FP32 from an FP32 correction carries an error near
             // eps32 |A| |d|, which on hard systems the following cycles spend their steps on.
             inf.refinements++;
-            float* rr = (float*)c->r;
-            convert_kernel<double, float><<<grid_for(n), kBlock, 0, s>>>(n, c->r64, rr, 1.0 / rn);
-            if ((rc = run_cycle<float, double>(c, rr, (const float*)c->Minv, x, tol / rn, m, cap - iters, cgs2,
-                                               s, rn, j0)))
+            if ((rc = run_cycle<float, double, float>(c, (float*)c->r, (const float*)c->Minv, x, tol / rn, m, cap - iters, cgs2,
+                                               s, rn, j0, nullptr, c->r64, 1.0 / rn, x_save)))
                 return rc;
             pending = true;
         } else {
@@ -2205,7 +2239,7 @@ int gmres_solve(vms_ctx* c, const void* A, const double* b, double* x, const vms
             if ((rc = launch_fill(d, n * sizeof(float), s))) return rc;
             // one sweep is asked for 0.9 of the remaining reduction (never below inner_rtol)
             const double inner_tol = std::max(inner_rtol, 0.9 * tol / rn);
-            const float* cycle_r = rr;
+            float* cycle_r = rr;
             int progress = 0;
             while (iters < cap) {
                 if ((rc = run_cycle<float, float>(c, cycle_r, (const float*)c->Minv, d, inner_tol, m,

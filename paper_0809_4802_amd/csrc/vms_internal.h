@@ -137,7 +137,6 @@ struct GmresState {
     double norm;                   // scratch: a finished reduction
     double kappa;                  // coarse pressure correction: 1 / (sum of free p-p entries), 0 = off
     double su;                     // sum of the free pressure entries of u_j
-    double st;                     // sum of the free pressure entries of the correction V y
     double rho;                    // norm of u_j after its second pass
     double rho_m;                  // the same of a cycle's last vector
     double cj;                     // q_j . w
