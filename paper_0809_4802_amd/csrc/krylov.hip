@@ -725,18 +725,22 @@ void launch_dr_basis(int n, int mv, int kk, const double* P, int ldp, T* V, hipS
         dr_basis_kernel<T, kDrMax><<<grid_for(n), kBlock, 0, s>>>(n, mv, kk, P, ldp, V);
 }
 
-// Deflated restarting: the kept block of H and its factors from the packed upload into the
-// cycle state (columns 0 .. kk-1 of H and R, zero below their last row).  One workgroup.
-__global__ __launch_bounds__(kBlock) void dr_load_kernel(int kk, const double* __restrict__ up, GmresState* gs) {
+// Deflated restarting: the kept block of H and its factors from the host's packed staging (mapped
+// memory, read here once) into the cycle state (columns 0 .. kk-1 of H and R, zero below their last
+// row), and the np basis coefficients P into Pd for dr_basis_kernel.  One workgroup.
+constexpr int kDrLoadThreads = 1024;
+__global__ __launch_bounds__(kDrLoadThreads) void dr_load_kernel(int kk, int np, const double* __restrict__ up,
+                                                                 double* __restrict__ Pd, GmresState* gs) {
     constexpr int ld = kMaxRestart + 1;
     const int tid = threadIdx.x;
-    for (int e = tid; e < kk * ld; e += blockDim.x) {
+    for (int e = tid; e < np; e += kDrLoadThreads) Pd[e] = up[e];
+    for (int e = tid; e < kk * ld; e += kDrLoadThreads) {
         const int col = e / ld, row = e % ld;
         gs->H[e] = row <= kk ? up[kDrOffH + col * (kk + 1) + row] : 0.0;
         gs->R[e] = row < kk ? up[kDrOffR + col * kk + row] : 0.0;
     }
-    for (int e = tid; e < (kk + 1) * (kk + 1); e += blockDim.x) gs->dr_qt[e] = up[kDrOffQt + e];
-    for (int e = tid; e < kk; e += blockDim.x) gs->svs[e] = up[kDrOffSvs + e];
+    for (int e = tid; e < (kk + 1) * (kk + 1); e += kDrLoadThreads) gs->dr_qt[e] = up[kDrOffQt + e];
+    for (int e = tid; e < kk; e += kDrLoadThreads) gs->svs[e] = up[kDrOffSvs + e];
 }
 
 // A P for the Arnoldi steps: block (i, b) times the preconditioner block of node b, so that
@@ -1383,14 +1387,35 @@ __global__ __launch_bounds__(kBlock, sizeof(T) * R > 8 ? 4 : 5) void update_fuse
     }
 }
 
+// What the host needs of a full cycle to deflate the next one (dr_prepare), written into its mapped
+// staging by the back-substitution's workgroup (every thread of it; y finished): rows 0 .. m of H and
+// the cycle state from y on, then the cycle number with release order, which the host polls for.
+// The host works on it while the device finishes the cycle and forms the true residual.
+__device__ void dr_export(int m, const GmresState* gs, GmresState* out, uint64_t* tag) {
+    constexpr int ld = kMaxRestart + 1;
+    for (int e = threadIdx.x; e < m * (m + 1); e += blockDim.x) {
+        const size_t at = (size_t)(e / (m + 1)) * ld + e % (m + 1);
+        out->H[at] = gs->H[at];
+    }
+    constexpr size_t first = offsetof(GmresState, y), words = (sizeof(GmresState) - first) / sizeof(uint64_t);
+    static_assert(first % sizeof(uint64_t) == 0 && sizeof(GmresState) % sizeof(uint64_t) == 0, "whole words");
+    const uint64_t* src = reinterpret_cast<const uint64_t*>(reinterpret_cast<const char*>(gs) + first);
+    uint64_t* dst = reinterpret_cast<uint64_t*>(reinterpret_cast<char*>(out) + first);
+    for (size_t e = threadIdx.x; e < words; e += blockDim.x) dst[e] = src[e];
+    __threadfence_system();
+    __syncthreads();
+    if (threadIdx.x == 0) __hip_atomic_store(tag, (uint64_t)gs->gen, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // y = R^{-1} g for the k x k triangle of the rotated Hessenberg matrix (one workgroup): the
 // triangle and the reciprocals of its diagonal are staged in LDS (column batches, loads in
 // flight together), then one wave eliminates
 // column by column, lane l holding entries l and l + 64 of the right-hand side; the pivot
 // entry is broadcast with readlane, so the sequential chain is a multiply and an FMA per column.
-__global__ __launch_bounds__(kBlock) void backsub_kernel(GmresState* gs) {
+__global__ __launch_bounds__(kBlock) void backsub_kernel(GmresState* gs, int m, GmresState* out,
+                                                         uint64_t* tag) {
     const int k = gs->k;
-    if (k == 0) return;
+    if (k == 0 && !out) return;
     constexpr int ld = kMaxRestart + 1;
     __shared__ double Rl[kMaxRestart * kMaxRestart];
     __shared__ double rinv[kMaxRestart];
@@ -1422,39 +1447,47 @@ __global__ __launch_bounds__(kBlock) void backsub_kernel(GmresState* gs) {
         g1 = threadIdx.x + 64 < k ? gs->g[threadIdx.x + 64] : 0.0;
     }
     __syncthreads();
-    if (threadIdx.x >= 64) return;
     const int l = threadIdx.x;
-    for (int col = k - 1; col >= 0; --col) {
-        const double yc = read_lane(col < 64 ? g0 : g1, col & 63) * rinv[col];
-        if (l == 0) gs->y[col] = yc;
-        if (l < col) g0 -= Rl[col * k + l] * yc;
-        if (l + 64 < col) g1 -= Rl[col * k + l + 64] * yc;
-    }
+    if (l < 64)
+        for (int col = k - 1; col >= 0; --col) {
+            const double yc = read_lane(col < 64 ? g0 : g1, col & 63) * rinv[col];
+            if (l == 0) gs->y[col] = yc;
+            if (l < col) g0 -= Rl[col * k + l] * yc;
+            if (l + 64 < col) g1 -= Rl[col * k + l + 64] * yc;
+        }
+    if (!out) return;
+    __syncthreads();
+    dr_export(m, gs, out, tag);
 }
 
 // The same for restart lengths up to 64, by one wave: lane l holds row l of the triangle, so that
 // an elimination step is two lane reads, a multiply and an FMA with no memory access in the chain
 // (the staged form reads its operands from LDS in every step: 10 us for 50 columns, 4 us so).
 constexpr int kBacksubLanes = 64;
-__global__ __launch_bounds__(kBacksubLanes) void backsub_wave_kernel(GmresState* gs) {
+__global__ __launch_bounds__(kBlock) void backsub_wave_kernel(GmresState* gs, int m, GmresState* out, uint64_t* tag) {
     constexpr int ld = kMaxRestart + 1;
     const int l = threadIdx.x;
-    double row[kBacksubLanes];
+    if (l < kBacksubLanes) {
+        double row[kBacksubLanes];
 #pragma unroll
-    for (int col = 0; col < kBacksubLanes; ++col) row[col] = gs->R[(size_t)col * ld + l];
-    const double diag = gs->R[(size_t)l * ld + l], gl = gs->g[l];
-    const int k = gs->k;
-    double g = l < k ? gl : 0.0, y = 0.0;
-    const double rinv = 1.0 / diag;
+        for (int col = 0; col < kBacksubLanes; ++col) row[col] = gs->R[(size_t)col * ld + l];
+        const double diag = gs->R[(size_t)l * ld + l], gl = gs->g[l];
+        const int k = gs->k;
+        double g = l < k ? gl : 0.0, y = 0.0;
+        const double rinv = 1.0 / diag;
 #pragma unroll
-    for (int col = kBacksubLanes - 1; col >= 0; --col) {
-        if (col < k) {
-            const double yc = read_lane(g, col) * read_lane(rinv, col);
-            if (l == col) y = yc;
-            if (l < col) g -= row[col] * yc;
+        for (int col = kBacksubLanes - 1; col >= 0; --col) {
+            if (col < k) {
+                const double yc = read_lane(g, col) * read_lane(rinv, col);
+                if (l == col) y = yc;
+                if (l < col) g -= row[col] * yc;
+            }
         }
+        if (l < k) gs->y[l] = y;
     }
-    if (l < k) gs->y[l] = y;
+    if (!out) return;
+    __syncthreads();
+    dr_export(m, gs, out, tag);
 }
 
 // t = sum_{i<k} y_i V_i
@@ -1589,23 +1622,26 @@ void launch_norm(vms_ctx* c, int n, const T* r, int k, hipStream_t s) {
                                                   ++c->scal_seq);
 }
 
-// Waits for mapped scalar k of the last launch_norm: spins on its tag in pinned memory (the
-// launches after it on the stream are already ordered), with a stream query every 256 spins so
-// that a failed or drained stream ends the wait.
-int read_scalar(vms_ctx* c, int k, double* h, hipStream_t s) {
-    const uint64_t want = c->scal_seq;
-    const uint64_t* tag = c->progress_host + 1 + k;
+// Waits for a word of the mapped page: spins on it (the launches after the one that writes it are
+// already ordered), with a stream query every 256 spins so that a failed or drained stream ends the
+// wait.  read_scalar: mapped scalar k of the last launch_norm.
+int wait_word(vms_ctx* c, int word, uint64_t want, const char* what, hipStream_t s) {
+    const uint64_t* tag = c->progress_host + word;
     for (unsigned spin = 0;; ++spin) {
-        if (__atomic_load_n(tag, __ATOMIC_ACQUIRE) == want) break;
+        if (__atomic_load_n(tag, __ATOMIC_ACQUIRE) == want) return VMS_OK;
         if ((spin & 255u) == 255u) {
             const hipError_t q = hipStreamQuery(s);
             if (q == hipSuccess) {
-                if (__atomic_load_n(tag, __ATOMIC_ACQUIRE) == want) break;
-                return set_error(c, VMS_EHIP, "read scalar: the stream finished without the value");
+                if (__atomic_load_n(tag, __ATOMIC_ACQUIRE) == want) return VMS_OK;
+                return set_error(c, VMS_EHIP, std::string(what) + ": the stream finished without the value");
             }
-            if (q != hipErrorNotReady) return check_hip(c, q, "read scalar: stream query");
+            if (q != hipErrorNotReady) return check_hip(c, q, what);
         }
     }
+}
+
+int read_scalar(vms_ctx* c, int k, double* h, hipStream_t s) {
+    if (int rc = wait_word(c, 1 + k, c->scal_seq, "read scalar", s)) return rc;
     *h = *reinterpret_cast<volatile const double*>(c->scal_host + k);
     return VMS_OK;
 }
@@ -1653,7 +1689,7 @@ int wait_progress(vms_ctx* c, uint32_t gen, int need, hipStream_t s) {
 // Launches one GMRES(m) cycle on A d = r0 with right preconditioner Minv, adding the Krylov
 // correction xscale Minv (V y) (+ coarse term) to x (double or float).  r0 is the cycle's initial
 // residual (precision T), formed here as r64 scaled when r64 is given; x_save receives x as it is
-// before the cycle.  The host follows the device's progress through the mapped word,
+// before the cycle; with to_deflate, a full cycle hands the host what dr_prepare needs.  The host follows the device's progress through the mapped word,
 // keeps at most kLeadSteps steps queued ahead of it and stops issuing steps once the cycle has
 // converged; nothing here synchronises the stream.  finish_cycle gives the number of steps
 // once the caller has synchronised.
@@ -1678,7 +1714,7 @@ T* basis_vectors(vms_ctx* c, int which) {
 template <typename T, typename TX, typename TM = T>
 int run_cycle(vms_ctx* c, T* r0, const TM* Minv, TX* x, double tol_abs, int m, int budget, int cgs2,
               hipStream_t s, double xscale = 1.0, int j0 = 0, const TM* Amat = nullptr, const double* r64 = nullptr,
-              double r64_scale = 1.0, double* x_save = nullptr) {
+              double r64_scale = 1.0, double* x_save = nullptr, bool to_deflate = false) {
     constexpr bool split = !std::is_same<TM, T>::value;
     if (split && !Amat) return set_error(c, VMS_EINVAL, "gmres: no matrix for the split operator");
     const int n = 4 * c->n_nodes;
@@ -1855,10 +1891,12 @@ int run_cycle(vms_ctx* c, T* r0, const TM* Minv, TX* x, double tol_abs, int m, i
         if (rc) return rc;
     }
     // y = R^{-1} g on the device
+    GmresState* out = to_deflate && steps == m - j0 ? static_cast<GmresState*>(c->dr_mapped) : nullptr;
+    uint64_t* tag = c->progress_dev + kDrTagWord;
     if (m <= kBacksubLanes)
-        backsub_wave_kernel<<<1, kBacksubLanes, 0, s>>>(c->gs);
+        backsub_wave_kernel<<<1, out ? kBlock : kBacksubLanes, 0, s>>>(c->gs, m, out, tag);
     else
-        backsub_kernel<<<1, kBlock, 0, s>>>(c->gs);
+        backsub_kernel<<<1, kBlock, 0, s>>>(c->gs, m, out, tag);
     combine_kernel<T><<<xcd_round(grid_for(n)), kBlock, 0, s>>>(n, V, c->gs, z);
     free_pressure_sum_kernel<T><<<red_grid(c->n_nodes), kBlock, 0, s>>>(c->n_nodes, z, c->dmask, c->red, c->gs);
     precond_accumulate_kernel<TM, T, TX><<<grid_for(n), kBlock, 0, s>>>(
@@ -1879,26 +1917,17 @@ int finish_cycle(vms_ctx* c, int* stopped = nullptr) {
     return k;
 }
 
-// Deflated restarting after a full cycle of m steps that kept j0 vectors of its predecessor
-// (the stream drained): the cycle's Hessenberg matrix, solution y and right-hand side give the
-// harmonic Ritz vectors to keep (dr_setup); the kept block of H, its QR factors and the
-// free-pressure sums go to the cycle state, and the basis is recombined in place.  *kk: the
-// vectors the next cycle starts with (0: a plain restart; nothing was changed).
-template <typename T>
-int dr_restart(vms_ctx* c, int m, int j0, int deflate, hipStream_t s, int* kk) {
+// Deflated restarting after a full cycle of m steps that kept j0 vectors of its predecessor: the
+// cycle's Hessenberg matrix, solution y and right-hand side (dr_export) give the harmonic Ritz
+// vectors to keep (dr_setup), packed into the staging.  Host work only: it runs while the device
+// ends the cycle and forms the true residual (0.1 ms at m = 50, k = 10, of which the device hides
+// about 40 us).  *kk: the vectors the next cycle can start with (0: a plain restart).
+int dr_prepare(vms_ctx* c, int m, int j0, int deflate, hipStream_t s, int* kk) {
     constexpr int ld = kMaxRestart + 1;
     *kk = 0;
-    GmresState* h = reinterpret_cast<GmresState*>(c->dr_pinned);
+    if (int rc = wait_word(c, kDrTagWord, c->cycle_gen, "read cycle state", s)) return rc;
+    const GmresState* h = reinterpret_cast<const GmresState*>(c->dr_pinned);
     double* up = reinterpret_cast<double*>(reinterpret_cast<char*>(c->dr_pinned) + kDrStateBytes);
-    const size_t tail = offsetof(GmresState, y);
-    int rc = check_hip(c, hipMemcpyAsync(h->H, c->gs->H, sizeof(double) * (size_t)m * ld, hipMemcpyDeviceToHost, s),
-                       "read Hessenberg matrix");
-    if (!rc)
-        rc = check_hip(c, hipMemcpyAsync(reinterpret_cast<char*>(h) + tail, reinterpret_cast<char*>(c->gs) + tail,
-                                         sizeof(GmresState) - tail, hipMemcpyDeviceToHost, s),
-                       "read cycle state");
-    if (!rc) rc = check_hip(c, hipStreamSynchronize(s), "sync");
-    if (rc) return rc;
     const double rho = h->rho_m;
     if (!(rho > 0.0) || !std::isfinite(rho)) return VMS_OK;
     // Hbar (m+1) x m, entries below each column's last row cleared: the kept block's columns end
@@ -1932,13 +1961,18 @@ int dr_restart(vms_ctx* c, int m, int j0, int deflate, hipStream_t s, int* kk) {
     std::copy(S.Hk.begin(), S.Hk.end(), up + kDrOffH);
     std::copy(S.R.begin(), S.R.end(), up + kDrOffR);
     std::copy(S.Qt.begin(), S.Qt.end(), up + kDrOffQt);
-    if ((rc = check_hip(c, hipMemcpyAsync(c->dr_p, up, sizeof(double) * kDrUpload, hipMemcpyHostToDevice, s),
-                        "upload deflation data")))
-        return rc;
-    dr_load_kernel<<<1, kBlock, 0, s>>>(k, c->dr_p, c->gs);
-    const int n = 4 * c->n_nodes;
-    launch_dr_basis<T>(n, mp, k, c->dr_p, mp, basis_vectors<T>(c, 0), s);
     *kk = k;
+    return VMS_OK;
+}
+
+// The kept block of H, its QR factors and the free-pressure sums go to the cycle state, and the
+// basis is recombined in place: the next cycle starts with kk vectors.
+template <typename T>
+int dr_apply(vms_ctx* c, int m, int kk, hipStream_t s) {
+    const int n = 4 * c->n_nodes, mp = m + 1;
+    const double* up = reinterpret_cast<const double*>(static_cast<const char*>(c->dr_mapped) + kDrStateBytes);
+    dr_load_kernel<<<1, kDrLoadThreads, 0, s>>>(kk, kk * mp, up, c->dr_p, c->gs);
+    launch_dr_basis<T>(n, mp, kk, c->dr_p, mp, basis_vectors<T>(c, 0), s);
     return check_hip(c, hipGetLastError(), "deflation launch");
 }
 
@@ -2025,8 +2059,8 @@ int launch_ap_setup(vms_ctx* c, const void* A, hipStream_t s) {
     return check_hip(c, hipGetLastError(), "A P setup launch");
 }
 
-// FP64 residual r64 = b - A x and its norm (synchronising).
-static int true_residual(vms_ctx* c, const void* A, const double* b, const double* x, double* rn, hipStream_t s) {
+// FP64 residual r64 = b - A x and its norm, which read_scalar(c, 0, ..) waits for.
+static void launch_true_residual(vms_ctx* c, const void* A, const double* b, const double* x, hipStream_t s) {
     const int n = 4 * c->n_nodes;
     if (c->prec == VMS_FP64)
         spmv_kernel<double, double, double, double, 1><<<spmv_grid(c->n_nodes), kBlock, 0, s>>>(
@@ -2035,7 +2069,6 @@ static int true_residual(vms_ctx* c, const void* A, const double* b, const doubl
         spmv_kernel<float, double, double, double, 1><<<spmv_grid(c->n_nodes), kBlock, 0, s>>>(
             c->n_nodes, c->rowptr, c->colidx, (const float*)A, x, b, c->r64, nullptr);
     launch_norm<double>(c, n, c->r64, 0, s);
-    return read_scalar(c, 0, rn, s);
 }
 
 int gmres_solve(vms_ctx* c, const void* A, const double* b, double* x, const vms_solve_opts* o,
@@ -2134,11 +2167,24 @@ int gmres_solve(vms_ctx* c, const void* A, const double* b, double* x, const vms
     bool using_learned = learned;
     bool pending = false;          // an FP64 cycle was launched and not yet counted
     int j0 = 0;                    // vectors the cycle in flight kept from its predecessor
-    bool dr_ready = false;         // the last cycle ran all its steps: its basis can be deflated
+    bool dr_out = false;           // the cycle in flight hands the host its state for deflation
     bool dr_live = deflate > 0;    // deflation still in use in this solve
     double rn_start = 0.0;         // true residual before the cycle in flight
     for (;;) {
-        if ((rc = true_residual(c, A, b, x, &rn, s))) return rc;      // synchronises
+        launch_true_residual(c, A, b, x, s);
+        // the host's part of the next deflated restart, while the device gets to the residual: after a
+        // full cycle that did not stop, when the budgets leave room for another
+        int kk = 0;
+        if (pending && dr_out) {
+            if ((rc = wait_word(c, kDrTagWord, c->cycle_gen, "read cycle state", s))) return rc;
+            int stopped = 0;
+            const int k = read_progress(c, c->cycle_gen, &stopped);
+            const int after = iters + k - j0;
+            if (k == m && !stopped && after < max_iters && !(using_learned && after >= learned_budget) &&
+                (rc = dr_prepare(c, m, j0, deflate, s, &kk)))
+                return rc;
+        }
+        if ((rc = read_scalar(c, 0, &rn, s))) return rc;
         int last_k = -1;
         if (pending) {
             int stopped = 0;
@@ -2146,7 +2192,6 @@ int gmres_solve(vms_ctx* c, const void* A, const double* b, double* x, const vms
             iters += last_k - j0;
             inf.restarts++;
             pending = false;
-            dr_ready = dr_live && last_k == m && !stopped;
             if (j0 > 0 && !(rn <= rn_start)) {
                 // A deflated cycle cannot raise the residual in exact arithmetic (y = 0 is
                 // feasible); when it does, the kept block's Arnoldi relation has drifted from the
@@ -2155,8 +2200,10 @@ int gmres_solve(vms_ctx* c, const void* A, const double* b, double* x, const vms
                 if ((rc = check_hip(c, hipMemcpyAsync(x, c->x64, sizeof(double) * n, hipMemcpyDeviceToDevice, s),
                                     "restore iterate")))
                     return rc;
-                if ((rc = true_residual(c, A, b, x, &rn, s))) return rc;
-                dr_live = dr_ready = false;
+                launch_true_residual(c, A, b, x, s);
+                if ((rc = read_scalar(c, 0, &rn, s))) return rc;
+                dr_live = false;
+                kk = 0;
                 inf.deflation_stopped = 1;
             }
         }
@@ -2185,15 +2232,12 @@ int gmres_solve(vms_ctx* c, const void* A, const double* b, double* x, const vms
             if ((rc = launch_ap_setup(c, A, s))) return rc;
             using_learned = false;
             inf.fell_back_to_bj = 1;
-            dr_ready = false;      // the kept basis belongs to the old operator
+            kk = 0;                // the kept basis belongs to the old operator
         }
         // the next cycle's kept vectors (0: a plain restart)
-        int kk = 0;
-        if (dr_ready) {
-            rc = (c->prec == VMS_FP64 || basis64) ? dr_restart<double>(c, m, j0, deflate, s, &kk)
-                                                   : dr_restart<float>(c, m, j0, deflate, s, &kk);
+        if (kk > 0) {
+            rc = (c->prec == VMS_FP64 || basis64) ? dr_apply<double>(c, m, kk, s) : dr_apply<float>(c, m, kk, s);
             if (rc) return rc;
-            dr_ready = false;
         }
         j0 = kk;
         rn_start = rn;
@@ -2201,17 +2245,18 @@ int gmres_solve(vms_ctx* c, const void* A, const double* b, double* x, const vms
         // while the learned blocks are on trial, no cycle runs past half of the budget, so that
         // the switch to block-Jacobi above happens there
         const int cap = using_learned ? learned_budget : max_iters;
+        dr_out = dr_live && cap - iters >= m - j0;
         if (c->prec == VMS_FP64) {
             // one restart cycle on the FP64 residual; the true residual is recomputed above
             if ((rc = run_cycle<double, double, double>(c, c->r64, (const double*)c->Minv, x, tol, m, cap - iters,
-                                                cgs2, s, 1.0, j0, nullptr, nullptr, 1.0, x_save)))
+                                                cgs2, s, 1.0, j0, nullptr, nullptr, 1.0, x_save, dr_out)))
                 return rc;
             pending = true;
         } else if (basis64) {
             // the same on the FP32-stored matrix and preconditioner, applied one after the other
             // (the stored A P blocks are rounded products, not the operator the residual sees)
             if ((rc = run_cycle<double, double, float>(c, c->r64, (const float*)c->Minv, x, tol, m, cap - iters,
-                                                       cgs2, s, 1.0, j0, (const float*)A, nullptr, 1.0, x_save)))
+                                                       cgs2, s, 1.0, j0, (const float*)A, nullptr, 1.0, x_save, dr_out)))
                 return rc;
             pending = true;
         } else if (!sweeps) {
@@ -2222,7 +2267,7 @@ int gmres_solve(vms_ctx* c, const void* A, const double* b, double* x, const vms
             // eps32 |A| |d|, which on hard systems the following cycles spend their steps on.
             inf.refinements++;
             if ((rc = run_cycle<float, double, float>(c, (float*)c->r, (const float*)c->Minv, x, tol / rn, m, cap - iters, cgs2,
-                                               s, rn, j0, nullptr, c->r64, 1.0 / rn, x_save)))
+                                               s, rn, j0, nullptr, c->r64, 1.0 / rn, x_save, dr_out)))
                 return rc;
             pending = true;
         } else {

@@ -156,6 +156,7 @@ struct GmresState {
 };
 // the host staging of deflated restarting: a GmresState (padded), then the packed upload
 constexpr size_t kDrStateBytes = (sizeof(GmresState) + 255) & ~size_t(255);
+constexpr int kDrTagWord = 4;        // word of the progress page: number of the cycle whose state was handed over
 constexpr size_t kDrStagingBytes = kDrStateBytes + sizeof(double) * kDrUpload;
 
 // Grid-wide reduction scratch.
@@ -259,9 +260,10 @@ struct vms_ctx {
     // graphs of deflated cycles (steps j0 .. m-1), keyed by (m, j0)
     hipGraphExec_t dr_exec[4] = {nullptr, nullptr, nullptr, nullptr};
     int dr_exec_key[4] = {0, 0, 0, 0};
-    double* dr_p = nullptr;              // [kDrUpload] device copy of the packed upload
-    void* dr_pinned = nullptr;           // pinned host [kDrStagingBytes]: a GmresState read back
-                                         // (kDrStateBytes), then the packed upload
+    double* dr_p = nullptr;              // [(kMaxRestart + 1) kDrMax] device copy of the basis coefficients
+    void* dr_pinned = nullptr;           // mapped host memory [kDrStagingBytes]: a GmresState written by the
+                                         // device (kDrStateBytes), then the packed upload it reads
+    void* dr_mapped = nullptr;           // its device address
     int64_t prof_cycles = 0;             // cycles seen while the phase timers are on
     bool prof_force = false;             // a sampled cycle: every launch of a timed phase is timed
 
