@@ -65,6 +65,18 @@ struct GivensCtx {
     int report;             // 1: publish the progress after every column; 0: only when the cycle stops
 };
 
+// a . b over four entries, with its roundings written out: left to the compiler, which of the first
+// two products is rounded by itself depends on the code around it, and the sums of two kernels that
+// have to give the same bits would differ.
+template <typename T>
+__device__ __forceinline__ T dot4(T a0, T a1, T a2, T a3, T b0, T b1, T b2, T b3) {
+    return fma(a3, b3, fma(a2, b2, fma(a0, b0, a1 * b1)));
+}
+template <typename V4>
+__device__ __forceinline__ auto dot4(const V4& a, const V4& b) {
+    return dot4(a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w);
+}
+
 // Givens rotation of column jc (held in LDS, rows 0 .. jc+1), with the rotations of columns
 // 0 .. jc-1 in LDS (cl, sl) and gj the rotated right-hand side entry jc.  The rotated column
 // (rows 0 .. jc) goes to Rl in LDS, for the workgroup to store; the rotation, g, the residual
@@ -74,9 +86,10 @@ struct GivensCtx {
 // stream).  In the chain x_{i+1} = c_i y_i - s_i x_i lane i holds rotation i and hands x_{i+1} to
 // lane i + 1 by a DPP shift: a multiply, an FMA and the shift per rotation (lane i's x is right,
 // and stays so, from round i on).  One lane fetching the operands from LDS took 65 ns a rotation.
-// i0 > 0: rows 0 .. i0-1 of the column were already rotated (Rl) and x0 is row i0.
+// i0 > 0: rows 0 .. i0-1 of the column were already rotated (Rl) and x0 is row i0.  next: receives the
+// right-hand side's entry jc + 1.
 __device__ int givens_column(int jc, const double* col, double* cl, double* sl, double gj, double* Rl,
-                             const GivensCtx& gc, GmresState* gs, int i0, double x0) {
+                             const GivensCtx& gc, GmresState* gs, int i0, double x0, double* next = nullptr) {
     const int lane = threadIdx.x & 63;
     double x = i0 > 0 ? x0 : col[0];
     const double hn = col[jc + 1];
@@ -108,6 +121,7 @@ __device__ int givens_column(int jc, const double* col, double* cl, double* sl, 
         if (stop) gs->done = 1;
         if (stop || gc.report) report_progress(gc.progress, gc.gen, jc + 1, stop);
     }
+    if (next) *next = gnext;
     return stop;
 }
 
@@ -306,15 +320,14 @@ __global__ __launch_bounds__(kBlock) void spmv_kernel(int n_rows, const int32_t*
         for (int u = 0; u < kSpmvUnroll; ++u) {
             const TX x0 = quad_bcast<0>(xr[u]), x1 = quad_bcast<1>(xr[u]), x2 = quad_bcast<2>(xr[u]),
                      x3 = quad_bcast<3>(xr[u]);
-            acc += TACC(av[u].x) * TACC(x0) + TACC(av[u].y) * TACC(x1) + TACC(av[u].z) * TACC(x2) +
-                   TACC(av[u].w) * TACC(x3);
+            acc += dot4<TACC>(av[u].x, av[u].y, av[u].z, av[u].w, x0, x1, x2, x3);
         }
         // rows longer than kSpmvUnroll blocks per lane (other meshes)
         for (int k = k0 + q + kSpmvUnroll * Q; k < k1; k += Q) {
             const VA a = *reinterpret_cast<const VA*>(A + (size_t)k * 16 + r * 4);
             const TX xc = x[(size_t)colidx[k] * 4 + r];
             const TX x0 = quad_bcast<0>(xc), x1 = quad_bcast<1>(xc), x2 = quad_bcast<2>(xc), x3 = quad_bcast<3>(xc);
-            acc += TACC(a.x) * TACC(x0) + TACC(a.y) * TACC(x1) + TACC(a.z) * TACC(x2) + TACC(a.w) * TACC(x3);
+            acc += dot4<TACC>(a.x, a.y, a.z, a.w, x0, x1, x2, x3);
         }
     }
     acc += __shfl_xor(acc, 4, 64);       // lanes 4q + r of a row: q = 0 and q = 1
@@ -869,14 +882,14 @@ __device__ __forceinline__ void dot_chunk(const V4* __restrict__ q4, const V4* _
             const V4 b = bv[r];
             if (KIND == 0) {
                 const V4 q = xv[r], u = uv[r];
-                a0 += wt * double(q.x * u.x + q.y * u.y + q.z * u.z + q.w * u.w);
-                a1 += wt * double(q.x * b.x + q.y * b.y + q.z * b.z + q.w * b.w);
+                a0 += wt * double(dot4(q, u));
+                a1 += wt * double(dot4(q, b));
             } else if (KIND == 1) {
                 const V4 u = uv[r];
-                a0 += wt * double(u.x * u.x + u.y * u.y + u.z * u.z + u.w * u.w);
-                a1 += wt * double(u.x * b.x + u.y * b.y + u.z * b.z + u.w * b.w);
+                a0 += wt * double(dot4(u, u));
+                a1 += wt * double(dot4(u, b));
             } else {
-                a0 += wt * double(b.x * b.x + b.y * b.y + b.z * b.z + b.w * b.w);
+                a0 += wt * double(dot4(b, b));
                 a1 += (mk[r] & 8u) ? 0.0 : wt * double(b.w);
             }
         }
@@ -1218,10 +1231,44 @@ __device__ __forceinline__ StepLoads step_load(int j, int nchunks, const double*
     return s;
 }
 
+// The step's scalars from its sums (s_i, t_i, ...), the free-pressure sums svl of the final vectors
+// and su of u_j.  Every wave forms them itself (the wave sums leave them in every lane), so that no
+// second barrier is needed; all lanes and workgroups do the same operations in the same order.
+__device__ __forceinline__ StepOut step_scalars_of(int j, double eps_dot, const double* sums, const double* svl,
+                                                   double su, int reorth) {
+    const int lane = threadIdx.x & 63;
+    double a[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+    for (int i = lane; i < j; i += 64) {
+        const double si = reorth ? sums[2 * i] : 0.0, ti = sums[2 * i + 1], pi = svl[i];
+        a[0] += si * si;
+        a[1] += si * ti;
+        a[2] += si * pi;
+        a[3] += ti * ti;
+        a[4] += ti * pi;
+    }
+#pragma unroll
+    for (int q = 0; q < 5; ++q) a[q] = wave_sum(a[q]);
+    const double r2 = sums[2 * j] - a[0];
+    double rho = j > 0 ? (r2 > eps_dot * sums[2 * j] ? sqrt(r2) : 0.0) : 1.0;
+    if (!(rho > 0.0) || !isfinite(rho)) rho = 0.0;
+    const double svj = j == 0 ? su : (rho > 0.0 ? (su - a[2]) / rho : 0.0);
+    double cj = 0.0, hh = 0.0, sun = 0.0;
+    if (rho > 0.0) {
+        cj = (sums[2 * j + 1] - a[1]) / rho;
+        const double cc = a[3] + cj * cj;
+        const double pw = sums[2 * j + 3] - a[4] - cj * svj;
+        const double h2 = sums[2 * j + 2] - cc;
+        hh = h2 > eps_dot * sums[2 * j + 2] ? sqrt(h2) / rho : 0.0;
+        if (!isfinite(hh)) hh = 0.0;
+        sun = hh > 0.0 ? pw / (rho * hh) : 0.0;
+    }
+    return StepOut{rho, cj, hh, sun, svj};
+}
+
 // Returns false (uniformly) when the cycle is done.  Every thread of the workgroup calls it.
 __device__ __forceinline__ bool step_scalars(int j, int nchunks, const double* __restrict__ part, const StepLoads& s,
                                              double eps_dot, StepLds& L, StepOut& o) {
-    const int tid = threadIdx.x, lane = tid & 63;
+    const int tid = threadIdx.x;
     const int ns = 2 * (j + 2);
     const int grp = tid / kFusedLanes, sub = tid % kFusedLanes;
     if (tid < j) L.svl[tid] = s.svl;
@@ -1255,36 +1302,7 @@ __device__ __forceinline__ bool step_scalars(int j, int nchunks, const double* _
     }
     __syncthreads();
     if (L.flags[0]) return false;              // the cycle stopped in an earlier launch
-    // every wave forms the scalars itself (the wave sums leave them in every lane), so that no
-    // second barrier is needed; all lanes and workgroups do the same operations in the same order
-    const int reorth = L.flags[1];
-    double a[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    for (int i = lane; i < j; i += 64) {
-        const double si = reorth ? L.sums[2 * i] : 0.0, ti = L.sums[2 * i + 1], pi = L.svl[i];
-        a[0] += si * si;
-        a[1] += si * ti;
-        a[2] += si * pi;
-        a[3] += ti * ti;
-        a[4] += ti * pi;
-    }
-#pragma unroll
-    for (int q = 0; q < 5; ++q) a[q] = wave_sum(a[q]);
-    const double su = L.su;
-    const double r2 = L.sums[2 * j] - a[0];
-    double rho = j > 0 ? (r2 > eps_dot * L.sums[2 * j] ? sqrt(r2) : 0.0) : 1.0;
-    if (!(rho > 0.0) || !isfinite(rho)) rho = 0.0;
-    const double svj = j == 0 ? su : (rho > 0.0 ? (su - a[2]) / rho : 0.0);
-    double cj = 0.0, hh = 0.0, sun = 0.0;
-    if (rho > 0.0) {
-        cj = (L.sums[2 * j + 1] - a[1]) / rho;
-        const double cc = a[3] + cj * cj;
-        const double pw = L.sums[2 * j + 3] - a[4] - cj * svj;
-        const double h2 = L.sums[2 * j + 2] - cc;
-        hh = h2 > eps_dot * L.sums[2 * j + 2] ? sqrt(h2) / rho : 0.0;
-        if (!isfinite(hh)) hh = 0.0;
-        sun = hh > 0.0 ? pw / (rho * hh) : 0.0;
-    }
-    o = StepOut{rho, cj, hh, sun, svj};
+    o = step_scalars_of(j, eps_dot, L.sums, L.svl, L.su, L.flags[1]);
     return true;
 }
 
@@ -1385,6 +1403,389 @@ __global__ __launch_bounds__(kBlock, sizeof(T) * R > 8 ? 4 : 5) void update_fuse
         uj[idx[r]] = T(q);
         if (hh > 0.0) V[(size_t)(j + 1) * N + idx[r]] = T((aw[r] - cj * q) / (rho * hh));
     }
+}
+
+// ---------------------------------------------------------------- cycles of small systems
+// All Arnoldi steps of a cycle and its tail in one launch of one workgroup, for systems of at most
+// kSmallNodes nodes and cycles of at most kSmallSteps columns.  Such a step's three launches are
+// start-up, hand-over between XCDs and serial latency, of which the vectors' work is a fraction;
+// here the vectors in progress, H and the rotations stay in LDS, the basis in the CU's caches, and a
+// step is four barriers.  The last wave keeps H beside the others' work: it forms the step's
+// scalars, makes column j-1 final beside the update, rotates it beside the next SpMV and forms
+// column j beside the next dots.  With every wave taking part in everything a step took 1.3 us more.
+// A step of a 125-node FP64 system takes 9.6 us (SpMV 2.4, dots 3.0, scalars 1.1, update 3.1)
+// against 11.9 by launches, and an inexact-Newton solve on it 1490 us against 1862.  With the cycle's
+// ends, us per step at restart 50, FP64 and mixed: 64 nodes 8.5 and 8.0 (by launches 12.2 and 12.2),
+// 125 nodes 10.3 and 9.4 (12.2 and 12.4), 210 nodes 14.8 and 13.4 (12.5 and 12.4): from about 150
+// nodes on, what one CU reads of matrix and basis takes longer than the launches.  Up to 58 columns
+// H stays in LDS, a row per lane.
+// Every sum is formed in the order of the three kernels (a wave takes a slot's 64-node parts in
+// turn) and with the same roundings, so that a cycle gives the same bits on either path.
+constexpr int kSmallNodes = 128;
+constexpr int kSmallBlocks = 4096;          // blocks of the matrix (their columns are kept in LDS)
+constexpr int kSmallSteps = 58;             // columns; rows of H one per lane
+constexpr int kSmallThreads = 1024;
+constexpr int kSmallWaves = kSmallThreads / 64 - 1;      // beside the wave that keeps H
+constexpr int kSmallWorkers = 64 * kSmallWaves;
+constexpr int kSmallLd = 61;                // odd: a row of H across its columns spreads over the banks
+constexpr int kSmallSlots = (kSmallSteps + 2 + kSmallWaves - 1) / kSmallWaves;   // dot slots per wave
+static_assert(kSmallNodes <= kDotThreads, "one dot chunk, one node per lane and part");
+static_assert(kSmallSlots == 4 && kSmallSteps + 3 <= kSmallLd && kSmallSteps + 2 <= 64, "slots; rows");
+
+__device__ __forceinline__ void wave_sync() {           // LDS of one wave: order its accesses
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+template <typename T>
+struct SmallLds {
+    T u[4 * kSmallNodes], w[4 * kSmallNodes];   // u_j, B u_j
+    double H[kSmallSteps + 1][kSmallLd];        // columns of H
+    double sums[2 * 64];                        // the step's slots
+    double svl[kSmallSteps + 2];                // free-pressure sums of the final vectors
+    double cl[64], sl[64], Rl[66];
+    double qt[kQtMax], c[kDrMax + 1];           // deflated restarting: Q^T, the right-hand side
+    StepOut o;
+    int done;
+    uint16_t ptr[kSmallNodes + 1];              // row bounds and columns of the blocks
+    uint8_t col[kSmallBlocks];
+};
+
+// Sums over the wave of eight values at once, as a reduce-scatter: lane l returns that of value
+// 4 (l & 1) + (l & 2) + (l >> 2 & 1).  Lanes are added in the order of wave_sum.
+__device__ __forceinline__ double wave_sum8(double (&v)[8]) {
+    const int lane = threadIdx.x & 63;
+    const bool b0 = lane & 1, b1 = lane & 2, b2 = lane & 4;
+    double a[4], c[2];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) a[i] = (b0 ? v[4 + i] : v[i]) + dpp_mov<0xB1>(b0 ? v[i] : v[4 + i]);   // lane ^ 1
+#pragma unroll
+    for (int i = 0; i < 2; ++i) c[i] = (b1 ? a[2 + i] : a[i]) + dpp_mov<0x4E>(b1 ? a[i] : a[2 + i]);   // lane ^ 2
+    double t = (b2 ? c[1] : c[0]) + dpp_mov<0x1B>(dpp_mov<0x141>(b2 ? c[0] : c[1]));                    // lane ^ 4
+    t += dpp_mov<0x128>(t);                                                                             // lane ^ 8
+    t += __shfl_xor(t, 16, 64);
+    return t + __shfl_xor(t, 32, 64);
+}
+
+// The dot slots y = wave, wave + kSmallWaves, ... of the step into L.sums.
+template <typename T>
+__device__ __forceinline__ void small_dots(int n_nodes, int j, const T* V, SmallLds<T>& L,
+                                           const uint8_t* __restrict__ dmask) {
+    using V4 = typename Vec4<T>::type;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const V4* u4 = reinterpret_cast<const V4*>(L.u);
+    const V4* w4 = reinterpret_cast<const V4*>(L.w);
+    double t = 0.0;
+    for (int part = 0; 64 * part < n_nodes; ++part) {
+        const int node = min(64 * part + lane, n_nodes - 1);
+        const bool in = 64 * part + lane < n_nodes;
+        V4 x[kSmallSlots];
+#pragma unroll
+        for (int q = 0; q < kSmallSlots; ++q)
+            x[q] = reinterpret_cast<const V4*>(V)[(size_t)min(wave + kSmallWaves * q, max(j - 1, 0)) * n_nodes + node];
+        const bool masked = (dmask[node] & 8u) != 0;
+        const V4 u = u4[node], b = w4[node];
+        double d[2 * kSmallSlots];
+#pragma unroll
+        for (int q = 0; q < kSmallSlots; ++q) {
+            const int y = wave + kSmallWaves * q;            // uniform over the wave
+            double d0 = 0.0, d1 = 0.0;
+            if (y <= j) {
+                const V4 v = y < j ? x[q] : u;
+                d0 = double(dot4(v, u));
+                d1 = double(dot4(v, b));
+            } else if (y == j + 1) {
+                d0 = double(dot4(b, b));
+                d1 = masked ? 0.0 : double(b.w);
+            }
+            d[2 * q] = in ? d0 : 0.0;
+            d[2 * q + 1] = in ? d1 : 0.0;
+        }
+        t += wave_sum8(d);
+    }
+    const int i = 4 * (lane & 1) + (lane & 2) + ((lane >> 2) & 1), y = wave + kSmallWaves * (i >> 1);
+    if (lane < 8 && y <= j + 1) L.sums[2 * y + (i & 1)] = t;
+}
+
+// What the books' wave keeps of a step until its column is formed: lane i holds s_i and t_i.
+struct SmallStep {
+    double s, t, rho, cj, hh;
+};
+
+// Column j-1 of H becomes final (first part of columns_close), lane = row; dr_first: the right-hand
+// side of a deflated cycle instead.
+template <typename T>
+__device__ __forceinline__ void small_final(int j, int dk, SmallLds<T>& L, const SmallStep& p, double beta,
+                                            GmresState* gs) {
+    const int r = threadIdx.x & 63;
+    if (j > 0 && r <= j) {
+        if (dk > 0 && j == dk) {
+            const double cr = beta * (r < dk ? p.s : p.rho);
+            L.c[r] = cr;
+            gs->dr_c[r] = cr;
+        } else {
+            const double hp = L.H[j - 1][r], hprev = L.H[j - 1][j];
+            const double h = r < j ? hp + hprev * p.s : hprev * p.rho;
+            wave_sync();
+            L.H[j - 1][r] = h;
+        }
+    }
+    wave_sync();
+}
+
+// Column j of H from the step's sums (second part of columns_close), lane = row.
+template <typename T>
+__device__ __forceinline__ void small_column(int j, int dk, SmallLds<T>& L, const SmallStep& p, int reorth) {
+    if (!(p.rho > 0.0)) return;
+    const int r = threadIdx.x & 63;
+    auto rowmax = [&](int l) { return l < dk ? dk : l + 1; };   // last nonzero row of column l
+    const int rr = min(r, kSmallLd - 1);
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int l0 = 0; l0 <= j - 2; l0 += 8) {
+        double h[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) h[q] = L.H[min(l0 + q, j - 2)][rr];
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+            if (l0 + q <= j - 2) acc[q & 3] += (r <= rowmax(l0 + q) ? h[q] : 0.0) * read_lane(p.s, l0 + q);
+    }
+    const double s_last = j > 0 ? read_lane(p.s, j - 1) : 0.0;
+    if (r <= j) {
+        double hs = 0.0;
+        if (j > 0 && reorth) {
+            if (j > 1)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) hs += acc[q];
+            hs += L.H[j - 1][r] * s_last;
+        }
+        L.H[j][r] = ((r < j ? p.t : p.cj) - hs) / p.rho;
+        if (r == j) L.H[j][j + 1] = p.hh;
+    }
+    wave_sync();
+}
+
+// The rotations that step j left due, by one wave (columns_rotate); gcur: the right-hand side's entry
+// at the next rotation.  Sets L.done when the cycle stops.
+template <typename T>
+__device__ void small_rotate(int j, int dk, SmallLds<T>& L, double rho, double hh, double& gcur, GivensCtx gc,
+                             bool tail, GmresState* gs) {
+    constexpr int ld = kMaxRestart + 1;
+    const int lane = threadIdx.x & 63;
+    const bool dr_first = dk > 0 && j == dk;
+    // Q^T of the kept block on rows 0 .. dk of src: rows 0 .. dk-1 into out, the last one returned
+    auto apply_qt = [&](const double* src, double* out) {
+        double t = 0.0;
+        if (lane <= dk) {
+#pragma unroll 4
+            for (int l = 0; l <= dk; ++l) t += L.qt[l * (dk + 1) + lane] * src[l];
+            if (lane < dk) out[lane] = t;
+        }
+        wave_sync();
+        return read_lane(t, dk);
+    };
+    auto rotate = [&](int jc) {
+        double* col = L.H[jc];
+        const double x0 = dk > 0 ? apply_qt(col, L.Rl) : 0.0;
+        double gnext;
+        const int st = givens_column(jc, col, L.cl, L.sl, gcur, L.Rl, gc, gs, dk, x0, &gnext);
+        wave_sync();
+        gcur = gnext;
+        if (lane <= jc) gs->R[(size_t)jc * ld + lane] = L.Rl[lane];
+        wave_sync();
+        return st;
+    };
+    int st = 0;
+    if (dr_first) {
+        const double x0 = apply_qt(L.c, gs->g);
+        st = (fabs(x0) <= gc.tol_abs || !(rho > 0.0) || !isfinite(x0)) ? 1 : 0;
+        gcur = x0;
+        if (lane == 0) {
+            gs->gin[dk] = x0;
+            gs->k = dk;
+            if (st) gs->done = 1;
+            if (st || gc.report) report_progress(gc.progress, gc.gen, dk, st);
+        }
+    } else if (j > 0) {
+        st = rotate(j - 1);
+        if (!(rho > 0.0)) {
+            st = 1;                          // u_j vanished: column j-1 closes the cycle
+            if (lane == 0) {
+                gs->done = 1;
+                report_progress(gc.progress, gc.gen, j, 1);
+            }
+        }
+    }
+    if (!(tail || st || !(rho > 0.0) || hh > 0.0)) {
+        // the Krylov space is invariant: column j (formed by now) is final with a zero subdiagonal
+        if (lane == 0) L.H[j][j + 1] = 0.0;
+        wave_sync();
+        rotate(j);
+        st = 1;
+        if (lane == 0) {
+            gs->done = 1;
+            report_progress(gc.progress, gc.gen, j + 1, 1);
+        }
+    }
+    if (st && lane == 0) L.done = 1;
+}
+
+template <typename T>
+__global__ __launch_bounds__(kSmallThreads) void small_cycle_kernel(int n_nodes, int dk, int end,
+                                                                    const int32_t* __restrict__ rowptr,
+                                                                    const int32_t* __restrict__ colidx,
+                                                                    const T* __restrict__ AP, const T* __restrict__ Az,
+                                                                    const uint8_t* __restrict__ dmask, T* V,
+                                                                    GmresState* gs, double eps_dot) {
+    constexpr int ld = kMaxRestart + 1;
+    constexpr int kRows = kSmallWorkers / kSpmvLanes;          // rows per pass of the SpMV
+    constexpr int Q = kSpmvLanes / 4;
+    constexpr int kBatch = 64 / sizeof(T);                     // basis vectors and blocks of a lane in flight
+    constexpr int kUnroll = 32 / sizeof(T);
+    using V4 = typename Vec4<T>::type;
+    extern __shared__ __align__(16) unsigned char small_smem[];
+    SmallLds<T>& L = *reinterpret_cast<SmallLds<T>*>(small_smem);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const bool books = wave == kSmallWaves;                    // the wave that keeps H
+    const int n = 4 * n_nodes;
+    if (gs->done) return;
+    const int reorth = gs->reorth;
+    const double beta = gs->beta, kappa = gs->kappa;
+    double su = gs->su, gcur = gs->gin[0];
+    SmallStep p{0.0, 0.0, 0.0, 0.0, 0.0};
+    GivensCtx gc{gs->tol_abs, gs->progress, gs->gen, 0};
+    for (int i = tid; i < n; i += kSmallThreads) L.u[i] = V[(size_t)dk * n + i];
+    for (int e = tid; e < dk * (dk + 1); e += kSmallThreads)
+        L.H[e / (dk + 1)][e % (dk + 1)] = gs->H[(size_t)(e / (dk + 1)) * ld + e % (dk + 1)];
+    if (dk > 0)
+        for (int e = tid; e < (dk + 1) * (dk + 1); e += kSmallThreads) L.qt[e] = gs->dr_qt[e];
+    if (tid < dk) L.svl[tid] = gs->svs[tid];
+    for (int i = tid; i <= n_nodes; i += kSmallThreads) L.ptr[i] = (uint16_t)rowptr[i];
+    for (int k = tid; k < rowptr[n_nodes]; k += kSmallThreads) L.col[k] = (uint8_t)colidx[k];
+    if (tid == 0) L.done = 0;
+    if (books) __builtin_amdgcn_s_setprio(3);
+    __syncthreads();
+    for (int j = dk; j < end; ++j) {
+        // w = (A P) u_j + kappa S(u_j) A z; beside it, the rotations of the step before
+        if (books) {
+            if (j > dk) small_rotate(j - 1, dk, L, p.rho, p.hh, gcur, gc, false, gs);
+        } else {
+            const int sub = tid % kSpmvLanes, q = sub >> 2, r = sub & 3;
+            for (int row0 = 0; row0 < n_nodes; row0 += kRows) {
+                const int row = row0 + tid / kSpmvLanes;
+                T acc = T(0);
+                if (row < n_nodes) {
+                    const int k1 = L.ptr[row + 1];
+                    const T az = Az[4 * (size_t)row + r];
+                    for (int kb = L.ptr[row] + q; kb < k1; kb += kUnroll * Q) {
+                        V4 av[kUnroll];
+#pragma unroll
+                        for (int u = 0; u < kUnroll; ++u)
+                            if (kb + u * Q < k1) av[u] = *reinterpret_cast<const V4*>(AP + (size_t)(kb + u * Q) * 16 + r * 4);
+#pragma unroll
+                        for (int u = 0; u < kUnroll; ++u) {
+                            if (kb + u * Q >= k1) continue;          // the four lanes of a quad agree
+                            const T xr = L.u[L.col[kb + u * Q] * 4 + r];
+                            const T x0 = quad_bcast<0>(xr), x1 = quad_bcast<1>(xr), x2 = quad_bcast<2>(xr),
+                                    x3 = quad_bcast<3>(xr);
+                            acc += dot4<T>(av[u].x, av[u].y, av[u].z, av[u].w, x0, x1, x2, x3);
+                        }
+                    }
+                    acc += __shfl_xor(acc, 4, 64);               // the eight lanes of a row agree
+                    if (q == 0) L.w[4 * row + r] = acc + T(kappa * su) * az;
+                }
+            }
+        }
+        __syncthreads();
+        if (L.done) break;                                     // uniform
+        if (books) {
+            if (j > dk) small_column(j - 1, dk, L, p, reorth);
+        } else {
+            small_dots(n_nodes, j, V, L, dmask);
+        }
+        __syncthreads();
+        if (books) {
+            const StepOut o = step_scalars_of(j, eps_dot, L.sums, L.svl, su, reorth);
+            p = SmallStep{reorth && lane < j ? L.sums[2 * lane] : 0.0, lane < j ? L.sums[2 * lane + 1] : 0.0, o.rho,
+                          o.cj, o.hh};
+            if (lane == 0) L.o = o;
+        }
+        __syncthreads();
+        const StepOut o = L.o;
+        // q_j and u_{j+1}; beside them, column j-1 of H becomes final
+        if (books) {
+            small_final(j, dk, L, p, beta, gs);
+            if (lane == 0) {
+                L.svl[j] = o.svj;
+                gs->svs[j] = o.svj;
+            }
+            if (!(o.hh > 0.0)) small_column(j, dk, L, p, reorth);     // the rotation closes column j
+        } else if (o.rho > 0.0) {
+            const double s_l = reorth && lane < j ? L.sums[2 * lane] : 0.0, t_l = lane < j ? L.sums[2 * lane + 1] : 0.0;
+            for (int i0 = 64 * wave; i0 < n; i0 += kSmallWorkers) {   // uniform over the wave
+                const int i = min(i0 + lane, n - 1);
+                double aq = double(L.u[i]), aw = double(L.w[i]);
+                for (int l0 = 0; l0 < j; l0 += kBatch) {
+                    T v[kBatch];
+#pragma unroll
+                    for (int q = 0; q < kBatch; ++q) v[q] = V[(size_t)min(l0 + q, j - 1) * n + i];
+#pragma unroll
+                    for (int q = 0; q < kBatch; ++q)
+                        if (l0 + q < j) {
+                            aq -= read_lane(s_l, l0 + q) * double(v[q]);
+                            aw -= read_lane(t_l, l0 + q) * double(v[q]);
+                        }
+                }
+                const double q = aq / o.rho;
+                if (i0 + lane < n) {
+                    V[(size_t)j * n + i] = T(q);
+                    if (o.hh > 0.0) {
+                        const T un = T((aw - o.cj * q) / (o.rho * o.hh));
+                        V[(size_t)(j + 1) * n + i] = un;
+                        L.u[i] = un;
+                    }
+                }
+            }
+        }
+        su = o.su_next;
+        __syncthreads();
+    }
+    const bool stopped = L.done;
+    __syncthreads();                                           // read before the next rotation may set it
+    if (!stopped) {
+        // the second pass of the last vector completes the last column
+        if (books) small_rotate(end - 1, dk, L, p.rho, p.hh, gcur, gc, false, gs);
+        __syncthreads();
+        if (!L.done) {                                         // not set again before the next barrier
+            if (books) small_column(end - 1, dk, L, p, reorth);
+            else small_dots(n_nodes, end, V, L, dmask);
+            __syncthreads();
+            if (books) {
+                const double si = reorth && lane < end ? L.sums[2 * lane] : 0.0;
+                double a[2] = {0.0, 0.0};
+                if (lane < end) {
+                    a[0] += si * si;
+                    a[1] += si * L.svl[lane];
+                    gs->scoef[lane] = si;
+                }
+                a[0] = wave_sum(a[0]);
+                a[1] = wave_sum(a[1]);
+                const double r2 = L.sums[2 * end] - a[0];
+                double rho = r2 > eps_dot * L.sums[2 * end] ? sqrt(r2) : 0.0;
+                if (!(rho > 0.0) || !isfinite(rho)) rho = 0.0;
+                if (lane == 0) {
+                    gs->svs[end] = rho > 0.0 ? (su - a[1]) / rho : 0.0;
+                    gs->rho_m = rho;
+                }
+                small_final(end, dk, L, SmallStep{si, 0.0, rho, 0.0, 0.0}, beta, gs);
+                gc.report = 1;
+                small_rotate(end, dk, L, rho, 1.0, gcur, gc, true, gs);
+            }
+        }
+    }
+    __syncthreads();
+    // H for the host (deflated restarting)
+    for (int e = tid; e < end * (end + 1); e += kSmallThreads)
+        gs->H[(size_t)(e / (end + 1)) * ld + e % (end + 1)] = L.H[e / (end + 1)][e % (end + 1)];
 }
 
 // What the host needs of a full cycle to deflate the next one (dr_prepare), written into its mapped
@@ -1818,7 +2219,16 @@ int run_cycle(vms_ctx* c, T* r0, const TM* Minv, TX* x, double tol_abs, int m, i
     // of a timed phase in it is timed (events cannot time launches inside a graph).
     const bool graphs = steps == m - j0 && cycle_graphs_enabled();
     const bool sampled = c->prof_mask != 0 && c->prof_cycles++ % c->prof_every == 0;
-    if (graphs && !sampled && j0 > 0) {
+    bool small = false;
+    if constexpr (!split) {
+        small = c->n_nodes <= kSmallNodes && c->nb <= kSmallBlocks && j0 + steps <= kSmallSteps && !sampled;
+        if (small)
+            small_cycle_kernel<T><<<1, kSmallThreads, sizeof(SmallLds<T>), s>>>(
+                c->n_nodes, j0, j0 + steps, c->rowptr, c->colidx, AP, Az, c->dmask, V, c->gs, eps_dot);
+    }
+    if (small) {
+        // done: one launch
+    } else if (graphs && !sampled && j0 > 0) {
         // a full deflated cycle: one recorded graph per (m, j0), kept in a small cache
         const int key = (m * 256 + j0) * 2 + pbit;
         int slot = -1;
@@ -1977,6 +2387,15 @@ int dr_apply(vms_ctx* c, int m, int kk, hipStream_t s) {
 }
 
 }  // namespace
+
+hipError_t small_cycle_configure() {
+    hipError_t e = hipFuncSetAttribute((const void*)small_cycle_kernel<float>,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(SmallLds<float>));
+    if (e == hipSuccess)
+        e = hipFuncSetAttribute((const void*)small_cycle_kernel<double>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)sizeof(SmallLds<double>));
+    return e;
+}
 
 int launch_fill(void* p, size_t bytes, hipStream_t s) {
     if (bytes == 0) return VMS_OK;

@@ -354,6 +354,7 @@ int launch_full_assemble(vms_ctx* ctx, const double* u, const double* u_prev, co
 int launch_full_update(vms_ctx* ctx, const double* dx, double* u, double* beta, hipStream_t s);
 
 // linear algebra (krylov.hip)
+hipError_t small_cycle_configure();
 int launch_fill(void* p, size_t bytes, hipStream_t s);
 int launch_spmv(vms_ctx* ctx, const void* A, const void* x, void* y, hipStream_t s);
 int launch_bj_setup(vms_ctx* ctx, const void* A, void* Minv, hipStream_t s);
