@@ -896,7 +896,36 @@ __device__ __forceinline__ void dot_chunk(const V4* __restrict__ q4, const V4* _
     }
 }
 
-template <typename T>
+// The same for G finished vectors x, which share the loads of u and w: a vector by itself costs three
+// loads per entry, two a pair four, and the large meshes' dots are bound by what the L2s deliver.
+template <int G, typename V4>
+__device__ __forceinline__ void dot_chunk_group(const V4* const (&x)[G], const V4* __restrict__ u4,
+                                                const V4* __restrict__ w4, int i0, int i1, double (&a)[2 * G]) {
+    constexpr int kDotUnroll = sizeof(V4) <= 16 ? kDotUnrollF32 : 1;
+    for (int ib = i0 + (int)threadIdx.x; ib < i1; ib += kDotUnroll * (int)blockDim.x) {
+        V4 bv[kDotUnroll], uv[kDotUnroll], xv[kDotUnroll][G];
+#pragma unroll
+        for (int r = 0; r < kDotUnroll; ++r) {
+            const int i = min(ib + r * (int)blockDim.x, i1 - 1);
+            bv[r] = w4[i];
+            uv[r] = u4[i];
+#pragma unroll
+            for (int g = 0; g < G; ++g) xv[r][g] = x[g][i];
+        }
+#pragma unroll
+        for (int r = 0; r < kDotUnroll; ++r) {
+            const double wt = ib + r * (int)blockDim.x < i1 ? 1.0 : 0.0;
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                a[2 * g] += wt * double(dot4(xv[r][g], uv[r]));
+                a[2 * g + 1] += wt * double(dot4(xv[r][g], bv[r]));
+            }
+        }
+    }
+}
+
+// Workgroup rows 0 .. ceil(j / G) - 1 take G finished vectors each, the next one u_j, the last one w.
+template <typename T, int G>
 __global__ __launch_bounds__(kDotThreads) void dots_kernel(int n_nodes, int j, const T* __restrict__ V,
                                                            const T* __restrict__ w,
                                                            const uint8_t* __restrict__ dmask,
@@ -905,31 +934,42 @@ __global__ __launch_bounds__(kDotThreads) void dots_kernel(int n_nodes, int j, c
     // launches); its partials are left as they are, and the update and the tail test the flag too
     if (gs->done) return;
     using V4 = typename Vec4<T>::type;
-    const int y = blockIdx.y;
-    const int kind = y < j ? 0 : (y == j ? 1 : 2);
+    const int groups = (j + G - 1) / G;
+    const int row = blockIdx.y;
+    const int y = row < groups ? G * row : j + (row - groups);       // the first vector
     const size_t N4 = (size_t)n_nodes;          // float4 / double4 entries per vector
-    const V4* u4 = reinterpret_cast<const V4*>(V) + (size_t)j * N4;
+    const V4* v4 = reinterpret_cast<const V4*>(V);
+    const V4* u4 = v4 + (size_t)j * N4;
     const V4* w4 = reinterpret_cast<const V4*>(w);
-    const V4* q4 = reinterpret_cast<const V4*>(V) + (size_t)(kind == 0 ? y : 0) * N4;
     const int per = (n_nodes + gridDim.x - 1) / gridDim.x;
     const int chunk = gridDim.x % kXcds == 0 ? xcd_slot(blockIdx.x, gridDim.x) : blockIdx.x;
     const int i0 = chunk * per, i1 = min(n_nodes, i0 + per);
-    double a0 = 0.0, a1 = 0.0;
-    if (kind == 0)
-        dot_chunk<0>(q4, u4, w4, dmask, i0, i1, a0, a1);
-    else if (kind == 1)
-        dot_chunk<1>(q4, u4, w4, dmask, i0, i1, a0, a1);
-    else
-        dot_chunk<2>(q4, u4, w4, dmask, i0, i1, a0, a1);
-    a0 = wave_sum(a0);
-    a1 = wave_sum(a1);
-    __shared__ double lds[2][kDotThreads / 64];
-    if ((threadIdx.x & 63) == 0) {
-        lds[0][threadIdx.x >> 6] = a0;
-        lds[1][threadIdx.x >> 6] = a1;
+    double a[2 * G] = {};
+    int slots = 2;
+    if (row < groups) {
+        if constexpr (G == 1) {
+            dot_chunk<0>(v4 + (size_t)y * N4, u4, w4, dmask, i0, i1, a[0], a[1]);
+        } else {
+            // the last group's missing vectors repeat its last one and are not stored
+            slots = 2 * min(G, j - y);
+            const V4* x[G];
+#pragma unroll
+            for (int g = 0; g < G; ++g) x[g] = v4 + (size_t)min(y + g, j - 1) * N4;
+            dot_chunk_group<G>(x, u4, w4, i0, i1, a);
+        }
+    } else if (y == j) {
+        dot_chunk<1>(v4, u4, w4, dmask, i0, i1, a[0], a[1]);
+    } else {
+        dot_chunk<2>(v4, u4, w4, dmask, i0, i1, a[0], a[1]);
+    }
+    __shared__ double lds[2 * G][kDotThreads / 64];
+#pragma unroll
+    for (int q = 0; q < 2 * G; ++q) {
+        a[q] = wave_sum(a[q]);
+        if ((threadIdx.x & 63) == 0) lds[q][threadIdx.x >> 6] = a[q];
     }
     __syncthreads();
-    if (threadIdx.x < 2) {
+    if ((int)threadIdx.x < slots) {
         double t = 0.0;
         for (int k = 0; k < kDotThreads / 64; ++k) t += lds[threadIdx.x][k];
         part[(size_t)(2 * y + threadIdx.x) * gridDim.x + chunk] = t;
@@ -1160,27 +1200,31 @@ static_assert(kFusedChunks % kXcds == 0 && kFusedChunks <= kDotChunks, "fused do
 // Large meshes: the dots write kWideChunks partials per slot (more workgroups streaming the
 // basis when j is small), slot_sum_kernel adds them, and the update reads one sum per slot.
 constexpr int kWideChunks = 64;
+// Two finished vectors a workgroup there: an Arnoldi step at 64^3 (mixed) 110.0 -> 105.9 us, at 56^3
+// (FP64) 142.9 -> 136.8; three 106.1 and 140.0, four 108.8 and 142.3 (fewer workgroups).  At 16 chunks
+// (12^3 .. 50^3 nodes) pairs gain nothing, there being too few workgroups as it is.
+constexpr int kWideGroup = 2;                                         // finished vectors per dot workgroup
 constexpr int kWideMinNodes = 131072;
 constexpr int kWideSumOffset = 2 * (kMaxRestart + 2) * kWideChunks;   // sums after the partials
-static_assert(kWideChunks <= kDotChunks && kWideChunks % kXcds == 0, "wide dot chunks");
+static_assert(kWideChunks <= kDotChunks && kWideChunks % kXcds == 0 && kWideChunks <= 64, "wide dot chunks: one a lane");
 static_assert(kWideSumOffset + 2 * (kMaxRestart + 2) <= kRedBlocks * (kMaxRestart + 1), "wide sums exceed scratch");
 
-// sums[y] = the nchunks partials of slot y added in chunk order (one workgroup; idle once the
-// cycle has stopped).
+// sums[y] = the nchunks partials of slot y added in chunk order, a wave per slot, its lanes holding the
+// partials (idle once the cycle has stopped).  One round of loads, whole lines; a thread per slot read
+// them 512 bytes apart from its neighbours' and took 1.2 us more per step (64^3 mixed 111.3 -> 110.1).
+// Letting the last dots workgroup of a slot add them saves the launch and costs more (114.4): every
+// workgroup then waits for its partials and an atomic.
 __global__ __launch_bounds__(kBlock) void slot_sum_kernel(int j, int nchunks, const double* __restrict__ part,
                                                           double* __restrict__ sums, const GmresState* gs) {
     if (gs->done) return;
-    const int ns = 2 * (j + 2);
-    for (int y = threadIdx.x; y < ns; y += blockDim.x) {
-        const double* p = part + (size_t)y * nchunks;
-        double v[kWideChunks];
+    const int lane = threadIdx.x & 63;
+    const int y = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
+    if (y >= 2 * (j + 2)) return;
+    const double v = lane < nchunks ? part[(size_t)y * nchunks + lane] : 0.0;
+    double t = 0.0;
 #pragma unroll
-        for (int c = 0; c < kWideChunks; ++c) v[c] = c < nchunks ? p[c] : 0.0;
-        double t = 0.0;
-#pragma unroll
-        for (int c = 0; c < kWideChunks; ++c) t += v[c];
-        sums[y] = t;
-    }
+    for (int c = 0; c < kWideChunks; ++c) t += read_lane(v, c);
+    if (lane == 0) sums[y] = t;
 }
 
 struct StepLds {
@@ -2161,6 +2205,13 @@ int run_cycle(vms_ctx* c, T* r0, const TM* Minv, TX* x, double tol_abs, int m, i
         launch();
         keep(j, ph);
     };
+    auto launch_dots = [&](int j, hipStream_t st) {
+        if (wide)
+            dots_kernel<T, kWideGroup><<<dim3(nch, (j + kWideGroup - 1) / kWideGroup + 2), kDotThreads, 0, st>>>(
+                c->n_nodes, j, V, w, c->dmask, part, c->gs);
+        else
+            dots_kernel<T, 1><<<dim3(nch, j + 2), kDotThreads, 0, st>>>(c->n_nodes, j, V, w, c->dmask, part, c->gs);
+    };
     // the Arnoldi steps and the tail on stream st; with lead, the host keeps at most kLeadSteps
     // steps queued ahead of the device and stops issuing once the cycle has converged
     auto issue = [&](int steps_, bool lead, hipStream_t st) -> int {
@@ -2190,11 +2241,10 @@ int run_cycle(vms_ctx* c, T* r0, const TM* Minv, TX* x, double tol_abs, int m, i
                 });
             }
             timed(VMS_PH_DOTS, (j + 2) * vb, j, st, [&] {
-                dots_kernel<T><<<dim3(nch, j + 2), kDotThreads, 0, st>>>(c->n_nodes, j, V, w, c->dmask, part,
-                                                                         c->gs);
+                launch_dots(j, st);
             });
             timed(VMS_PH_UPDATE, (j + 4) * vb, j, st, [&] {
-                if (wide) slot_sum_kernel<<<1, kBlock, 0, st>>>(j, nch, part, part + kWideSumOffset, c->gs);
+                if (wide) slot_sum_kernel<<<(2 * (j + 2) + kBlock / 64 - 1) / (kBlock / 64), kBlock, 0, st>>>(j, nch, part, part + kWideSumOffset, c->gs);
                 // two vector rows per thread halve the workgroups that each form the step's
                 // scalars, except for FP64 vectors on small meshes, where one row per thread
                 // keeps more waves streaming the basis
@@ -2209,8 +2259,7 @@ int run_cycle(vms_ctx* c, T* r0, const TM* Minv, TX* x, double tol_abs, int m, i
             });
         }
         // the second pass of the last vector completes the last column
-        dots_kernel<T><<<dim3(nch, steps_ + 2), kDotThreads, 0, st>>>(c->n_nodes, steps_, V, w, c->dmask, part,
-                                                                      c->gs);
+        launch_dots(steps_, st);
         reduce_kernel<<<2, kRedThreads, 0, st>>>(steps_, nch, part, c->gs, eps_dot, j0, lead ? 1 : 0);
         columns_kernel<<<1, kBlock, 0, st>>>(steps_, j0, c->gs);
         return VMS_OK;
