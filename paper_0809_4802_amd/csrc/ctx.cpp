@@ -125,7 +125,7 @@ static void free_all(vms_ctx* c) {
     }
     void* ptrs[] = {c->full_cc, c->full_epos, c->zfull, c->xyz4, c->tets, c->dmask, c->dlist, c->rowptr, c->colidx, c->diagpos,
                     c->tpos, c->tile_meta, c->tile_nodes, c->items, c->bmask, c->tile_part, c->rtile_meta, c->rtile_nodes, c->ritems, c->n2e_ptr, c->A, c->rhs, c->du, c->rnorm, c->flags,
-                    c->V, c->w, c->z, c->d, c->r, c->Minv, c->AP, c->Az, c->x64, c->r64, c->gs, c->red,
+                    c->V, c->w, c->z, c->d, c->r, c->Minv, c->AP, c->Az, c->pp, c->x64, c->r64, c->gs, c->red,
                     c->feats, c->hid, c->pblk, c->gblk, c->gdel, c->tvec, c->wgrad, c->fscal, c->dr_p,
                     c->V64, c->w64, c->z64};
     for (void* p : ptrs)
@@ -739,6 +739,7 @@ extern "C" int vms_create(const vms_mesh_desc* mesh, const vms_create_opts* opts
     TRY(dev_alloc(c, &c->Minv, nn * 16 * es, "alloc Minv"));
     TRY(dev_alloc(c, &c->AP, c->nb * 16 * es, "alloc A P"));
     TRY(dev_alloc(c, &c->Az, N * es, "alloc A z"));
+    TRY(dev_alloc(c, &c->pp, c->nb * es, "alloc pressure couplings"));
     TRY(dev_alloc(c, &c->x64, N * sizeof(double), "alloc x64"));
     TRY(dev_alloc(c, &c->r64, N * sizeof(double), "alloc r64"));
     TRY(dev_alloc(c, &c->gs, sizeof(GmresState), "alloc gmres state"));

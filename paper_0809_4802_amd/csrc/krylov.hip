@@ -351,53 +351,13 @@ inline int spmv_grid(int n_rows) { return xcd_round((int)(((int64_t)kSpmvLanes *
 // identity and is counted in flags[2].
 template <typename TM>
 __device__ void invert_block_store(const double (&D)[4][4], TM* __restrict__ out, int32_t* flags) {
-    double m[4][8];
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            m[r][c] = D[r][c];
-            m[r][4 + c] = (r == c) ? 1.0 : 0.0;
-        }
-    bool ok = true;
-#pragma unroll
-    for (int col = 0; col < 4; ++col) {
-        int piv = col;
-        double best = fabs(m[col][col]);
-#pragma unroll
-        for (int r = col + 1; r < 4; ++r)
-            if (fabs(m[r][col]) > best) {
-                best = fabs(m[r][col]);
-                piv = r;
-            }
-        if (!(best > 0.0)) {
-            ok = false;
-            break;
-        }
-        if (piv != col) {
-#pragma unroll
-            for (int c = 0; c < 8; ++c) {
-                const double t = m[col][c];
-                m[col][c] = m[piv][c];
-                m[piv][c] = t;
-            }
-        }
-        const double ip = 1.0 / m[col][col];
-#pragma unroll
-        for (int c = 0; c < 8; ++c) m[col][c] *= ip;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            if (r == col) continue;
-            const double f = m[r][col];
-#pragma unroll
-            for (int c = 0; c < 8; ++c) m[r][c] -= f * m[col][c];
-        }
-    }
+    double m[4][4];
+    const bool ok = invert4(D, m);
     if (!ok) atomicAdd(&flags[2], 1);
 #pragma unroll
     for (int r = 0; r < 4; ++r)
 #pragma unroll
-        for (int c = 0; c < 4; ++c) out[r * 4 + c] = ok ? TM(m[r][4 + c]) : TM(r == c ? 1 : 0);
+        for (int c = 0; c < 4; ++c) out[r * 4 + c] = ok ? TM(m[r][c]) : TM(r == c ? 1 : 0);
 }
 
 template <typename TA, typename TM>
@@ -538,22 +498,29 @@ __device__ __forceinline__ bool free_pressure(const uint8_t* __restrict__ dmask,
 // rounding noise: the caller then passes enabled = 0 (the noise of FP32-stored entries can
 // exceed any fixed fraction of the magnitudes, and kappa = 1 / noise would swamp the Krylov
 // space).  As a guard, the correction is also off when |sum| <= 1e-8 x the summed magnitudes.
+// The entries come packed from ap_rows_kernel (pp: one per block, zero where they do not count), kPpAhead
+// of a row in flight.  Read from the matrix, one by one behind their columns' masks and 64 bytes
+// apart, they took 172 us at 64^3 (mixed) and 31 us at 32^3; now 21 and 9.  With n_nodes = 0, kappa is 0.
+constexpr int kPpAhead = 8;
 template <typename TA>
 __global__ __launch_bounds__(kBlock) void coarse_setup_kernel(int n_nodes, const int32_t* __restrict__ rowptr,
-                                                              const int32_t* __restrict__ colidx,
-                                                              const TA* __restrict__ A,
-                                                              const uint8_t* __restrict__ dmask, int enabled,
-                                                              RedScratch* red, GmresState* gs) {
+                                                              const TA* __restrict__ pp, RedScratch* red,
+                                                              GmresState* gs) {
     __shared__ double lds[(kBlock / 64) * 2];
     double v[2] = {0.0, 0.0};
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n_nodes; i += gridDim.x * blockDim.x) {
-        if (dmask[i] & 8u) continue;
-        for (int k = rowptr[i]; k < rowptr[i + 1]; ++k)
-            if (!(dmask[colidx[k]] & 8u)) {
-                const double a = double(A[(size_t)k * 16 + 15]);
-                v[0] += a;
-                v[1] += fabs(a);
-            }
+        const int k1 = rowptr[i + 1];
+        for (int k = rowptr[i]; k < k1; k += kPpAhead) {
+            TA a[kPpAhead];
+#pragma unroll
+            for (int q = 0; q < kPpAhead; ++q) a[q] = pp[min(k + q, k1 - 1)];
+#pragma unroll
+            for (int q = 0; q < kPpAhead; ++q)
+                if (k + q < k1) {
+                    v[0] += double(a[q]);
+                    v[1] += fabs(double(a[q]));
+                }
+        }
     }
     block_sum<2>(v, lds);
     if (threadIdx.x == 0) {
@@ -567,7 +534,7 @@ __global__ __launch_bounds__(kBlock) void coarse_setup_kernel(int n_nodes, const
     __syncthreads();
     if (threadIdx.x == 0) {
         const bool usable = isfinite(tot[0]) && fabs(tot[0]) > 1e-8 * tot[1];
-        gs->kappa = (enabled && usable) ? 1.0 / tot[0] : 0.0;
+        gs->kappa = usable ? 1.0 / tot[0] : 0.0;
         red->counter = 0u;
     }
 }
@@ -759,6 +726,15 @@ __global__ __launch_bounds__(kDrLoadThreads) void dr_load_kernel(int kk, int np,
 // A P for the Arnoldi steps: block (i, b) times the preconditioner block of node b, so that
 // the step's SpMV applies the preconditioner on the fly.  Four lanes per block, lane r forms
 // row r; the product is summed in FP64 and stored in T.
+template <typename T, typename V4>
+__device__ __forceinline__ T ap_entry(const V4& a, T m0, T m1, T m2, T m3) {
+    return T(dot4<double>(a.x, a.y, a.z, a.w, m0, m1, m2, m3));
+}
+// The same with lane q of the quad holding row q's entry of the column.
+template <typename T, typename V4>
+__device__ __forceinline__ T ap_quad(const V4& a, T m) {
+    return ap_entry<T>(a, quad_bcast<0>(m), quad_bcast<1>(m), quad_bcast<2>(m), quad_bcast<3>(m));
+}
 template <typename T>
 __global__ void ap_blocks_kernel(int64_t nb, const int32_t* __restrict__ colidx, const T* __restrict__ A,
                                  const T* __restrict__ Minv, T* __restrict__ AP) {
@@ -769,26 +745,53 @@ __global__ void ap_blocks_kernel(int64_t nb, const int32_t* __restrict__ colidx,
     using V4 = typename Vec4<T>::type;
     const V4 a = *reinterpret_cast<const V4*>(A + k * 16 + r * 4);
     const T* M = Minv + (size_t)colidx[k] * 16;
-    double o[4];
+    T o[4];
 #pragma unroll
-    for (int cc = 0; cc < 4; ++cc)
-        o[cc] = double(a.x) * double(M[cc]) + double(a.y) * double(M[4 + cc]) + double(a.z) * double(M[8 + cc]) +
-                double(a.w) * double(M[12 + cc]);
-    *reinterpret_cast<V4*>(AP + k * 16 + r * 4) = V4{T(o[0]), T(o[1]), T(o[2]), T(o[3])};
+    for (int cc = 0; cc < 4; ++cc) o[cc] = ap_entry<T>(a, M[cc], M[4 + cc], M[8 + cc], M[12 + cc]);
+    *reinterpret_cast<V4*>(AP + k * 16 + r * 4) = V4{o[0], o[1], o[2], o[3]};
 }
 
-// A z for z = 1 on every free pressure dof: per row, the sum of the pressure columns of the
-// blocks whose column node has a free pressure.  Four lanes per block row.
+// The same by rows, with what the coarse pressure mode needs of A: A z for z = 1 on every free pressure
+// dof (per row, the sum of the pressure columns of the blocks whose column node has a free pressure,
+// in order), and, if pp is given, the entries that couple two free pressures.  Four lanes per block
+// row, lane r holding row r of the block and of its column's preconditioner block; kApAhead blocks in
+// flight.  As three launches that each read the matrix, this and the sum of pp took 363 us at 64^3
+// (mixed) and 60 us at 32^3; now 115 + 21 and 17 + 9.  With 8 FP32 blocks in flight 144 and 18.6; with
+// every lane loading the whole preconditioner block (4 in flight) 168 and 20.
 template <typename T>
-__global__ void coarse_column_kernel(int n_rows, const int32_t* __restrict__ rowptr,
-                                     const int32_t* __restrict__ colidx, const T* __restrict__ A,
-                                     const uint8_t* __restrict__ dmask, T* __restrict__ Az) {
+__global__ __launch_bounds__(kBlock) void ap_rows_kernel(int n_rows, const int32_t* __restrict__ rowptr,
+                                                         const int32_t* __restrict__ colidx, const T* __restrict__ A,
+                                                         const T* __restrict__ Minv, const uint8_t* __restrict__ dmask,
+                                                         T* __restrict__ AP, T* __restrict__ Az, T* __restrict__ pp) {
+    constexpr int kApAhead = 64 / sizeof(T);             // most rows of a tetrahedral mesh at once in FP32
+    using V4 = typename Vec4<T>::type;
     const int tid = blockIdx.x * blockDim.x + threadIdx.x;
     const int row = tid >> 2, r = tid & 3;
     if (row >= n_rows) return;
+    const int k1 = rowptr[row + 1];
+    const bool row_free = !(dmask[row] & 8u);
     double acc = 0.0;
-    for (int k = rowptr[row]; k < rowptr[row + 1]; ++k)
-        if (!(dmask[colidx[k]] & 8u)) acc += double(A[(size_t)k * 16 + r * 4 + 3]);
+    for (int kb = rowptr[row]; kb < k1; kb += kApAhead) {
+        V4 a[kApAhead], m[kApAhead];
+        bool col_free[kApAhead];
+#pragma unroll
+        for (int u = 0; u < kApAhead; ++u) {
+            const int k = min(kb + u, k1 - 1), col = colidx[k];
+            a[u] = *reinterpret_cast<const V4*>(A + (size_t)k * 16 + r * 4);
+            col_free[u] = !(dmask[col] & 8u);
+            m[u] = *reinterpret_cast<const V4*>(Minv + (size_t)col * 16 + r * 4);
+        }
+#pragma unroll
+        for (int u = 0; u < kApAhead; ++u) {
+            if (kb + u >= k1) continue;                  // the four lanes of a row agree
+            const size_t k = (size_t)kb + u;
+            *reinterpret_cast<V4*>(AP + k * 16 + r * 4) =
+                V4{ap_quad<T>(a[u], m[u].x), ap_quad<T>(a[u], m[u].y), ap_quad<T>(a[u], m[u].z),
+                   ap_quad<T>(a[u], m[u].w)};
+            if (col_free[u]) acc += double(a[u].w);
+            if (pp && r == 3) pp[k] = row_free && col_free[u] ? a[u].w : T(0);
+        }
+    }
     Az[4 * (size_t)row + r] = T(acc);
 }
 
@@ -2459,7 +2462,6 @@ int launch_fill(void* p, size_t bytes, hipStream_t s) {
 }
 
 int launch_spmv(vms_ctx* c, const void* A, const void* x, void* y, hipStream_t s) {
-    const int n = 4 * c->n_nodes;
     if (c->prec == VMS_FP64)
         spmv_kernel<double, double, double, double, 0><<<spmv_grid(c->n_nodes), kBlock, 0, s>>>(
             c->n_nodes, c->rowptr, c->colidx, (const double*)A, (const double*)x, (const double*)nullptr, (double*)y, nullptr);
@@ -2498,32 +2500,31 @@ static int launch_full_pc_setup(vms_ctx* c, const void* A, void* Minv, hipStream
     return check_hip(c, hipGetLastError(), "schur diagonal setup launch");
 }
 
-// A P and A z for the Arnoldi steps (after the preconditioner blocks are set).
-int launch_ap_setup(vms_ctx* c, const void* A, hipStream_t s) {
+// A P and A z for the Arnoldi steps (after the preconditioner blocks are set), and for condensed systems
+// the coarse pressure mode's kappa (set before, for uncondensed ones).
+template <typename T>
+static void launch_ap_setup_t(vms_ctx* c, const T* A, int coarse_pressure, hipStream_t s) {
+    if (c->zfull) {
+        const int g = (int)((4 * c->nb + kBlock - 1) / kBlock);
+        ap_blocks_kernel<T><<<g, kBlock, 0, s>>>(c->nb, c->colidx, A, (const T*)c->Minv, (T*)c->AP);
+        spmv_kernel<T, double, T, double, 0><<<spmv_grid(c->n_nodes), kBlock, 0, s>>>(
+            c->n_nodes, c->rowptr, c->colidx, A, c->zfull, (const double*)nullptr, (T*)c->Az, nullptr);
+        return;
+    }
+    T* pp = coarse_pressure ? (T*)c->pp : nullptr;
+    ap_rows_kernel<T><<<grid_for(4 * (int64_t)c->n_nodes), kBlock, 0, s>>>(
+        c->n_nodes, c->rowptr, c->colidx, A, (const T*)c->Minv, c->dmask, (T*)c->AP, (T*)c->Az, pp);
+    const int nk = pp ? c->n_nodes : 0;
+    coarse_setup_kernel<T><<<red_grid(nk), kBlock, 0, s>>>(nk, c->rowptr, pp, c->red, c->gs);
+}
+
+int launch_ap_setup(vms_ctx* c, const void* A, int coarse_pressure, hipStream_t s) {
     const double es = elt_size(c);
     PhaseScope ph(c, VMS_PH_PCAPPLY, (double)c->nb * (32.0 * es + 4.0) + (double)c->n_nodes * 16.0 * es, s);
-    const int g = (int)((4 * c->nb + kBlock - 1) / kBlock);
-    if (c->prec == VMS_FP64) {
-        ap_blocks_kernel<double><<<g, kBlock, 0, s>>>(c->nb, c->colidx, (const double*)A, (const double*)c->Minv,
-                                                     (double*)c->AP);
-        if (c->zfull)
-            spmv_kernel<double, double, double, double, 0><<<spmv_grid(c->n_nodes), kBlock, 0, s>>>(
-                c->n_nodes, c->rowptr, c->colidx, (const double*)A, c->zfull, (const double*)nullptr,
-                (double*)c->Az, nullptr);
-        else
-            coarse_column_kernel<double><<<grid_for(4 * (int64_t)c->n_nodes), kBlock, 0, s>>>(
-                c->n_nodes, c->rowptr, c->colidx, (const double*)A, c->dmask, (double*)c->Az);
-    } else {
-        ap_blocks_kernel<float><<<g, kBlock, 0, s>>>(c->nb, c->colidx, (const float*)A, (const float*)c->Minv,
-                                                    (float*)c->AP);
-        if (c->zfull)
-            spmv_kernel<float, double, float, double, 0><<<spmv_grid(c->n_nodes), kBlock, 0, s>>>(
-                c->n_nodes, c->rowptr, c->colidx, (const float*)A, c->zfull, (const double*)nullptr,
-                (float*)c->Az, nullptr);
-        else
-            coarse_column_kernel<float><<<grid_for(4 * (int64_t)c->n_nodes), kBlock, 0, s>>>(
-                c->n_nodes, c->rowptr, c->colidx, (const float*)A, c->dmask, (float*)c->Az);
-    }
+    if (c->prec == VMS_FP64)
+        launch_ap_setup_t(c, (const double*)A, coarse_pressure, s);
+    else
+        launch_ap_setup_t(c, (const float*)A, coarse_pressure, s);
     return check_hip(c, hipGetLastError(), "A P setup launch");
 }
 
@@ -2598,14 +2599,8 @@ int gmres_solve(vms_ctx* c, const void* A, const double* b, double* x, const vms
             full_coarse_setup_kernel<float><<<red_grid(nn), kBlock, 0, s>>>(
                 nn, c->rowptr, c->colidx, (const float*)A, c->dmask, c->zfull, coarse_pressure, c->red, c->gs);
         }
-    } else if (c->prec == VMS_FP64) {
-        coarse_setup_kernel<double><<<red_grid(c->n_nodes), kBlock, 0, s>>>(
-            c->n_nodes, c->rowptr, c->colidx, (const double*)A, c->dmask, coarse_pressure, c->red, c->gs);
-    } else {
-        coarse_setup_kernel<float><<<red_grid(c->n_nodes), kBlock, 0, s>>>(
-            c->n_nodes, c->rowptr, c->colidx, (const float*)A, c->dmask, coarse_pressure, c->red, c->gs);
     }
-    if ((rc = launch_ap_setup(c, A, s))) return rc;
+    if ((rc = launch_ap_setup(c, A, coarse_pressure, s))) return rc;
     launch_norm<double>(c, n, b, 1, s);
     double bn = 0.0;
     if ((rc = read_scalar(c, 1, &bn, s))) return rc;
@@ -2697,7 +2692,7 @@ int gmres_solve(vms_ctx* c, const void* A, const double* b, double* x, const vms
             // the learned blocks did not deliver within half the budget: continue from the
             // current iterate with plain block-Jacobi
             if ((rc = launch_bj_setup(c, A, c->Minv, s))) return rc;
-            if ((rc = launch_ap_setup(c, A, s))) return rc;
+            if ((rc = launch_ap_setup(c, A, coarse_pressure, s))) return rc;
             using_learned = false;
             inf.fell_back_to_bj = 1;
             kk = 0;                // the kept basis belongs to the old operator

@@ -22,81 +22,79 @@ constexpr int OFF_W1 = 0, OFF_B1 = NHID * NIN, OFF_W2 = OFF_B1 + NHID, OFF_B2 = 
 
 inline int grid_for(int64_t n, int block = kBlock) { return (int)((n + block - 1) / block); }
 
-// Gauss-Jordan inverse of a 4x4 block in FP64 with partial pivoting; false if singular.
-__device__ bool invert4(const double in[16], double out[16]) {
-    double m[4][8];
-    for (int r = 0; r < 4; ++r)
-        for (int c = 0; c < 4; ++c) {
-            m[r][c] = in[r * 4 + c];
-            m[r][4 + c] = r == c ? 1.0 : 0.0;
-        }
-    for (int col = 0; col < 4; ++col) {
-        int piv = col;
-        double best = fabs(m[col][col]);
-        for (int r = col + 1; r < 4; ++r)
-            if (fabs(m[r][col]) > best) {
-                best = fabs(m[r][col]);
-                piv = r;
-            }
-        if (!(best > 0.0)) return false;
-        if (piv != col)
-            for (int c = 0; c < 8; ++c) {
-                const double t = m[col][c];
-                m[col][c] = m[piv][c];
-                m[piv][c] = t;
-            }
-        const double ip = 1.0 / m[col][col];
-        for (int c = 0; c < 8; ++c) m[col][c] *= ip;
-        for (int r = 0; r < 4; ++r) {
-            if (r == col) continue;
-            const double f = m[r][col];
-            for (int c = 0; c < 8; ++c) m[r][c] -= f * m[col][c];
-        }
-    }
-    for (int r = 0; r < 4; ++r)
-        for (int c = 0; c < 4; ++c) out[r * 4 + c] = m[r][4 + c];
-    return true;
+// Features of node i (see vms.h) and D_i^-1 (float, row-major).  Four lanes per node, lane r = row r of
+// the blocks, kFeatAhead blocks in flight: the launch reads every block of the matrix once, a whole
+// block per quad and load.  With a lane per node (64 bytes apart, a block at a time) and the inverse
+// in scratch memory it took 17.6 us at 32^3 (mixed); now 13.3, most of it FP64 arithmetic (4 or 16
+// blocks in flight take the same).
+constexpr int kFeatAhead = 8;
+
+// Entry r of four, by selects: the empty asm keeps the compiler from indexing them in scratch memory.
+__device__ __forceinline__ double by_lane(int r, double a, double b, double c, double d) {
+    asm("" : "+v"(a));
+    asm("" : "+v"(b));
+    asm("" : "+v"(c));
+    asm("" : "+v"(d));
+    return r < 2 ? (r == 0 ? a : b) : (r == 2 ? c : d);
 }
 
-// Features of node i (see vms.h) and D_i^-1 (float, row-major).
 template <typename TA>
-__global__ void features_kernel(int n, const int32_t* __restrict__ rowptr, const int32_t* __restrict__ diagpos,
-                                const TA* __restrict__ A, const uint8_t* __restrict__ dmask,
-                                float* __restrict__ feats, float* __restrict__ dinv, int32_t* flags) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int dp = diagpos[i];
-    double D[16];
+__global__ __launch_bounds__(kBlock) void features_kernel(int n, const int32_t* __restrict__ rowptr,
+                                                          const int32_t* __restrict__ diagpos,
+                                                          const TA* __restrict__ A, const uint8_t* __restrict__ dmask,
+                                                          float* __restrict__ feats, float* __restrict__ dinv,
+                                                          int32_t* flags) {
+    using V4 = typename Vec4<TA>::type;
+    const int tid = blockIdx.x * blockDim.x + threadIdx.x;
+    const int i = tid >> 2, r = tid & 3;
+    if (i >= n) return;                         // the four lanes of a quad agree
+    const int dp = diagpos[i], k1 = rowptr[i + 1];
+    const V4* rows = reinterpret_cast<const V4*>(A) + r;
+    const V4 d = rows[4 * (size_t)dp];
+    const double dr[4] = {double(d.x), double(d.y), double(d.z), double(d.w)};
+    double off = 0.0;
+    for (int k = rowptr[i]; k < k1; k += kFeatAhead) {
+        V4 b[kFeatAhead];
+#pragma unroll
+        for (int q = 0; q < kFeatAhead; ++q) b[q] = rows[4 * (size_t)min(k + q, k1 - 1)];
+#pragma unroll
+        for (int q = 0; q < kFeatAhead; ++q)
+            if (k + q < k1 && k + q != dp)
+                off += fabs(double(b[q].x)) + fabs(double(b[q].y)) + fabs(double(b[q].z)) + fabs(double(b[q].w));
+    }
+    double D[4][4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        D[0][c] = dpp_mov<0x00>(dr[c]);          // quad broadcasts of rows 0 .. 3
+        D[1][c] = dpp_mov<0x55>(dr[c]);
+        D[2][c] = dpp_mov<0xAA>(dr[c]);
+        D[3][c] = dpp_mov<0xFF>(dr[c]);
+    }
     double fro = 0.0;
-    for (int q = 0; q < 16; ++q) {
-        D[q] = double(A[(size_t)dp * 16 + q]);
-        fro += D[q] * D[q];
-    }
+#pragma unroll
+    for (int q = 0; q < 16; ++q) fro += D[q >> 2][q & 3] * D[q >> 2][q & 3];
     fro = sqrt(fro);
-    double off[4] = {0, 0, 0, 0};
-    for (int k = rowptr[i]; k < rowptr[i + 1]; ++k) {
-        if (k == dp) continue;
-        const TA* b = A + (size_t)k * 16;
-        for (int r = 0; r < 4; ++r)
-            off[r] += fabs(double(b[r * 4])) + fabs(double(b[r * 4 + 1])) + fabs(double(b[r * 4 + 2])) +
-                      fabs(double(b[r * 4 + 3]));
-    }
     float* x = feats + (size_t)i * NIN;
     const double ifro = fro > 0.0 ? 1.0 / fro : 0.0;
-    for (int q = 0; q < 16; ++q) x[q] = float(D[q] * ifro);
-    x[16] = float(log(fmax(fro, 1e-300)));
-    const uint32_t dm = dmask[i];
-    for (int r = 0; r < 4; ++r) {
-        x[17 + r] = float(log1p(off[r] / fmax(fabs(D[r * 5]), 1e-300)));
-        x[21 + r] = (dm & (1u << r)) ? 1.f : 0.f;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) x[4 * r + c] = float(dr[c] * ifro);
+    const double drr = by_lane(r, dr[0], dr[1], dr[2], dr[3]);
+    x[17 + r] = float(log1p(off / fmax(fabs(drr), 1e-300)));
+    x[21 + r] = (dmask[i] & (1u << r)) ? 1.f : 0.f;
+    double Di[4][4];
+    const bool ok = invert4(D, Di);
+    if (r == 0) {
+        x[16] = float(log(fmax(fro, 1e-300)));
+        if (!ok) atomicAdd(&flags[2], 1);
     }
-    double Di[16];
-    if (!invert4(D, Di)) {
-        atomicAdd(&flags[2], 1);
-        for (int q = 0; q < 16; ++q) Di[q] = (q % 5 == 0) ? 1.0 : 0.0;
+    if (!dinv) return;
+    float op[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const double v = by_lane(r, Di[0][c], Di[1][c], Di[2][c], Di[3][c]);
+        op[c] = ok ? float(v) : (r == c ? 1.f : 0.f);
     }
-    if (dinv)
-        for (int q = 0; q < 16; ++q) dinv[(size_t)i * 16 + q] = float(Di[q]);
+    *reinterpret_cast<float4*>(dinv + (size_t)i * 16 + 4 * r) = make_float4(op[0], op[1], op[2], op[3]);
 }
 
 // Four consecutive values of a caller's array: one wide load that asks for no more than the
@@ -633,11 +631,11 @@ constexpr int kBwdBlocks = 256;
 
 int features(vms_ctx* c, const void* A, float* feats, float* dinv, hipStream_t s) {
     if (c->prec == VMS_FP64)
-        features_kernel<double><<<grid_for(c->n_nodes), kBlock, 0, s>>>(c->n_nodes, c->rowptr, c->diagpos,
+        features_kernel<double><<<grid_for(4 * (int64_t)c->n_nodes), kBlock, 0, s>>>(c->n_nodes, c->rowptr, c->diagpos,
                                                                        (const double*)A, c->dmask, feats, dinv,
                                                                        c->flags);
     else
-        features_kernel<float><<<grid_for(c->n_nodes), kBlock, 0, s>>>(c->n_nodes, c->rowptr, c->diagpos,
+        features_kernel<float><<<grid_for(4 * (int64_t)c->n_nodes), kBlock, 0, s>>>(c->n_nodes, c->rowptr, c->diagpos,
                                                                       (const float*)A, c->dmask, feats, dinv,
                                                                       c->flags);
     return check_hip(c, hipGetLastError(), "features launch");
