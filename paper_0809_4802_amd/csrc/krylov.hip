@@ -1024,7 +1024,7 @@ __device__ __forceinline__ ColLoads columns_load(int j, const GmresState* gs, bo
 __device__ void columns_close(int j, int dk, GmresState* gs, const StepIn* in, const ColLoads& c) {
     constexpr int ld = kMaxRestart + 1;
     constexpr int kWaves = kBlock / 64;
-    constexpr int kBatch = 4;                           // further H loads per batch
+    constexpr int kBatch = 64;                           // further H loads per batch
     static_assert(kMaxRestart <= 128 && kBlock >= 64 + kMaxRestart, "two row passes; rows on waves 1..");
     __shared__ double Hc[kMaxRestart + 2];              // column j-1, final
     __shared__ double sv[kMaxRestart];                  // s
@@ -1459,25 +1459,28 @@ __global__ __launch_bounds__(kBlock, sizeof(T) * R > 8 ? 4 : 5) void update_fuse
 // here the vectors in progress, H and the rotations stay in LDS, the basis in the CU's caches, and a
 // step is four barriers.  The last wave keeps H beside the others' work: it forms the step's
 // scalars, makes column j-1 final beside the update, rotates it beside the next SpMV and forms
-// column j beside the next dots.  With every wave taking part in everything a step took 1.3 us more.
-// A step of a 125-node FP64 system takes 9.6 us (SpMV 2.4, dots 3.0, scalars 1.1, update 3.1)
-// against 11.9 by launches, and an inexact-Newton solve on it 1490 us against 1862.  With the cycle's
-// ends, us per step at restart 50, FP64 and mixed: 64 nodes 8.5 and 8.0 (by launches 12.2 and 12.2),
-// 125 nodes 10.3 and 9.4 (12.2 and 12.4), 210 nodes 14.8 and 13.4 (12.5 and 12.4): from about 150
-// nodes on, what one CU reads of matrix and basis takes longer than the launches.  Up to 58 columns
-// H stays in LDS, a row per lane.
+// column j beside the next dots.  The others load the basis vectors they need next before they wait
+// at a barrier.  Twelve waves: with sixteen (128 registers) these loads spill and a step takes 0.6 us
+// more, without them it takes 0.6 us more too; with all waves taking part in everything, 1.8.
+// A step of a 125-node FP64 system takes 9.0 us against 11.9 by launches, and an inexact-Newton solve
+// on it 1386 us against 1862.  With the cycle's ends, us per step at restart 50, FP64 and mixed: 27
+// nodes 6.2 and 6.5, 64 nodes 7.2 and 6.9 (by launches 12.2 and 12.2), 125 nodes 9.7 and 8.9 (12.2 and
+// 12.4); with sixteen waves 210 nodes took 14.8 and 13.4 (12.5 and 12.4): from about 150 nodes on, what
+// one CU reads of matrix and basis takes longer than the launches.  Keeping the first vectors in
+// LDS too gains nothing.  Up to 58 columns H stays in LDS, a row per lane.
 // Every sum is formed in the order of the three kernels (a wave takes a slot's 64-node parts in
 // turn) and with the same roundings, so that a cycle gives the same bits on either path.
 constexpr int kSmallNodes = 128;
 constexpr int kSmallBlocks = 4096;          // blocks of the matrix (their columns are kept in LDS)
 constexpr int kSmallSteps = 58;             // columns; rows of H one per lane
-constexpr int kSmallThreads = 1024;
+constexpr int kSmallThreads = 768;          // three waves a SIMD: 168 registers
 constexpr int kSmallWaves = kSmallThreads / 64 - 1;      // beside the wave that keeps H
 constexpr int kSmallWorkers = 64 * kSmallWaves;
 constexpr int kSmallLd = 61;                // odd: a row of H across its columns spreads over the banks
-constexpr int kSmallSlots = (kSmallSteps + 2 + kSmallWaves - 1) / kSmallWaves;   // dot slots per wave
+constexpr int kSmallSlots = 4;              // dot slots of a wave at a time
 static_assert(kSmallNodes <= kDotThreads, "one dot chunk, one node per lane and part");
-static_assert(kSmallSlots == 4 && kSmallSteps + 3 <= kSmallLd && kSmallSteps + 2 <= 64, "slots; rows");
+static_assert(4 * kSmallNodes <= kSmallWorkers, "one row of the vectors per worker");
+static_assert(kSmallSteps + 3 <= kSmallLd && kSmallSteps + 2 <= 64, "rows");
 
 __device__ __forceinline__ void wave_sync() {           // LDS of one wave: order its accesses
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -1514,44 +1517,55 @@ __device__ __forceinline__ double wave_sum8(double (&v)[8]) {
     return t + __shfl_xor(t, 32, 64);
 }
 
-// The dot slots y = wave, wave + kSmallWaves, ... of the step into L.sums.
+// The finished vectors of dot slots y0, y0 + kSmallWaves, ... at part's nodes.
+template <typename T>
+__device__ __forceinline__ void small_load(int n_nodes, int j, int y0, int part, const T* V,
+                                           typename Vec4<T>::type (&x)[kSmallSlots]) {
+    using V4 = typename Vec4<T>::type;
+    const int node = min(64 * part + ((int)threadIdx.x & 63), n_nodes - 1);
+#pragma unroll
+    for (int q = 0; q < kSmallSlots; ++q)
+        x[q] = reinterpret_cast<const V4*>(V)[(size_t)min(y0 + kSmallWaves * q, max(j - 1, 0)) * n_nodes + node];
+}
+
+// The wave's dot slots of the step into L.sums; x: the first part's vectors (small_load).
 template <typename T>
 __device__ __forceinline__ void small_dots(int n_nodes, int j, const T* V, SmallLds<T>& L,
-                                           const uint8_t* __restrict__ dmask) {
+                                           const uint8_t* __restrict__ dmask,
+                                           typename Vec4<T>::type (&x)[kSmallSlots]) {
     using V4 = typename Vec4<T>::type;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const V4* u4 = reinterpret_cast<const V4*>(L.u);
     const V4* w4 = reinterpret_cast<const V4*>(L.w);
-    double t = 0.0;
-    for (int part = 0; 64 * part < n_nodes; ++part) {
-        const int node = min(64 * part + lane, n_nodes - 1);
-        const bool in = 64 * part + lane < n_nodes;
-        V4 x[kSmallSlots];
+    for (int y0 = wave; y0 <= j + 1; y0 += kSmallWaves * kSmallSlots) {
+        double t = 0.0;
+        for (int part = 0; 64 * part < n_nodes; ++part) {
+            const int node = min(64 * part + lane, n_nodes - 1);
+            const bool in = 64 * part + lane < n_nodes;
+            if (part > 0 || y0 > wave) small_load(n_nodes, j, y0, part, V, x);
+            const bool masked = (dmask[node] & 8u) != 0;
+            const V4 u = u4[node], b = w4[node];
+            double d[2 * kSmallSlots];
 #pragma unroll
-        for (int q = 0; q < kSmallSlots; ++q)
-            x[q] = reinterpret_cast<const V4*>(V)[(size_t)min(wave + kSmallWaves * q, max(j - 1, 0)) * n_nodes + node];
-        const bool masked = (dmask[node] & 8u) != 0;
-        const V4 u = u4[node], b = w4[node];
-        double d[2 * kSmallSlots];
-#pragma unroll
-        for (int q = 0; q < kSmallSlots; ++q) {
-            const int y = wave + kSmallWaves * q;            // uniform over the wave
-            double d0 = 0.0, d1 = 0.0;
-            if (y <= j) {
-                const V4 v = y < j ? x[q] : u;
-                d0 = double(dot4(v, u));
-                d1 = double(dot4(v, b));
-            } else if (y == j + 1) {
-                d0 = double(dot4(b, b));
-                d1 = masked ? 0.0 : double(b.w);
+            for (int q = 0; q < kSmallSlots; ++q) {
+                const int y = y0 + kSmallWaves * q;              // uniform over the wave
+                double d0 = 0.0, d1 = 0.0;
+                if (y <= j) {
+                    const V4 v = y < j ? x[q] : u;
+                    d0 = double(dot4(v, u));
+                    d1 = double(dot4(v, b));
+                } else if (y == j + 1) {
+                    d0 = double(dot4(b, b));
+                    d1 = masked ? 0.0 : double(b.w);
+                }
+                d[2 * q] = in ? d0 : 0.0;
+                d[2 * q + 1] = in ? d1 : 0.0;
             }
-            d[2 * q] = in ? d0 : 0.0;
-            d[2 * q + 1] = in ? d1 : 0.0;
+            t += wave_sum8(d);
         }
-        t += wave_sum8(d);
+        const int i = 4 * (lane & 1) + (lane & 2) + ((lane >> 2) & 1), y = y0 + kSmallWaves * (i >> 1);
+        if (lane < 8 && y <= j + 1) L.sums[2 * y + (i & 1)] = t;
     }
-    const int i = 4 * (lane & 1) + (lane & 2) + ((lane >> 2) & 1), y = wave + kSmallWaves * (i >> 1);
-    if (lane < 8 && y <= j + 1) L.sums[2 * y + (i & 1)] = t;
 }
 
 // What the books' wave keeps of a step until its column is formed: lane i holds s_i and t_i.
@@ -1686,20 +1700,17 @@ __global__ __launch_bounds__(kSmallThreads) void small_cycle_kernel(int n_nodes,
     constexpr int ld = kMaxRestart + 1;
     constexpr int kRows = kSmallWorkers / kSpmvLanes;          // rows per pass of the SpMV
     constexpr int Q = kSpmvLanes / 4;
-    constexpr int kBatch = 64 / sizeof(T);                     // basis vectors and blocks of a lane in flight
+    constexpr int kBatch = 64 / sizeof(T);                    // basis vectors and blocks of a lane in flight
     constexpr int kUnroll = 32 / sizeof(T);
     using V4 = typename Vec4<T>::type;
     extern __shared__ __align__(16) unsigned char small_smem[];
     SmallLds<T>& L = *reinterpret_cast<SmallLds<T>*>(small_smem);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const bool books = wave == kSmallWaves;                    // the wave that keeps H
+    const bool books = __builtin_amdgcn_readfirstlane(wave) == kSmallWaves;     // the wave that keeps H
     const int n = 4 * n_nodes;
     if (gs->done) return;
     const int reorth = gs->reorth;
     const double beta = gs->beta, kappa = gs->kappa;
-    double su = gs->su, gcur = gs->gin[0];
-    SmallStep p{0.0, 0.0, 0.0, 0.0, 0.0};
-    GivensCtx gc{gs->tol_abs, gs->progress, gs->gen, 0};
     for (int i = tid; i < n; i += kSmallThreads) L.u[i] = V[(size_t)dk * n + i];
     for (int e = tid; e < dk * (dk + 1); e += kSmallThreads)
         L.H[e / (dk + 1)][e % (dk + 1)] = gs->H[(size_t)(e / (dk + 1)) * ld + e % (dk + 1)];
@@ -1709,104 +1720,42 @@ __global__ __launch_bounds__(kSmallThreads) void small_cycle_kernel(int n_nodes,
     for (int i = tid; i <= n_nodes; i += kSmallThreads) L.ptr[i] = (uint16_t)rowptr[i];
     for (int k = tid; k < rowptr[n_nodes]; k += kSmallThreads) L.col[k] = (uint8_t)colidx[k];
     if (tid == 0) L.done = 0;
-    if (books) __builtin_amdgcn_s_setprio(3);
     __syncthreads();
-    for (int j = dk; j < end; ++j) {
-        // w = (A P) u_j + kappa S(u_j) A z; beside it, the rotations of the step before
-        if (books) {
+    // the two kinds of waves run loops of their own (their registers are then not held side by
+    // side), which meet at the same barriers: four per step, and the tail's
+    if (books) {
+        double su = gs->su, gcur = gs->gin[0];
+        SmallStep p{0.0, 0.0, 0.0, 0.0, 0.0};
+        GivensCtx gc{gs->tol_abs, gs->progress, gs->gen, 0};
+        __builtin_amdgcn_s_setprio(3);
+        int j = dk;
+        for (; j < end; ++j) {
             if (j > dk) small_rotate(j - 1, dk, L, p.rho, p.hh, gcur, gc, false, gs);
-        } else {
-            const int sub = tid % kSpmvLanes, q = sub >> 2, r = sub & 3;
-            for (int row0 = 0; row0 < n_nodes; row0 += kRows) {
-                const int row = row0 + tid / kSpmvLanes;
-                T acc = T(0);
-                if (row < n_nodes) {
-                    const int k1 = L.ptr[row + 1];
-                    const T az = Az[4 * (size_t)row + r];
-                    for (int kb = L.ptr[row] + q; kb < k1; kb += kUnroll * Q) {
-                        V4 av[kUnroll];
-#pragma unroll
-                        for (int u = 0; u < kUnroll; ++u)
-                            if (kb + u * Q < k1) av[u] = *reinterpret_cast<const V4*>(AP + (size_t)(kb + u * Q) * 16 + r * 4);
-#pragma unroll
-                        for (int u = 0; u < kUnroll; ++u) {
-                            if (kb + u * Q >= k1) continue;          // the four lanes of a quad agree
-                            const T xr = L.u[L.col[kb + u * Q] * 4 + r];
-                            const T x0 = quad_bcast<0>(xr), x1 = quad_bcast<1>(xr), x2 = quad_bcast<2>(xr),
-                                    x3 = quad_bcast<3>(xr);
-                            acc += dot4<T>(av[u].x, av[u].y, av[u].z, av[u].w, x0, x1, x2, x3);
-                        }
-                    }
-                    acc += __shfl_xor(acc, 4, 64);               // the eight lanes of a row agree
-                    if (q == 0) L.w[4 * row + r] = acc + T(kappa * su) * az;
-                }
-            }
-        }
-        __syncthreads();
-        if (L.done) break;                                     // uniform
-        if (books) {
+            __syncthreads();
+            if (L.done) break;
             if (j > dk) small_column(j - 1, dk, L, p, reorth);
-        } else {
-            small_dots(n_nodes, j, V, L, dmask);
-        }
-        __syncthreads();
-        if (books) {
+            __syncthreads();
             const StepOut o = step_scalars_of(j, eps_dot, L.sums, L.svl, su, reorth);
             p = SmallStep{reorth && lane < j ? L.sums[2 * lane] : 0.0, lane < j ? L.sums[2 * lane + 1] : 0.0, o.rho,
                           o.cj, o.hh};
             if (lane == 0) L.o = o;
-        }
-        __syncthreads();
-        const StepOut o = L.o;
-        // q_j and u_{j+1}; beside them, column j-1 of H becomes final
-        if (books) {
+            __syncthreads();
             small_final(j, dk, L, p, beta, gs);
             if (lane == 0) {
                 L.svl[j] = o.svj;
                 gs->svs[j] = o.svj;
             }
             if (!(o.hh > 0.0)) small_column(j, dk, L, p, reorth);     // the rotation closes column j
-        } else if (o.rho > 0.0) {
-            const double s_l = reorth && lane < j ? L.sums[2 * lane] : 0.0, t_l = lane < j ? L.sums[2 * lane + 1] : 0.0;
-            for (int i0 = 64 * wave; i0 < n; i0 += kSmallWorkers) {   // uniform over the wave
-                const int i = min(i0 + lane, n - 1);
-                double aq = double(L.u[i]), aw = double(L.w[i]);
-                for (int l0 = 0; l0 < j; l0 += kBatch) {
-                    T v[kBatch];
-#pragma unroll
-                    for (int q = 0; q < kBatch; ++q) v[q] = V[(size_t)min(l0 + q, j - 1) * n + i];
-#pragma unroll
-                    for (int q = 0; q < kBatch; ++q)
-                        if (l0 + q < j) {
-                            aq -= read_lane(s_l, l0 + q) * double(v[q]);
-                            aw -= read_lane(t_l, l0 + q) * double(v[q]);
-                        }
-                }
-                const double q = aq / o.rho;
-                if (i0 + lane < n) {
-                    V[(size_t)j * n + i] = T(q);
-                    if (o.hh > 0.0) {
-                        const T un = T((aw - o.cj * q) / (o.rho * o.hh));
-                        V[(size_t)(j + 1) * n + i] = un;
-                        L.u[i] = un;
-                    }
-                }
-            }
-        }
-        su = o.su_next;
-        __syncthreads();
-    }
-    const bool stopped = L.done;
-    __syncthreads();                                           // read before the next rotation may set it
-    if (!stopped) {
-        // the second pass of the last vector completes the last column
-        if (books) small_rotate(end - 1, dk, L, p.rho, p.hh, gcur, gc, false, gs);
-        __syncthreads();
-        if (!L.done) {                                         // not set again before the next barrier
-            if (books) small_column(end - 1, dk, L, p, reorth);
-            else small_dots(n_nodes, end, V, L, dmask);
+            su = o.su_next;
             __syncthreads();
-            if (books) {
+        }
+        if (j == end) {
+            // the second pass of the last vector completes the last column
+            small_rotate(end - 1, dk, L, p.rho, p.hh, gcur, gc, false, gs);
+            __syncthreads();
+            if (!L.done) {
+                small_column(end - 1, dk, L, p, reorth);
+                __syncthreads();
                 const double si = reorth && lane < end ? L.sums[2 * lane] : 0.0;
                 double a[2] = {0.0, 0.0};
                 if (lane < end) {
@@ -1826,6 +1775,88 @@ __global__ __launch_bounds__(kSmallThreads) void small_cycle_kernel(int n_nodes,
                 small_final(end, dk, L, SmallStep{si, 0.0, rho, 0.0, 0.0}, beta, gs);
                 gc.report = 1;
                 small_rotate(end, dk, L, rho, 1.0, gcur, gc, true, gs);
+            }
+        }
+    } else {
+        const int sub = tid % kSpmvLanes, quad = sub >> 2, r = sub & 3;
+        const int iv = min(tid, n - 1);                        // the worker's vector row
+        double su = gs->su;
+        int j = dk;
+        for (; j < end; ++j) {
+            // w = (A P) u_j + kappa S(u_j) A z
+            for (int row0 = 0; row0 < n_nodes; row0 += kRows) {
+                const int row = row0 + tid / kSpmvLanes;
+                T acc = T(0);
+                if (row < n_nodes) {
+                    const int k1 = L.ptr[row + 1];
+                    const T az = Az[4 * (size_t)row + r];
+                    for (int kb = L.ptr[row] + quad; kb < k1; kb += kUnroll * Q) {
+                        V4 av[kUnroll];
+#pragma unroll
+                        for (int u = 0; u < kUnroll; ++u)
+                            if (kb + u * Q < k1) av[u] = *reinterpret_cast<const V4*>(AP + (size_t)(kb + u * Q) * 16 + r * 4);
+#pragma unroll
+                        for (int u = 0; u < kUnroll; ++u) {
+                            if (kb + u * Q >= k1) continue;          // the four lanes of a quad agree
+                            const T xr = L.u[L.col[kb + u * Q] * 4 + r];
+                            const T x0 = quad_bcast<0>(xr), x1 = quad_bcast<1>(xr), x2 = quad_bcast<2>(xr),
+                                    x3 = quad_bcast<3>(xr);
+                            acc += dot4<T>(av[u].x, av[u].y, av[u].z, av[u].w, x0, x1, x2, x3);
+                        }
+                    }
+                    acc += __shfl_xor(acc, 4, 64);               // the eight lanes of a row agree
+                    if (quad == 0) L.w[4 * row + r] = acc + T(kappa * su) * az;
+                }
+            }
+            V4 x[kSmallSlots];                                 // loads that need not wait for the barrier
+            small_load(n_nodes, j, wave, 0, V, x);
+            __syncthreads();
+            if (L.done) break;
+            small_dots(n_nodes, j, V, L, dmask, x);
+            T v[kBatch];                                       // nor these for the scalars
+            if (64 * wave < n) {
+#pragma unroll
+                for (int q = 0; q < kBatch; ++q) v[q] = V[(size_t)min(q, max(j - 1, 0)) * n + iv];
+            }
+            __syncthreads();
+            __syncthreads();
+            // q_j and u_{j+1}
+            const StepOut o = L.o;
+            if (o.rho > 0.0 && 64 * wave < n) {
+                const double s_l = reorth && lane < j ? L.sums[2 * lane] : 0.0;
+                const double t_l = lane < j ? L.sums[2 * lane + 1] : 0.0;
+                double aq = double(L.u[iv]), aw = double(L.w[iv]);
+                for (int l0 = 0; l0 < j; l0 += kBatch) {
+#pragma unroll
+                    for (int q = 0; q < kBatch; ++q)
+                        if (l0 + q < j) {
+                            aq -= read_lane(s_l, l0 + q) * double(v[q]);
+                            aw -= read_lane(t_l, l0 + q) * double(v[q]);
+                        }
+                    if (l0 + kBatch < j)
+#pragma unroll
+                        for (int q = 0; q < kBatch; ++q) v[q] = V[(size_t)min(l0 + kBatch + q, j - 1) * n + iv];
+                }
+                const double q = aq / o.rho;
+                if (tid < n) {
+                    V[(size_t)j * n + tid] = T(q);
+                    if (o.hh > 0.0) {
+                        const T un = T((aw - o.cj * q) / (o.rho * o.hh));
+                        V[(size_t)(j + 1) * n + tid] = un;
+                        L.u[tid] = un;
+                    }
+                }
+            }
+            su = o.su_next;
+            __syncthreads();
+        }
+        if (j == end) {
+            __syncthreads();
+            if (!L.done) {
+                V4 x[kSmallSlots];
+                small_load(n_nodes, end, wave, 0, V, x);
+                small_dots(n_nodes, end, V, L, dmask, x);
+                __syncthreads();
             }
         }
     }
