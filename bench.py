@@ -40,7 +40,7 @@ PROFILE_EVERY = 8            # timed region: HIP events on the dominant kernel's
 COUNTER_ITERS = 64           # --counters: Arnoldi steps (SpMV launches) in the counter run
 COPY_MIB = 256               # --counters: size of the reference copy
 KERNEL_OF_PHASE = {"condense": "tile_kernel", "spmv": "spmv_kernel", "dots": "dots_kernel",
-                   "update": "update_fused_kernel", "pc_apply": "ap_blocks_kernel"}
+                   "update": "update_fused_kernel", "pc_apply": "ap_rows_kernel"}
 TRAIN_RE = (75.0, 125.0)     # Reynolds numbers of the learned correction's training systems
 DEFLATE = 10                 # harmonic Ritz vectors kept by the deflated-restart forms (GMRES(50))
 WORKLOAD_TEXT = ("lid-driven cavity 32^3 cells x 6 tets ({ne} tets, {nn} nodes), Re {re:g}, steady Newton to "
