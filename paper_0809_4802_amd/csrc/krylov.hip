@@ -268,7 +268,9 @@ __device__ __forceinline__ double quad_bcast(double v) {
 // of four times (as many bytes as the matrix block otherwise).  The four lanes share the row
 // and the block sequence, so a quad is active or inactive as a whole.
 // ROT: the launch of Arnoldi step rot_j + 1, whose workgroup 0 makes the rotations that step rot_j
-// left due (columns_rotate); the others take the rows, XCD for XCD as without it.
+// left due (columns_rotate); the others take the rows, XCD for XCD as without it.  With MODE 0 that step
+// multiplies by the caller's matrix, whose address is the cycle state's: a recorded step serves every
+// matrix that the context solves with.
 template <typename TA, typename TX, typename TY, typename TACC, int MODE, typename TB = double, bool ROT = false>
 __global__ __launch_bounds__(kBlock) void spmv_kernel(int n_rows, const int32_t* __restrict__ rowptr,
                                                       const int32_t* __restrict__ colidx,
@@ -276,6 +278,7 @@ __global__ __launch_bounds__(kBlock) void spmv_kernel(int n_rows, const int32_t*
                                                       const TB* __restrict__ b, TY* __restrict__ y, GmresState* gs,
                                                       int rot_j = 0, int dk = 0, int report = 0) {
     int slot;
+    if (ROT && MODE == 0) A = static_cast<const TA*>(gs->A);
     if (ROT) {
         if (blockIdx.x == 0) {
             __builtin_amdgcn_s_setprio(3);
@@ -637,12 +640,14 @@ __global__ __launch_bounds__(kBlock) void cycle_norm_kernel(int n, const double*
 }
 
 // Starts the cycle from the nparts partials: its norm to gs->beta, g = beta e_1, k = 0, the done
-// flag (workgroup 0), and V[0] = r / beta (V0 = V + j0 n for a deflated cycle).  Every workgroup
-// adds the partials itself, in the same order.
+// flag and the matrix of a cycle that applies P and A one after the other (workgroup 0), and
+// V[0] = r / beta (V0 = V + j0 n for a deflated cycle).  Every workgroup adds the partials itself, in
+// the same order.
 template <typename T>
 __global__ __launch_bounds__(kBlock) void cycle_v0_kernel(int n, const T* __restrict__ r, T* __restrict__ V0,
                                                           int nparts, const RedScratch* red, GmresState* gs,
-                                                          double tol_abs, int reorth, unsigned gen) {
+                                                          double tol_abs, int reorth, unsigned gen,
+                                                          const void* A) {
     __shared__ double tot[2];
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     const double e = i < n ? double(r[i]) : 0.0;
@@ -661,6 +666,7 @@ __global__ __launch_bounds__(kBlock) void cycle_v0_kernel(int n, const T* __rest
         gs->norm = nrm;
         gs->reorth = reorth;
         gs->gen = gen;
+        gs->A = A;
         report_progress(gs, 0, gs->done);
     }
 }
@@ -2202,7 +2208,8 @@ int run_cycle(vms_ctx* c, T* r0, const TM* Minv, TX* x, double tol_abs, int m, i
     T* V = basis_vectors<T>(c, 0);
     T* w = basis_vectors<T>(c, 1);
     T* z = basis_vectors<T>(c, 2);
-    // recorded graphs are told apart by restart length, kept vectors and basis precision
+    // recorded graphs are told apart by restart length, kept vectors and basis precision; every address in
+    // them is the context's (the caller's matrix is found through the cycle state)
     const int pbit = sizeof(T) == 8 ? 1 : 0;
     const uint32_t gen = ++c->cycle_gen;
     c->cycle_timed.clear();
@@ -2211,7 +2218,7 @@ int run_cycle(vms_ctx* c, T* r0, const TM* Minv, TX* x, double tol_abs, int m, i
     cycle_norm_kernel<T><<<red_grid(n), kBlock, 0, s>>>(n, r64, r64_scale, r0, x_old, x_save, c->dmask, c->red);
     // a deflated cycle puts the residual after the kept vectors and runs steps j0 .. m-1
     cycle_v0_kernel<T><<<grid_for(n), kBlock, 0, s>>>(n, r0, V + (size_t)j0 * n, red_grid(n), c->red, c->gs, tol_abs,
-                                                      cgs2, gen);
+                                                      cgs2, gen, Amat);
     const int steps = std::min(m - j0, budget);
     const double vb = (double)n * sizeof(T);      // bytes of one Krylov vector
     // algorithmic bytes of the Arnoldi SpMV: blocks and column indices, row pointers, the input
@@ -2264,7 +2271,7 @@ int run_cycle(vms_ctx* c, T* r0, const TM* Minv, TX* x, double tol_abs, int m, i
                 });
                 timed(VMS_PH_SPMV, spmv_bytes, j, st, [&] {
                     spmv_kernel<TM, T, T, T, 0, double, true><<<1 + spmv_grid(c->n_nodes), kBlock, 0, st>>>(
-                        c->n_nodes, c->rowptr, c->colidx, Amat, z, (const double*)nullptr, w, c->gs, j - 1, j0,
+                        c->n_nodes, c->rowptr, c->colidx, (const TM*)nullptr, z, (const double*)nullptr, w, c->gs, j - 1, j0,
                         lead ? 1 : 0);
                 });
             } else {

@@ -198,6 +198,7 @@ struct GmresState {
     unsigned counter;              // arrival counter of last-block reductions
     unsigned gen;                  // cycle number (host-assigned) reported with the progress word
     uint64_t* progress;            // host-mapped progress word: gen << 32 | k << 1 | done
+    const void* A;                 // the cycle's matrix, where P and A are applied one after the other
     // deflated restarting: the cycle starts with dk kept vectors V[0 .. dk-1], whose
     // columns of H (rows 0 .. dk) and R the host set; dr_qt is Q^T of the QR factors of that
     // (dk + 1) x dk block (column-major), dr_c the cycle's least-squares right-hand side
