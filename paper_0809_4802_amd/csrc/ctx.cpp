@@ -636,12 +636,10 @@ extern "C" int vms_create(const vms_mesh_desc* mesh, const vms_create_opts* opts
                 ntn += (int32_t)fresh.size();
                 ++r1;
             }
-            if (n2e_ptr[r1] - n2e_ptr[r0] >= kNoSlot) {
-                free_all(c);
-                delete c;
-                return set_error(nullptr, VMS_EINVAL, "vms_create: node " + std::to_string(r0) +
-                                                          " has more elements than a tile's records number");
-            }
+            // a tile of more slots than are staged has one node, and its item k holds slot k (the kernel
+            // goes by that: there can be more slots than an item's 16 bits number)
+            const int32_t slots = n2e_ptr[r1] - n2e_ptr[r0];
+            const bool numbered = slots <= kResidualSlots;
             const int32_t nbase = (int32_t)rnodes.size(), ibase = (int32_t)ritems.size();
             for (int64_t i = r0; i < r1; ++i) {
                 loc[i] = (int32_t)(i - r0);
@@ -676,8 +674,8 @@ extern "C" int vms_create(const vms_mesh_desc* mesh, const vms_create_opts* opts
                     for (int a = 0; a < 4; ++a) {
                         const int32_t v = t[ord[a]];
                         l |= (uint32_t)loc[v] << (8 * a);
-                        slot[a] = 0xffffu;
-                        if (own[ord[a]]) slot[a] = (uint32_t)(n2e_pos[4 * (int64_t)e + ord[a]] - n2e_ptr[r0]);
+                        slot[a] = kNoSlot;
+                        if (own[ord[a]] && numbered) slot[a] = (uint32_t)(n2e_pos[4 * (int64_t)e + ord[a]] - n2e_ptr[r0]);
                     }
                     sorted[count - 1].push_back(make_uint4((uint32_t)e | (own[0] ? 0x80000000u : 0u), l,
                                                            slot[0] | (slot[1] << 16), slot[2] | (slot[3] << 16)));
@@ -686,7 +684,6 @@ extern "C" int vms_create(const vms_mesh_desc* mesh, const vms_create_opts* opts
                 ritems.insert(ritems.end(), sorted[q].begin(), sorted[q].end());
                 sorted[q].clear();
             }
-            const int32_t slots = n2e_ptr[r1] - n2e_ptr[r0];
             rmeta.push_back(make_int4((int32_t)r0, (int32_t)r1, nbase, (int32_t)rnodes.size() - nbase));
             rmeta.push_back(make_int4(ibase, (int32_t)ritems.size(), n2e_ptr[r0], slots));
             for (int x = 0; x < 2; ++x)

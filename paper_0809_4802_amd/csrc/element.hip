@@ -884,7 +884,8 @@ struct ResidualArgs {
     const int4* __restrict__ meta;        // per tile: (n0, n1, node base, nodes), (item0, item1, slot base, slots)
     const int32_t* __restrict__ nodes;
     const uint4* __restrict__ items;      // x: element (bit 31: the tile owns its vertex 0); y: local nodes,
-                                          // owned ones first, orientation kept; z, w: their slots (0xffff: none)
+                                          // owned ones first, orientation kept; z, w: their slots (0xffff: none,
+                                          // and in a tile of more slots than are staged)
     const int32_t* __restrict__ n2e_ptr;  // a node's first slot, over the whole mesh
 };
 
@@ -944,11 +945,9 @@ __global__ __launch_bounds__(kResThreads, 3) void residual_kernel(ElemArgs args,
                                (int)(rec.y >> 24)};
             // the slots of this pass; none (-1) for vertices of other tiles
             int slot[4] = {(int)(rec.z & 0xffffu), (int)(rec.z >> 16), (int)(rec.w & 0xffffu), (int)(rec.w >> 16)};
+            if (m1.w > kResidualSlots) slot[0] = k - m1.x - first;     // one node, item k in slot k
 #pragma unroll
-            for (int a = 0; a < 4; ++a) {
-                const int q = slot[a] - first;
-                slot[a] = (slot[a] != kNoSlot && q >= 0 && q < slots) ? q : -1;
-            }
+            for (int a = 0; a < 4; ++a) slot[a] = slot[a] >= 0 && slot[a] < slots ? slot[a] : -1;
             double g[4][3], det;
             {
                 double X[4][3], J[3][3];
