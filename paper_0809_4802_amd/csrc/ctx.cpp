@@ -804,7 +804,7 @@ extern "C" int vms_create(const vms_mesh_desc* mesh, const vms_create_opts* opts
                   "upload"));
     TRY(check_hip(c, hipMemcpy(c->ritems, ritems.data(), ritems.size() * sizeof(uint4), hipMemcpyHostToDevice), "upload"));
     TRY(check_hip(c, hipMemcpy(c->n2e_ptr, n2e_ptr.data(), (nn + 1) * sizeof(int32_t), hipMemcpyHostToDevice), "upload"));
-    TRY(check_hip(c, tile_kernels_configure(c), "configure tile kernels"));
+    TRY(check_hip(c, tile_kernels_configure(), "configure tile kernels"));
     TRY(check_hip(c, small_cycle_configure(), "configure cycle kernels"));
     TRY(check_hip(c, hipMemset(c->red, 0, sizeof(RedScratch)), "clear"));
     TRY(check_hip(c, hipMemset(c->gs, 0, sizeof(GmresState)), "clear"));

@@ -1339,8 +1339,9 @@ ResidualArgs residual_args(vms_ctx* c) {
 
 }  // namespace
 
-hipError_t tile_kernels_configure(vms_ctx* c) {
-    const int lds = (int)std::max(c->tile_lds, c->tile_lds_tr);
+// The attribute is the function's, so it is the bound over all contexts and not this context's need: a
+// context made later must not lower it for an earlier one.
+hipError_t tile_kernels_configure() {
     const void* fns[] = {
         (const void*)tile_kernel<double, double, true, kTileThreads>,
         (const void*)tile_kernel<float, MixedAcc, true, kTileThreads>,
@@ -1351,9 +1352,9 @@ hipError_t tile_kernels_configure(vms_ctx* c) {
         (const void*)tile_kernel<double, double, false, kTileThreadsDet>,
         (const void*)tile_kernel<float, MixedAcc, false, kTileThreadsDet>};
     hipError_t e = hipFuncSetAttribute((const void*)residual_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)c->rtile_lds[1]);
+                                       (int)kResidualLdsMax);
     for (const void* f : fns)
-        if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kTileLdsMax);
     return e;
 }
 

@@ -65,10 +65,18 @@ constexpr int kTileBlocksDet = VMS_TILE_BLOCKS_DET;     // blocks per one-wavefr
 // lanes of a wave, which update the same entry of different blocks, spread over the LDS
 // banks), rhs rows and residual rows.
 constexpr int kLdsBlockStride = VMS_LDS_BLOCK_STRIDE;
-__host__ __device__ inline size_t align16(size_t x) { return (x + 15) & ~size_t(15); }
-__host__ __device__ inline size_t tile_lds_bytes(int64_t nblocks, int64_t nnodes, size_t elt) {
+__host__ __device__ constexpr size_t align16(size_t x) { return (x + 15) & ~size_t(15); }
+__host__ __device__ constexpr size_t tile_lds_bytes(int64_t nblocks, int64_t nnodes, size_t elt) {
     return align16(nblocks * kLdsBlockStride * elt) + 2 * nnodes * 4 * 8;
 }
+// The most dynamic LDS that any context's tiles take, of the assembly (a row has at most kTileMaxNodes
+// blocks; a staged node three double4) and of the residual alone.
+constexpr size_t kTileLdsMax =
+    std::max(tile_lds_bytes(std::max(kTileBlocksFP64, kTileMaxNodes), kTileNodes, sizeof(double)),
+             kMixedAccSize == sizeof(double) ? size_t(0) : tile_lds_bytes(kTileBlocksFP32, kTileNodes, kMixedAccSize)) +
+    96 * size_t(kTileMaxNodes);
+constexpr size_t kResidualLdsMax = 32 * (size_t(kResidualSlots) + 3 * kTileMaxNodes);
+static_assert(kTileLdsMax <= 163840 - 1024 && kResidualLdsMax <= 163840 - 1024, "LDS of a CU");
 
 // Four-wide vector of a precision (one node's dofs, one block row).
 template <typename T>
@@ -385,7 +393,7 @@ struct PhaseScope {
 };
 
 // element kernels (element.hip)
-hipError_t tile_kernels_configure(vms_ctx* ctx);
+hipError_t tile_kernels_configure();
 // rglob (may be null) receives the assembled residual rows; every launch leaves the norm's
 // partial sums per tile in ctx->tile_part, which launch_norm_finalize adds into out.
 int launch_condense(vms_ctx* ctx, const double* u, const double* u_prev, const double* beta,
