@@ -2311,7 +2311,9 @@ int run_cycle(vms_ctx* c, T* r0, const TM* Minv, TX* x, double tol_abs, int m, i
     const bool sampled = c->prof_mask != 0 && c->prof_cycles++ % c->prof_every == 0;
     bool small = false;
     if constexpr (!split) {
-        small = c->n_nodes <= kSmallNodes && c->nb <= kSmallBlocks && j0 + steps <= kSmallSteps && !sampled;
+        // with the timers on, only in place of a graph: partial cycles are timed launch by launch
+        small = c->n_nodes <= kSmallNodes && c->nb <= kSmallBlocks && j0 + steps <= kSmallSteps && !sampled &&
+                (c->prof_mask == 0 || graphs);
         if (small)
             small_cycle_kernel<T><<<1, kSmallThreads, sizeof(SmallLds<T>), s>>>(
                 c->n_nodes, j0, j0 + steps, c->rowptr, c->colidx, AP, Az, c->dmask, V, c->gs, eps_dot);
