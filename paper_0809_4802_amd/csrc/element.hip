@@ -64,6 +64,12 @@ __device__ __forceinline__ void flag_element(const ElemArgs& a, int kind, int e)
 }
 
 // FP64 state of one element: geometry, nodal data and the derived fields.
+// The four entries of a node in a caller's array.
+__device__ __forceinline__ double4 caller_row(const double* p, size_t node) {
+    const auto v = reinterpret_cast<const CallerVec4<double>::type*>(p)[node];
+    return make_double4(v.x, v.y, v.z, v.w);
+}
+
 struct Elem {
     int4 t;
     double g[4][3];
@@ -109,7 +115,7 @@ __device__ __forceinline__ bool load_element(const ElemArgs& A, int e, Elem& E, 
         X[a][0] = x.x;
         X[a][1] = x.y;
         X[a][2] = x.z;
-        const double4 uu = reinterpret_cast<const double4*>(A.u)[nid[a]];
+        const double4 uu = caller_row(A.u, nid[a]);
         E.v[a][0] = uu.x;
         E.v[a][1] = uu.y;
         E.v[a][2] = uu.z;
@@ -172,7 +178,7 @@ __device__ __forceinline__ bool load_element(const ElemArgs& A, int e, Elem& E, 
     if (E.transient) {
 #pragma unroll
         for (int a = 0; a < 4; ++a) {
-            const double4 up = reinterpret_cast<const double4*>(A.u_prev)[nid[a]];
+            const double4 up = caller_row(A.u_prev, nid[a]);
             const double d[3] = {E.v[a][0] - up.x, E.v[a][1] - up.y, E.v[a][2] - up.z};
 #pragma unroll
             for (int i = 0; i < 3; ++i) {
@@ -324,15 +330,13 @@ __device__ __forceinline__ void coarse_block_row(const T G[3][3], const T ga[3],
     K[3] = r < 3 ? qv * ga[r] : T(0);
 }
 
-// Four adjacent values of a caller's array in one store that asks for no more than the alignment
-// of its entries.
 __device__ __forceinline__ void store4(float* p, const float (&v)[4]) {
-    typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
-    *reinterpret_cast<f32x4u*>(p) = f32x4u{v[0], v[1], v[2], v[3]};
+    using V4 = CallerVec4<float>::type;
+    *reinterpret_cast<V4*>(p) = V4{v[0], v[1], v[2], v[3]};
 }
 __device__ __forceinline__ void store4(double* p, const double (&v)[4]) {
-    typedef double f64x4u __attribute__((ext_vector_type(4), aligned(8)));
-    *reinterpret_cast<f64x4u*>(p) = f64x4u{v[0], v[1], v[2], v[3]};
+    using V4 = CallerVec4<double>::type;
+    *reinterpret_cast<V4*>(p) = V4{v[0], v[1], v[2], v[3]};
 }
 
 template <typename T>
@@ -556,8 +560,8 @@ __global__ __launch_bounds__(NT, VMS_TILE_WAVES_PER_SIMD) void tile_kernel(
     for (int i = threadIdx.x; i < ntn; i += blockDim.x) {
         const int g = ta.nodes[nbase + i];
         sx[i] = args.xyz4[g];
-        su[i] = reinterpret_cast<const double4*>(args.u)[g];
-        if (transient) sup[i] = reinterpret_cast<const double4*>(args.u_prev)[g];
+        su[i] = caller_row(args.u, g);
+        if (transient) sup[i] = caller_row(args.u_prev, g);
     }
     // the write-out's masks, fetched now so that their latency hides behind the items: the
     // first two blocks of this thread (block masks) and its rhs entry's node (Dirichlet bits)
@@ -907,13 +911,13 @@ __global__ __launch_bounds__(kResThreads, 3) void residual_kernel(ElemArgs args,
     const double nu = args.nu, inv_dt = transient ? args.inv_dt : 0.0;
     for (int i = threadIdx.x; i < ntn; i += kResThreads) {
         const int g = ta.nodes[m0_.z + i];
-        const double4 u = reinterpret_cast<const double4*>(args.u)[g];
+        const double4 u = caller_row(args.u, g);
         sx[i] = args.xyz4[g];
         su[i] = u;
         if (extra) {
             double q[3] = {0.0, 0.0, 0.0};
             if (transient) {
-                const double4 up = reinterpret_cast<const double4*>(args.u_prev)[g];
+                const double4 up = caller_row(args.u_prev, g);
                 q[0] = inv_dt * (u.x - up.x);
                 q[1] = inv_dt * (u.y - up.y);
                 q[2] = inv_dt * (u.z - up.z);
@@ -1221,7 +1225,7 @@ __global__ __launch_bounds__(kBlock) void recover_kernel(ElemArgs args, const do
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
         const uint32_t dm = args.dmask[nid[b]];
-        const double4 d4 = reinterpret_cast<const double4*>(du)[nid[b]];
+        const double4 d4 = caller_row(du, nid[b]);
         const double dd[4] = {(dm & 1u) ? 0.0 : d4.x, (dm & 2u) ? 0.0 : d4.y, (dm & 4u) ? 0.0 : d4.z,
                               (dm & 8u) ? 0.0 : d4.w};
         double Kfc[3][4];

@@ -294,7 +294,8 @@ __global__ __launch_bounds__(kBlock) void spmv_kernel(int n_rows, const int32_t*
     // row bounds, which the block loads wait for anyway
     const int skip = ROT ? gs->done : 0;
     constexpr int Q = kSpmvLanes / 4;
-    using VA = typename Vec4<TA>::type;
+    // the blocks of A P are the context's, the others may be a caller's
+    using VA = typename std::conditional_t<ROT && MODE == 2, Vec4<TA>, CallerVec4<TA>>::type;
     const int tid = slot * blockDim.x + threadIdx.x;
     const int row = tid / kSpmvLanes, sub = tid % kSpmvLanes;
     const int q = sub >> 2, r = sub & 3;
@@ -749,7 +750,7 @@ __global__ void ap_blocks_kernel(int64_t nb, const int32_t* __restrict__ colidx,
     const int r = (int)(tid & 3);
     if (k >= nb) return;
     using V4 = typename Vec4<T>::type;
-    const V4 a = *reinterpret_cast<const V4*>(A + k * 16 + r * 4);
+    const auto a = *reinterpret_cast<const typename CallerVec4<T>::type*>(A + k * 16 + r * 4);
     const T* M = Minv + (size_t)colidx[k] * 16;
     T o[4];
 #pragma unroll
@@ -778,12 +779,13 @@ __global__ __launch_bounds__(kBlock) void ap_rows_kernel(int n_rows, const int32
     const bool row_free = !(dmask[row] & 8u);
     double acc = 0.0;
     for (int kb = rowptr[row]; kb < k1; kb += kApAhead) {
-        V4 a[kApAhead], m[kApAhead];
+        typename CallerVec4<T>::type a[kApAhead];
+        V4 m[kApAhead];
         bool col_free[kApAhead];
 #pragma unroll
         for (int u = 0; u < kApAhead; ++u) {
             const int k = min(kb + u, k1 - 1), col = colidx[k];
-            a[u] = *reinterpret_cast<const V4*>(A + (size_t)k * 16 + r * 4);
+            a[u] = *reinterpret_cast<const typename CallerVec4<T>::type*>(A + (size_t)k * 16 + r * 4);
             col_free[u] = !(dmask[col] & 8u);
             m[u] = *reinterpret_cast<const V4*>(Minv + (size_t)col * 16 + r * 4);
         }

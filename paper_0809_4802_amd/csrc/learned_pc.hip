@@ -44,7 +44,7 @@ __global__ __launch_bounds__(kBlock) void features_kernel(int n, const int32_t* 
                                                           const TA* __restrict__ A, const uint8_t* __restrict__ dmask,
                                                           float* __restrict__ feats, float* __restrict__ dinv,
                                                           int32_t* flags) {
-    using V4 = typename Vec4<TA>::type;
+    using V4 = typename CallerVec4<TA>::type;
     const int tid = blockIdx.x * blockDim.x + threadIdx.x;
     const int i = tid >> 2, r = tid & 3;
     if (i >= n) return;                         // the four lanes of a quad agree
@@ -97,14 +97,13 @@ __global__ __launch_bounds__(kBlock) void features_kernel(int n, const int32_t* 
     *reinterpret_cast<float4*>(dinv + (size_t)i * 16 + 4 * r) = make_float4(op[0], op[1], op[2], op[3]);
 }
 
-// Four consecutive values of a caller's array: one wide load that asks for no more than the
-// alignment of its entries.
+// Four consecutive values of a caller's array, as floats.
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
-typedef double f64x4u __attribute__((ext_vector_type(4), aligned(8)));
-__device__ __forceinline__ f32x4 load4(const float* p) { return *reinterpret_cast<const f32x4u*>(p); }
+__device__ __forceinline__ f32x4 load4(const float* p) {
+    return *reinterpret_cast<const CallerVec4<float>::type*>(p);
+}
 __device__ __forceinline__ f32x4 load4(const double* p) {
-    const f64x4u v = *reinterpret_cast<const f64x4u*>(p);
+    const auto v = *reinterpret_cast<const CallerVec4<double>::type*>(p);
     return f32x4{float(v.x), float(v.y), float(v.z), float(v.w)};
 }
 
@@ -198,7 +197,7 @@ __global__ __launch_bounds__(kBlock) void forward_kernel(int n, const float* __r
             for (int q = 0; q < 4; ++q) o[q] += dr[k] * mk[q];
         }
         if (live) {
-            using V4 = typename Vec4<TM>::type;
+            using V4 = typename CallerVec4<TM>::type;
             *reinterpret_cast<V4*>(P + i0 * 16 + 4 * g) = V4{TM(o[0]), TM(o[1]), TM(o[2]), TM(o[3])};
             if (!(isfinite(o[0]) && isfinite(o[1]) && isfinite(o[2]) && isfinite(o[3]))) atomicAdd(&flags[3], 1);
         }

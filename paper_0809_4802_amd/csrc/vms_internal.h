@@ -90,6 +90,19 @@ struct Vec4<float> {
     using type = float4;
 };
 
+// The same in a caller's array, which is only promised to be aligned to its entries: accessed in one wide
+// load or store that asks for no more.
+template <typename T>
+struct CallerVec4;
+template <>
+struct CallerVec4<double> {
+    typedef double type __attribute__((ext_vector_type(4), aligned(8)));
+};
+template <>
+struct CallerVec4<float> {
+    typedef float type __attribute__((ext_vector_type(4), aligned(4)));
+};
+
 // Lane exchanges of a double by DPP (two 32-bit moves; no LDS round trip).  CTRL: a
 // quad_perm pattern, or 0x140 (row_mirror: lane i <-> 15 - i in a row of 16), 0x141
 // (row_half_mirror: lane i <-> 7 - i in a group of 8) and 0x138 (a shift by one lane).  Every lane of the wave must be active.
