@@ -57,6 +57,15 @@ __device__ __forceinline__ void report_progress(GmresState* gs, int k, int done)
     report_progress(gs->progress, gs->gen, k, done);
 }
 
+// The done flag, where a workgroup of the same launch may set it (columns_rotate beside the rows of an
+// SpMV or the last dots' sums): whoever misses it does work that no later launch reads.
+__device__ __forceinline__ int ld_done(const GmresState* gs) {
+    return __hip_atomic_load(&gs->done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void set_done(GmresState* gs) {
+    __hip_atomic_store(&gs->done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // What the end of a column needs from the cycle state, loaded ahead.
 struct GivensCtx {
     double tol_abs;
@@ -118,7 +127,7 @@ __device__ int givens_column(int jc, const double* col, double* cl, double* sl, 
         gs->g[jc] = cs * gj;
         gs->gin[jc + 1] = gnext;
         gs->k = jc + 1;
-        if (stop) gs->done = 1;
+        if (stop) set_done(gs);
         if (stop || gc.report) report_progress(gc.progress, gc.gen, jc + 1, stop);
     }
     if (next) *next = gnext;
@@ -198,7 +207,7 @@ __device__ void columns_rotate(int j, int dk, GmresState* gs, int report, bool t
             if (lane == 0) {
                 gs->gin[dk] = dr_x0;
                 gs->k = dk;
-                if (st) gs->done = 1;
+                if (st) set_done(gs);
                 if (st || gc.report) report_progress(gc.progress, gc.gen, dk, st);
             }
         } else if (j > 0) {
@@ -206,7 +215,7 @@ __device__ void columns_rotate(int j, int dk, GmresState* gs, int report, bool t
             if (!(rho > 0.0)) {
                 st = 1;                      // u_j vanished: column j-1 closes the cycle
                 if (lane == 0) {
-                    gs->done = 1;
+                    set_done(gs);
                     report_progress(gc.progress, gc.gen, j, 1);
                 }
             }
@@ -229,7 +238,7 @@ __device__ void columns_rotate(int j, int dk, GmresState* gs, int report, bool t
     if (wave == 0) {
         givens_column(j, Hc, cl, sl, gs->gin[j], Rl, gc, gs, dk, dr_x0);
         if (lane == 0) {
-            gs->done = 1;
+            set_done(gs);
             report_progress(gc.progress, gc.gen, j + 1, 1);
         }
     }
@@ -292,7 +301,7 @@ __global__ __launch_bounds__(kBlock) void spmv_kernel(int n_rows, const int32_t*
     }
     // a finished GMRES cycle reads no blocks and stores nothing; the flag is read alongside the
     // row bounds, which the block loads wait for anyway
-    const int skip = ROT ? gs->done : 0;
+    const int skip = ROT ? ld_done(gs) : 0;
     constexpr int Q = kSpmvLanes / 4;
     // the blocks of A P are the context's, the others may be a caller's
     using VA = typename std::conditional_t<ROT && MODE == 2, Vec4<TA>, CallerVec4<TA>>::type;
@@ -1145,7 +1154,7 @@ __global__ __launch_bounds__(kRedThreads) void reduce_kernel(int j, int nchunks,
     }
     if (tid < j) svl[tid] = gs->svs[tid];
     if (tid == 0) {
-        flags[0] = gs->done;
+        flags[0] = ld_done(gs);
         flags[1] = gs->reorth;
         su_l = gs->su;
     }
@@ -1671,7 +1680,7 @@ __device__ void small_rotate(int j, int dk, SmallLds<T>& L, double rho, double h
         if (lane == 0) {
             gs->gin[dk] = x0;
             gs->k = dk;
-            if (st) gs->done = 1;
+            if (st) set_done(gs);
             if (st || gc.report) report_progress(gc.progress, gc.gen, dk, st);
         }
     } else if (j > 0) {
@@ -1679,7 +1688,7 @@ __device__ void small_rotate(int j, int dk, SmallLds<T>& L, double rho, double h
         if (!(rho > 0.0)) {
             st = 1;                          // u_j vanished: column j-1 closes the cycle
             if (lane == 0) {
-                gs->done = 1;
+                set_done(gs);
                 report_progress(gc.progress, gc.gen, j, 1);
             }
         }
@@ -1691,7 +1700,7 @@ __device__ void small_rotate(int j, int dk, SmallLds<T>& L, double rho, double h
         rotate(j);
         st = 1;
         if (lane == 0) {
-            gs->done = 1;
+            set_done(gs);
             report_progress(gc.progress, gc.gen, j + 1, 1);
         }
     }
