@@ -360,21 +360,23 @@ enum {
     VMS_PH_PCSETUP = 3,        /* preconditioner block setup                              */
     VMS_PH_PCAPPLY = 4,        /* A P formed once per solve (the Arnoldi SpMV applies P);
                                   with basis_fp64 on a mixed ctx, P applied at every step  */
-    VMS_PH_SPMV = 5,           /* block-CSR SpMV with A P in the Arnoldi step             */
+    VMS_PH_SPMV = 5,           /* block-CSR SpMV with A P in the Arnoldi step, with the Givens
+                                  rotation of the step before in one of its workgroups      */
     VMS_PH_DOTS = 6,           /* Gram-Schmidt dot products (Q^T u, Q^T w, norms)         */
     VMS_PH_UPDATE = 7,         /* Gram-Schmidt update (q_j and the next vector), with the
                                   step's sums of the dot partials and the Hessenberg
-                                  columns and Givens rotations in one of its workgroups     */
+                                  columns in one of its workgroups                          */
     VMS_PH_FILL = 8,           /* zero fill of the assembled outputs                      */
     VMS_NPHASES = 9
 };
 /* phase_mask: bit p enables phase p (VMS_PROFILE_ALL: every phase), 0 disables.
  * every >= 1: only every every-th launch of an enabled phase is timed (a sample;
  * the accumulators then cover the sampled launches only).  A full GMRES restart
- * cycle is replayed from a recorded HIP graph, and events cannot time launches
- * inside a graph: there the sample is every every-th cycle, launched directly,
- * with each of its launches of an enabled phase timed (the environment variable
- * VMS_CYCLE_GRAPHS=0 turns the graphs off).  Each call clears the accumulators.
+ * cycle is replayed from a recorded HIP graph (on systems of at most 128 nodes
+ * and cycles of at most 58 columns it is one launch instead), and events cannot
+ * time the steps inside: there the sample is every every-th cycle, launched step
+ * by step, with each of its launches of an enabled phase timed (the environment
+ * variable VMS_CYCLE_GRAPHS=0 turns the graphs off).  Each call clears the accumulators.
  * Timing one phase, sparsely, keeps the event cost off the rest. */
 #define VMS_PROFILE_ALL ((1u << VMS_NPHASES) - 1u)
 int vms_profile(vms_ctx* ctx, uint32_t phase_mask, int32_t every);

@@ -11,10 +11,11 @@
 // GPU layout: all vectors are node-interleaved (4 n_nodes entries, dofs
 // (vx, vy, vz, p) of a node adjacent) so that a 4x4 block multiplies one
 // 32-byte (FP64) or 16-byte (FP32) segment.  The Hessenberg matrix, the Givens
-// rotations and the residual estimate live in device memory and are updated
-// by single-workgroup reduction kernels, so an Arnoldi step is a fixed
-// sequence of launches with no host round trip; the host looks at the
-// convergence flag only every few steps.
+// rotations and the residual estimate live in device memory, updated by single
+// workgroups beside the streaming ones, so an Arnoldi step is a fixed
+// sequence of launches with no host round trip.  The rotations publish the
+// progress in a host-mapped word: after every column where the host issues the
+// steps, at the stop and at the end in recorded cycles and those of small systems.
 #include <cstdio>
 #include <cstdlib>
 #include <cstddef>
@@ -673,7 +674,6 @@ __global__ __launch_bounds__(kBlock) void cycle_v0_kernel(int n, const T* __rest
         gs->k = 0;
         gs->tol_abs = tol_abs;
         gs->done = (nrm <= tol_abs || !(nrm > 0.0)) ? 1 : 0;
-        gs->norm = nrm;
         gs->reorth = reorth;
         gs->gen = gen;
         gs->A = A;
@@ -1480,11 +1480,12 @@ __global__ __launch_bounds__(kBlock, sizeof(T) * R > 8 ? 4 : 5) void update_fuse
 // at a barrier.  Twelve waves: with sixteen (128 registers) these loads spill and a step takes 0.6 us
 // more, without them it takes 0.6 us more too; with all waves taking part in everything, 1.8.
 // A step of a 125-node FP64 system takes 9.0 us against 11.9 by launches, and an inexact-Newton solve
-// on it 1386 us against 1862.  With the cycle's ends, us per step at restart 50, FP64 and mixed: 27
-// nodes 6.2 and 6.5, 64 nodes 7.2 and 6.9 (by launches 12.2 and 12.2), 125 nodes 9.7 and 8.9 (12.2 and
-// 12.4); with sixteen waves 210 nodes took 14.8 and 13.4 (12.5 and 12.4): from about 150 nodes on, what
-// one CU reads of matrix and basis takes longer than the launches.  Keeping the first vectors in
-// LDS too gains nothing.  Up to 58 columns H stays in LDS, a row per lane.
+// on it 1386 us against 1862.  With the cycle's ends, us per step at restart 50, FP64 and mixed, against
+// launches: 27 nodes 6.2 and 6.2, 64 nodes 7.2 and 6.7 (12.5 and 12.6), 125 nodes 9.7 and 8.7 (12.8 and
+// 12.7), 150 nodes 11.4 and 10.4 (12.8 and 12.7), 175 nodes 11.8 and 10.5 (13.0 and 12.8).  The line lies
+// at two 64-node parts of a dot product; the launches are not yet ahead at 176 nodes, the most whose rows
+// these waves hold, and sixteen waves at 210 nodes (14.8 and 13.4 against 12.5 and 12.4) are behind.
+// Keeping the first vectors in LDS too gains nothing.  Up to 58 columns H stays in LDS, a row per lane.
 // Every sum is formed in the order of the three kernels (a wave takes a slot's 64-node parts in
 // turn) and with the same roundings, so that a cycle gives the same bits on either path.
 constexpr int kSmallNodes = 128;
@@ -2110,7 +2111,6 @@ __global__ void axpy64_kernel(int n, double alpha, const T* __restrict__ d, doub
 static_assert(VMS_RED_GRID_MAX <= kRedBlocks, "reduction grid exceeds the partials");
 inline int red_grid(int64_t n) { return std::max(1, std::min(VMS_RED_GRID_MAX, grid_for(n))); }
 
-// Reads a device double with a stream sync.
 // Launches the norm of r (n entries) into mapped scalar k with a fresh tag.
 template <typename T>
 void launch_norm(vms_ctx* c, int n, const T* r, int k, hipStream_t s) {

@@ -37,7 +37,7 @@ constexpr int kTileNodes = 64;           // max nodes owned by one assembly tile
 constexpr int kResidualThreads = 256;     // threads per tile
 constexpr int kResidualNodes = 32;        // max nodes owned by one
 constexpr int kResidualSlots = 2048;      // max element rows staged by one (64 KB)
-constexpr int kNoSlot = 0xffff;           // slot of a vertex that the tile does not own
+constexpr int kNoSlot = 0xffff;           // slot of a vertex that the tile does not own (or does not number)
 constexpr int kTileMaxNodes = 255;       // max nodes staged by one tile (8-bit local numbers)
 #ifndef VMS_TILE_BLOCKS_FP64
 #define VMS_TILE_BLOCKS_FP64 280
@@ -58,8 +58,8 @@ constexpr int kTileMaxNodes = 255;       // max nodes staged by one tile (8-bit 
 using MixedAcc = std::conditional_t<VMS_MIXED_LDS_FP64 != 0, double, float>;
 constexpr size_t kMixedAccSize = sizeof(MixedAcc);
 constexpr int kTileBlocksFP64 = VMS_TILE_BLOCKS_FP64;   // max 4x4 blocks staged in LDS per tile (FP64 values)
-constexpr int kTileBlocksFP32 = VMS_TILE_BLOCKS_FP32;
-constexpr int kTileBlocksDet = VMS_TILE_BLOCKS_DET;     // blocks per one-wavefront tile (deterministic contexts)   // same for FP32 values (LDS per tile stays under 64 KB)
+constexpr int kTileBlocksFP32 = VMS_TILE_BLOCKS_FP32;   // same for FP32 values
+constexpr int kTileBlocksDet = VMS_TILE_BLOCKS_DET;     // blocks per one-wavefront tile (deterministic contexts)
 
 // Dynamic LDS of a tile: block values (each 4x4 block padded to 17 entries so that the
 // lanes of a wave, which update the same entry of different blocks, spread over the LDS
@@ -205,7 +205,6 @@ struct GmresState {
     double svs[kMaxRestart + 1];   // free-pressure sum of every final basis vector
     double tol_abs;                // stop when |g[k]| <= tol_abs
     double beta;                   // norm of the cycle's initial residual
-    double norm;                   // scratch: a finished reduction
     double kappa;                  // coarse pressure correction: 1 / (sum of free p-p entries), 0 = off
     double su;                     // sum of the free pressure entries of u_j
     double rho;                    // norm of u_j after its second pass
@@ -216,7 +215,6 @@ struct GmresState {
     int k;                         // Arnoldi steps completed in this cycle
     int done;                      // 0 while the cycle runs; 1 once it stopped (converged or
                                    // breakdown), later kernels idle
-    unsigned counter;              // arrival counter of last-block reductions
     unsigned gen;                  // cycle number (host-assigned) reported with the progress word
     uint64_t* progress;            // host-mapped progress word: gen << 32 | k << 1 | done
     const void* A;                 // the cycle's matrix, where P and A are applied one after the other
@@ -307,7 +305,7 @@ struct vms_ctx {
     void* Az = nullptr;              // [4 n_nodes] A z, z = 1 on every free pressure dof
     void* pp = nullptr;              // [nb] the entries of A that couple two free pressures (condensed systems)
     double* x64 = nullptr;           // [4 n_nodes] the iterate before a deflated GMRES cycle
-    // mixed context, GMRES with an FP64 basis: its basis, w and z (allocated on first use)
+    // mixed context created with basis_fp64: the FP64 basis, w and z
     double* V64 = nullptr;           // [(max_restart + 1)][4 n_nodes]
     double* w64 = nullptr;
     double* z64 = nullptr;
@@ -318,9 +316,9 @@ struct vms_ctx {
     // that the host can follow it without synchronising the stream
     uint64_t* progress_host = nullptr;
     uint64_t* progress_dev = nullptr;
-    // GMRES norms the host reads after a stream synchronisation (the true residual, the inner
-    // residual, the right-hand side), written by the device into the same pinned allocation,
-    // 64 bytes after the progress word: no copy kernel per read
+    // GMRES norms that the host reads (the true residual, the right-hand side, the inner residual),
+    // written by the device into the same pinned allocation, 64 bytes after the progress word, and
+    // then their tags, which the host polls for: no copy kernel and no stream synchronisation per read
     double* scal_host = nullptr;
     double* scal_dev = nullptr;
     uint64_t scal_seq = 0;               // tag of the last norm launched (words 1 .. 3 of the progress page)
